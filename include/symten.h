@@ -535,10 +535,11 @@ int ctm_env_set(ctm_env_t env, int k, symten_t t);
  * singular triplets of one matrix; ctm_move takes them from a symmetric
  * eigenproblem (the Gram matrix Y Y^T, or the Jordan-Wielandt matrix
  * [[0, Y], [Y^T, 0]] in FP64 moves), solved by these kernels: Householder
- * tridiagonalisation with the rows of each matrix held in the LDS of its own
- * workgroups (one exchange between them per column), every eigenvalue by
- * multisection of Sturm counts, eigenvectors by inverse iteration (close
- * eigenvalues reorthogonalised), back-transformation through the reflectors.
+ * tridiagonalisation with the rows of each matrix held in the registers of its
+ * own workgroups (one exchange between them per column), every eigenvalue by
+ * multisection of Sturm counts, eigenvectors from the twisted factorisation
+ * (close eigenvalues reorthogonalised, degenerate ones by inverse iteration),
+ * back-transformation through the reflectors.
  * count problems; A[i]: device, n[i] x n[i], column-major with leading
  * dimension lda[i] >= n[i], symmetric with both triangles stored, read only
  * (row i is read as column i); w[i]: device,

@@ -7,28 +7,26 @@
 //   1. Householder tridiagonalisation T = Q^T A Q (Q = H_0 ... H_{n-3},
 //      H_k = I - tau_k v_k v_k^T).  The rows of a matrix are spread over the
 //      workgroups of one job, cyclically (row i on workgroup i mod G), and
-//      stay in LDS for the whole reduction.  The rank-2 update of column k,
-//      A -= v w^T + w v^T, is applied lazily: each workgroup applies it to
-//      its own rows in the pass of column k+1 that also forms p = tau A v, so
-//      one column costs one exchange between the job's workgroups (its p
-//      slices and the next row, through global memory, then a barrier on an
-//      atomic counter).  The jobs of a launch sit on disjoint workgroups,
-//      each job on the workgroups of one XCD where it fits.
+//      stay in registers for the whole reduction.  The rank-2 update of
+//      column k, A -= v w^T + w v^T, is applied lazily: each workgroup applies
+//      it to its own rows in the pass of column k+1 that also forms
+//      p = tau A v, so one column costs one exchange between the job's
+//      workgroups (its p slices and the next row, through global memory).
+//      The jobs of a launch sit on disjoint workgroups, each job on the
+//      workgroups of one XCD where it fits.
 //   2. All eigenvalues by multisection: one wavefront per eigenvalue, its 64
 //      lanes evaluating Sturm counts of T at 64 points of the current
 //      interval, about 9 passes to 2 ulp.
 //   3. Eigenvectors of T for the kept eigenvalues from the twisted
-//      factorisation of T - lam I (two recurrences, no iteration; for an
-//      eigenvalue apart from the others both run at once).  Eigenvalues
-//      closer than 1e-3 ||T|| form a cluster, done in order by one
-//      wavefront: each vector has the earlier ones projected out, and if
-//      less than half of it is left (a degenerate value) it comes from
-//      inverse iteration instead (tridiagonal LU with partial pivoting, two
-//      solves from a fixed pseudo-random start, reorthogonalised in every
-//      solve).
-//   4. Back-transformation z <- Q z through the stored reflectors, one
-//      vector per workgroup held in LDS, one block-wide reduction per
-//      reflector, the reflectors streamed through LDS in chunks.
+//      factorisation of T - lam I (two recurrences at once, no iteration), a
+//      workgroup each.  Eigenvalues closer than 1e-3 ||T|| form a cluster,
+//      gone through in order by one wavefront: each vector has the earlier
+//      ones projected out, and if less than half of it is left (a degenerate
+//      value) it comes from inverse iteration instead (tridiagonal LU with
+//      partial pivoting, two solves from a fixed pseudo-random start,
+//      reorthogonalised in every solve).
+//   4. Back-transformation z <- Q z through the stored reflectors, a vector
+//      in the registers of one wavefront (four above n = 704).
 // The matrix is scaled by a power of two (exact) so that its largest entry
 // is in [1, 2); eigenvalues are returned unscaled.
 #include <algorithm>
@@ -47,20 +45,18 @@ namespace {
 
 constexpr int kEigThreads = 256;                 // bisection: four eigenvalues per workgroup
 constexpr int kEigWaves = kEigThreads / 64;
-// Tridiagonalisation and back-transformation: one workgroup per compute unit
-// (their LDS), so 1024 threads give each SIMD four waves to hide LDS and
-// FP64 latency with.
-constexpr int kTriThreads = 1024;
-constexpr int kTriWaves = kTriThreads / 64;
-constexpr int kSpinLimit = 1 << 21;     // polls of a barrier before it gives up
+constexpr int kSpinLimit = 1 << 21;     // polls of an exchange before it gives up
+
+__host__ __device__ inline int v_stride(int n) { return (n + 63) & ~63; }
 
 struct TridJob {
     const double* A;                   // n x n, column-major (ld lda), both triangles
-    int n, lda, G, R;                  // order, leading dim, workgroups, LDS rows per workgroup
-    double *d, *e, *tau, *V, *scale;   // outputs (scaled by *scale)
-    double* xbuf;                      // exchange area (xbuf_doubles)
-    int* counter;                      // barrier counter (zero at launch)
-    int* status;                       // set to 1 if a barrier gave up
+    int n, lda, G;                     // order, leading dim, workgroups
+    double *d, *e, *tau, *V, *scale;   // outputs (scaled by *scale); V: reflector k in row k, stride v_stride(n),
+                                       // zeros outside its entries k+1 .. n-1
+    double* xbuf;                      // exchange area (xbuf_doubles), filled with kEmpty
+    int* status;                       // set to 1 if an exchange gave up
+    int variant;                       // index into kTridVariants
 };
 
 // Wavefront reductions on DPP lane moves (no LDS round trips): within
@@ -126,237 +122,524 @@ __device__ double block_max(double x, double* red) {
     return s;
 }
 
-// Values exchanged between the workgroups of a job are written and read
-// with relaxed agent-scope atomic accesses, which bypass the caches that are
-// not coherent across compute units, so the barrier needs no cache-wide
-// write-back or invalidation: each wave waits until its stores have
-// completed, then one thread per workgroup adds to the job's counter and
-// polls it.  The poll is bounded: after kSpinLimit polls the workgroup
-// records the failure and stops waiting at this and every later barrier, so
-// the launch always ends.
-__device__ inline void st_x(double* p, double v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Sums of four per-lane values over the wavefront: the rows share the two
+// widest exchange steps (v_permlane32_swap / v_permlane16_swap trade halves
+// between two registers, so adding the pair sums both rows at once), then
+// each 16-lane group finishes one row with DPP moves: 21 instructions against
+// 72 for four separate sums.  Lane group q = lane / 16 gets the sum of row
+// reduced_row(q).
+constexpr int kRowGroup = 4, kColGroup = 3;
+template <bool W32>
+__device__ inline void swap_halves(double& x, double& y) {
+    const uint64_t a = __builtin_bit_cast(uint64_t, x), b = __builtin_bit_cast(uint64_t, y);
+    uint64_t l, h;
+    if constexpr (W32) {
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+        l = ((uint64_t)(uint32_t)hi[0] << 32) | (uint32_t)lo[0];
+        h = ((uint64_t)(uint32_t)hi[1] << 32) | (uint32_t)lo[1];
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+        l = ((uint64_t)(uint32_t)hi[0] << 32) | (uint32_t)lo[0];
+        h = ((uint64_t)(uint32_t)hi[1] << 32) | (uint32_t)lo[1];
+    }
+    x = __builtin_bit_cast(double, l);
+    y = __builtin_bit_cast(double, h);
 }
-__device__ inline double ld_x(const double* p) {
-    return __hip_atomic_load(const_cast<double*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ inline double four_sums(const double (&x)[kRowGroup]) {
+    double y0 = x[0], t0 = x[1], y1 = x[2], t1 = x[3];
+    swap_halves<true>(y0, t0);
+    swap_halves<true>(y1, t1);
+    y0 += t0;   // lanes 0..31: row 0, 32..63: row 1
+    y1 += t1;
+    swap_halves<false>(y0, y1);
+    double z = y0 + y1;   // 16-lane groups: rows 0, 2, 1, 3
+    z += dpp_move<0xB1, 0xF>(z);
+    z += dpp_move<0x4E, 0xF>(z);
+    z += dpp_move<0x141, 0xF>(z);
+    z += dpp_move<0x140, 0xF>(z);
+    return z;
 }
-__device__ void job_barrier(int* counter, int& epoch, int G, int* failed) {
-    ++epoch;
-    __builtin_amdgcn_s_waitcnt(0);   // this wave's exchange stores have completed
-    __syncthreads();
-    if (threadIdx.x == 0 && !*failed) {
-        __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int target = epoch * G;
-        int polls = 0;
-        while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            __builtin_amdgcn_s_sleep(1);
-            if (++polls > kSpinLimit) {
-                *failed = 1;
-                break;
+__device__ inline int reduced_row(int group) { return 2 * (group & 1) + (group >> 1); }
+
+// Exchange between the workgroups of a job.  Every value has a slot of its
+// own in an area filled with kEmpty, written once; readers poll the slots
+// themselves, so there is no counter, no barrier between workgroups and no
+// wait for a store.  kEmpty is a signalling NaN: every exchanged value is the
+// result of an FP64 operation, which never is one.  Readers use agent-scope
+// loads, which are served by L2 and not by a compute unit's L1.  While all
+// workgroups of a job run on one XCD (same XCC_ID register), a store that
+// reaches that XCD's L2 is enough; otherwise stores are agent-scope too.
+// Measured per exchange of 696 values among 32 workgroups of one XCD: 1.0 us
+// (1.6 us with an atomic counter and plain loads); 3136 values among 128
+// workgroups over all XCDs: 2.1 us (3.5 us with the counter).  Polls are
+// bounded: after kSpinLimit of them the workgroup records the failure and
+// waits no more, so the launch always ends.
+constexpr uint64_t kEmpty = 0xFFF4DEADBEEF5A5Aull;
+// The job's pointers come out of memory, so their address space is stated:
+// flat accesses would count as LDS accesses too, and every LDS wait would wait
+// for the exchange.  32-bit offsets from a wavefront-uniform base keep an
+// address in one register.
+#ifdef __HIP_DEVICE_COMPILE__
+#define GLOBAL_MEM __attribute__((address_space(1)))
+#define LOCAL_MEM __attribute__((address_space(3)))
+#else
+#define GLOBAL_MEM
+#define LOCAL_MEM
+#endif
+typedef GLOBAL_MEM uint64_t gu64;
+typedef GLOBAL_MEM double gf64;
+template <class P>
+__device__ inline P* at8(P* base, uint32_t idx) {
+    return (P*)((GLOBAL_MEM char*)base + 8 * idx);
+}
+template <bool LOCAL>
+__device__ inline void put_x(gu64* base, uint32_t idx, double v) {
+    __hip_atomic_store(at8(base, idx), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED,
+                       LOCAL ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void put_x(gu64* base, uint32_t idx, double v, bool local) {
+    if (local) put_x<true>(base, idx, v);
+    else put_x<false>(base, idx, v);
+}
+__device__ inline uint64_t get_x(gu64* base, uint32_t idx) {
+    return __hip_atomic_load(at8(base, idx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// 1/x and 1/sqrt(x) of a normal, positive x: the hardware's approximation and
+// two Newton steps
+__device__ inline double rcp_newton(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+__device__ inline double rsq_newton(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+// Householder vector of a column with leading entry alpha and squared norm
+// xn2 of the rest: beta, tau and the factor of the rest.  A rest below
+// 2^-480 of the scaled matrix counts as zero.
+__device__ inline void householder(double alpha, double xn2, double& beta, double& tau, double& scal) {
+    beta = alpha;
+    tau = scal = 0.0;
+    if (xn2 > 0x1p-960) {
+        const double h2 = fma(alpha, alpha, xn2), y = rsq_newton(h2);
+        double h = h2 * y;
+        h = fma(0.5 * y, fma(-h, h, h2), h);
+        beta = -copysign(h, alpha);
+        tau = fma(fabs(alpha), y, 1.0);                       // (beta - alpha) / beta
+        scal = copysign(rcp_newton(fabs(alpha) + h), alpha);  // 1 / (alpha - beta)
+    }
+}
+__global__ void fill_empty_kernel(uint64_t* __restrict__ d, int64_t n) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        d[i] = kEmpty;
+}
+
+// Step 1 for one workgroup g of a job.  The matrix stays in registers: the
+// NW waves form WR row groups of WC waves; wave (wr, wc) holds, for its RW
+// rows i = g + G (wr + WR s), the columns j = lane + 64 (wc + WC c), c < CW
+// (the last RL rows in LDS where the registers do not take them all), and the
+// entries of v and w at those columns.  Thread tid owns the columns
+// j = tid + T q of the column vectors.  Per column k:
+//  (a) the Householder vector from the column, each thread its entries, and
+//      {w, v} to every wave through LDS;
+//  (b) one pass over the rows i > k that applies the pending rank-2 update of
+//      column k-1 and forms p_i = tau (row_i . v); the owner of row k+1
+//      publishes it;
+//  (c) every thread polls its entries of p and of row k+1;
+//  (d) w = p - (tau/2)(p.v) v is the pending update, and row k+1 with it the
+//      next column.
+// It is bound by this serial chain, not by arithmetic or memory.  At n = 696
+// (29 workgroups of one XCD) a column takes 2.5 us: 0.7 us of exchange, 0.5 us
+// for the pass, the rest the four LDS rounds (two sums, two broadcasts); the
+// reduction 1.74 ms.  With the rows in LDS and an atomic counter as barrier
+// the pass read and wrote 150 KB of LDS per column, and the reduction took
+// 3.5 ms.  At n = 2624 (175 workgroups over all XCDs) 6 us per column, 16 ms;
+// there the exchange is bound by the reads that pass the L2s (1.4 TB/s), so
+// slots of finished columns are not polled (20 ms with them).  Four waves per
+// workgroup where the registers allow it (n <= 704): eight read the {w, v}
+// pairs twice as often.
+template <int T, int WC, int CW, int RW, int RL = 0>
+struct Trid {
+    static constexpr int NW = T / 64, WR = NW / WC, R = RW * WR;
+    static constexpr int RR = RW - RL;                  // rows of a wave in registers; RL in LDS
+    static constexpr int NP = 64 * WC * CW;             // columns, padded
+    static constexpr int PQ = (CW + WR - 1) / WR;       // columns exchanged per thread
+    static constexpr int NQ = T * PQ;                   // exchanged columns, padded to threads
+    static constexpr bool SOLO = R >= NP;               // the job has one workgroup: no exchange
+    // LDS, in doubles: p (one workgroup: the raw p and row k+1 too) and the
+    // next column; {v, w} of the own rows (and a slot per lane for the rest);
+    // {w, v} of all columns; sums and partial row sums
+    static constexpr int LP = 0, LX = LP + NQ, LOWN = LX + NQ, LVW = LOWN + 2 * (R + 64),
+                         LRAW = LVW + (WR > 1 ? 2 * NQ : 0), LRED = LRAW + (SOLO ? 2 * NP : 0), LPART = LRED + 2 * NW,
+                         LFAIL = LPART + (WC > 1 ? NW * (RW + 3) : 0), LROW = LFAIL + 2, LDS = LROW + WR * RL * NP;
+    static_assert(WC * WR == NW, "waves form a grid");
+    static_assert(256 * R <= 65536 && R + 64 < 65536, "places are 16 bits");
+
+    static __device__ __forceinline__ void columns(const TridJob& J, const int g, double* sm, double (&a)[RR][CW],
+                                                   const double sc, const bool local) {
+        const int n = J.n, G = SOLO ? 1 : J.G, ldv = v_stride(n);
+        const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int wc = w % WC, wr = w / WC;
+        double* part_s = sm + LPART;
+        double* rows = sm + LROW + wr * RL * NP + lane + 64 * wc;   // this lane's entries of the LDS rows
+        const int gr = (G * R + 15) & ~15, region = gr + NP;   // per column: p slices, then row k+1
+        gu64* reg = (gu64*)J.xbuf + ((2 * G + 15) & ~15);
+        const gf64* A = (const gf64*)J.A;
+        gf64 *V = (gf64*)J.V, *Jd = (gf64*)J.d, *Je = (gf64*)J.e, *Jtau = (gf64*)J.tau;
+        auto* failed = (LOCAL_MEM volatile int*)(sm + LFAIL);
+        // sum over the workgroup's threads, in a fixed order
+        auto put_sum = [&](double x, int at) {
+            x = wave_sum(x);
+            if (lane == 0) sm[at + w] = x;
+        };
+        auto get_sum = [&](int at) {
+            double x = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) x += sm[at + q];
+            return x;
+        };
+        // this thread's exchanged columns: x the next column, v, w; place:
+        // their p slot and, above it, their place among the own rows
+        double x[PQ], vq[PQ], wq[PQ];
+        uint32_t place[PQ];
+        double part = 0.0;
+#pragma unroll
+        for (int q = 0; q < PQ; ++q) {
+            const int j = tid + T * q, jc = min(j, n - 1), r = jc / G;
+            x[q] = j < n ? A[j] * sc : 0.0;   // column 0
+            const double y = j >= 2 ? x[q] : 0.0;
+            part = fma(y, y, part);
+            vq[q] = wq[q] = 0.0;
+            place[q] = ((jc - r * G) * R + r) | (j < n && jc - r * G == g ? (r % WR) * RW + r / WR : R + lane) << 16;
+        }
+        for (int j = tid; j < 2 * (R + 64); j += T) sm[LOWN + j] = 0.0;   // column -1 leaves no update
+        double v[CW], vA[CW], wA[CW];   // v of column k; v and w of column k-1
+#pragma unroll
+        for (int c = 0; c < CW; ++c) v[c] = vA[c] = wA[c] = 0.0;
+        int own = G > 1 ? 1 : 0, own_r = G > 1 ? 0 : 1;   // workgroup and local row of row k+1
+        int own_k = 0;                                    // workgroup that stores column k
+#pragma unroll 1
+        for (int k = 0; k + 1 < n; ++k) {
+            __asm__("" : "+s"(reg), "+s"(V));   // scalar bases: no per-lane address carried round the loop
+            // (a) Householder vector of column k
+#pragma unroll
+            for (int q = 0; q < PQ; ++q) sm[LX + tid + T * q] = x[q];
+            put_sum(part, LRED + NW);
+            __syncthreads();
+            const double dk = sm[LX + k], alpha = sm[LX + k + 1], xn2 = get_sum(LRED + NW);
+            double beta, tau, scal;
+            householder(alpha, xn2, beta, tau, scal);
+#pragma unroll
+            for (int q = 0; q < PQ; ++q) vq[q] = tid + T * q > k + 1 && (T * (q + 1) <= NP || tid + T * q < NP)
+                                                     ? x[q] * scal
+                                                     : (tid + T * q == k + 1 ? 1.0 : 0.0);
+            const int c_lo = max(k + 1 - 64 * wc, 0) / (64 * WC);   // columns j > k: slots c >= c_lo
+            if constexpr (WR > 1) {
+#pragma unroll
+                for (int q = 0; q < PQ; ++q)
+                    *(double2*)(sm + LVW + 2 * (tid + T * q)) = make_double2(wq[q], vq[q]);
+                __syncthreads();
+#pragma unroll
+                for (int c0 = 0; c0 < CW; c0 += kColGroup) {
+                    if (c0 + kColGroup > c_lo) {
+#pragma unroll
+                        for (int c = c0; c < c0 + kColGroup && c < CW; ++c) {
+                            const double2 wv = *(const double2*)(sm + LVW + 2 * (lane + 64 * (wc + WC * c)));
+                            vA[c] = v[c];
+                            wA[c] = wv.x;
+                            v[c] = wv.y;
+                        }
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < CW; ++c) {
+                    vA[c] = v[c];
+                    wA[c] = wq[c];
+                    v[c] = vq[c];
+                }
             }
+            if (SOLO || g == own_k) {
+#pragma unroll
+                for (int q = 0; q < PQ; ++q)
+                    if (64 * w + T * q < ldv) *at8(V, tid + T * q) = vq[q];
+                if (tid == 0) {
+                    Jd[k] = dk;
+                    Je[k] = beta;
+                    Jtau[k] = tau;
+                }
+            }
+            V += ldv;
+            // (b) own rows i > k: slots s >= s_lo
+            const int s_lo = (max(own_r + (g < own ? 1 : 0) - wr, 0) + WR - 1) / WR;
+#pragma unroll
+            for (int s0 = 0; s0 < RW; s0 += kRowGroup) {
+                if (s0 + kRowGroup > s_lo) {
+                    double vu[kRowGroup], wu[kRowGroup], acc[kRowGroup];
+#pragma unroll
+                    for (int u = 0; u < kRowGroup; ++u) {
+                        acc[u] = 0.0;
+                        if (s0 + u < RW) {
+                            const double2 t = *(const double2*)(sm + LOWN + 2 * (wr * RW + s0 + u));
+                            vu[u] = t.x;
+                            wu[u] = t.y;
+                        }
+                    }
+#pragma unroll
+                    for (int c0 = 0; c0 < CW; c0 += kColGroup) {
+                        if (c0 + kColGroup > c_lo) {
+#pragma unroll
+                            for (int c = c0; c < c0 + kColGroup && c < CW; ++c) {
+#pragma unroll
+                                for (int u = 0; u < kRowGroup && s0 + u < RW; ++u) {
+                                    double y = s0 + u < RR ? a[min(s0 + u, RR - 1)][c]
+                                                           : rows[(s0 + u - RR) * NP + 64 * WC * c];
+                                    y = fma(-vu[u], wA[c], y);
+                                    y = fma(-wu[u], vA[c], y);
+                                    if (s0 + u < RR) a[min(s0 + u, RR - 1)][c] = y;
+                                    else rows[(s0 + u - RR) * NP + 64 * WC * c] = y;
+                                    acc[u] = fma(y, v[c], acc[u]);
+                                }
+                            }
+                        }
+                    }
+                    const double z = four_sums(acc);
+                    const int s = s0 + reduced_row(lane >> 4);
+                    if ((lane & 15) == 0 && s < RW) {
+                        if constexpr (WC > 1) part_s[w * (RW + 3) + s] = z;
+                        else if constexpr (SOLO) sm[LRAW + wr + WR * s] = tau * z;
+                        else put_x(reg, g * R + wr + WR * s, tau * z, local);
+                    }
+                }
+            }
+            if (g == own && own_r % WR == wr) {   // publish row k+1
+                const int sp = own_r / WR;
+                if constexpr (RL > 0)
+                    if (sp >= RR) {
+#pragma unroll
+                        for (int c = 0; c < CW; ++c)
+                            put_x(reg + gr, lane + 64 * (wc + WC * c), rows[(sp - RR) * NP + 64 * WC * c], local);
+                    }
+#pragma unroll
+                for (int s = 0; s < RR; ++s) {
+                    if (s == sp) {
+                        if (SOLO) {
+#pragma unroll
+                            for (int c = 0; c < CW; ++c) sm[LRAW + NP + lane + 64 * (wc + WC * c)] = a[s][c];
+                        } else if (local) {
+#pragma unroll
+                            for (int c = 0; c < CW; ++c) put_x<true>(reg + gr, lane + 64 * (wc + WC * c), a[s][c]);
+                        } else {
+#pragma unroll
+                            for (int c = 0; c < CW; ++c) put_x<false>(reg + gr, lane + 64 * (wc + WC * c), a[s][c]);
+                        }
+                    }
+                }
+            }
+            if constexpr (WC > 1) {
+                __syncthreads();
+                if (tid < R) {   // local row tid = (row group tid % WR, slot tid / WR)
+                    double y = 0.0;
+#pragma unroll
+                    for (int q = 0; q < WC; ++q) y += part_s[((tid % WR) * WC + q) * (RW + 3) + tid / WR];
+                    put_x(reg, g * R + tid, tau * y, local);
+                }
+            }
+            // (c) this thread's columns of p and of row k+1
+            double pr[PQ], rr[PQ];
+            if constexpr (SOLO) {
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < PQ; ++q) {
+                    pr[q] = sm[LRAW + min(tid + T * q, NP - 1)];
+                    rr[q] = sm[LRAW + NP + min(tid + T * q, NP - 1)];
+                }
+            } else {
+                // slots of a wave without a column in k+1 .. n-1 are left out
+                uint64_t pu[PQ], ru[PQ];
+#pragma unroll
+                for (int q = 0; q < PQ; ++q) pu[q] = ru[q] = 0;
+                for (int polls = 0;;) {
+                    bool empty = false;
+#pragma unroll
+                    for (int q = 0; q < PQ; ++q) {
+                        if (T * q + 64 * w + 63 > k && T * q + 64 * w < n) {
+                            pu[q] = get_x(reg, place[q] & 0xffff);
+                            ru[q] = get_x(reg + gr, tid + T * q);
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < PQ; ++q)
+                        empty |= (pu[q] == kEmpty && (unsigned)(tid + T * q - k - 1) < (unsigned)(n - k - 1)) ||
+                                 ru[q] == kEmpty;
+                    if (!__any(empty) || *failed) break;
+                    if (++polls > kSpinLimit) {
+                        *failed = 1;
+                        break;
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < PQ; ++q) {
+                    pr[q] = __builtin_bit_cast(double, pu[q]);
+                    rr[q] = __builtin_bit_cast(double, ru[q]);
+                }
+                reg += region;
+            }
+            part = 0.0;
+#pragma unroll
+            for (int q = 0; q < PQ; ++q) {
+                pr[q] = (unsigned)(tid + T * q - k - 1) < (unsigned)(n - k - 1) ? pr[q] : 0.0;
+                part = fma(pr[q], vq[q], part);
+                sm[LP + tid + T * q] = pr[q];
+            }
+            put_sum(part, LRED);
+            __syncthreads();
+            // (d) w, the pending update, and the next column
+            const double c2 = 0.5 * tau * get_sum(LRED), w1 = sm[LP + k + 1] - c2;   // (v's entry k+1 is 1)
+            part = 0.0;
+#pragma unroll
+            for (int q = 0; q < PQ; ++q) {
+                wq[q] = fma(-c2, vq[q], pr[q]);
+                x[q] = fma(-vq[q], w1, rr[q]) - wq[q];
+                // (row k+1 is zero at j >= n; a thread beyond the padded columns read another's entry)
+                const double y = tid + T * q >= k + 3 && (T * (q + 1) <= NP || tid + T * q < NP) ? x[q] : 0.0;
+                part = fma(y, y, part);
+                *(double2*)(sm + LOWN + 2 * (place[q] >> 16)) = make_double2(vq[q], wq[q]);
+            }
+            if (++own == G) {
+                own = 0;
+                ++own_r;
+            }
+            if (++own_k == G) own_k = 0;
+        }
+        if (g == 0) {
+#pragma unroll
+            for (int q = 0; q < PQ; ++q)
+                if (tid + T * q == n - 1) Jd[n - 1] = x[q];
         }
     }
-    __syncthreads();
-}
 
-// Accesses to a job's exchange area.  Every column writes its own region
-// (row and p slices at fresh offsets, each region starting on a 128-byte
-// line), so no cache line of the area is read before it is written.  Once
-// the workgroups have found that they all run on one XCD (same XCC_ID
-// register), plain loads and stores suffice: stores reach the XCD's L2
-// before the barrier and the readers' L1 never holds a line of a region
-// written later.  Otherwise the agent-scope accesses above are used.
-struct Xchg {
-    double* base;
-    bool local;
-    __device__ void st(int64_t idx, double v) const {
-        if (local) base[idx] = v;
-        else st_x(base + idx, v);
-    }
-    __device__ double ld(int64_t idx) const { return local ? base[idx] : ld_x(base + idx); }
-};
-constexpr int kSlots = 2;   // n <= kSlots * kTriThreads: entries j = tid + kTriThreads s per thread
-
-// Step 1.  bmap[b] = (job, rank) of workgroup b; job < 0: idle workgroup.
-// Dynamic LDS: R rows of n, v and w of the last two columns (2 x 2 n), the
-// reduction scratch.  Thread t owns the entries j = t + kTriThreads q of the
-// column vectors (the column, v, p, w), kept in registers.  Per column k:
-// (a) the Householder vector from the column (every workgroup; its norm and
-// the two leading entries come out of one block reduction); (b) one pass
-// over the own rows i > k that applies the pending update of column k-1 and
-// forms p_i = tau (row_i . v); the owner of row k+1 publishes it; (c) the
-// barrier; (d) p and row k+1 are loaded together, w = p - (tau/2)(p.v) v
-// (second block reduction) becomes the pending update and row k+1 with it
-// the next column.  Block reductions alternate between two scratch halves,
-// so each costs one workgroup barrier.
-__device__ inline double block_sum_x(double x, double* red, int& par) {
-    x = wave_sum(x);
-    double* r = red + par * kTriWaves;
-    if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = x;
-    __syncthreads();
-    double s = 0.0;
+    static __device__ __forceinline__ void job(const TridJob& J, const int g, double* sm) {
+        const int n = J.n, G = SOLO ? 1 : J.G;
+        const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int wc = w % WC, wr = w / WC;
+        double* red = sm + LRED;
+        volatile int* failed = (volatile int*)(sm + LFAIL);
+        const gf64* A = (const gf64*)J.A;
+        if (tid == 0) *failed = 0;
+        double a[RR][CW];
+        double* rows = sm + LROW + wr * RL * NP + lane + 64 * wc;
+        double mx = 0.0;
 #pragma unroll
-    for (int i = 0; i < kTriWaves; ++i) s += r[i];
-    par ^= 1;
-    return s;
-}
-__global__ __launch_bounds__(kTriThreads) void tridiag_kernel(const TridJob* __restrict__ jobs,
-                                                               const int2* __restrict__ bmap) {
+        for (int s = 0; s < RW; ++s) {
+            const int i = g + G * (wr + WR * s);
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                const int j = lane + 64 * (wc + WC * c);
+                const double y = (i < n && j < n) ? A[j + (int64_t)i * J.lda] : 0.0;   // row i = column i
+                if (s < RR) a[min(s, RR - 1)][c] = y;
+                else rows[(s - RR) * NP + 64 * WC * c] = y;
+                mx = fmax(mx, fabs(y));
+            }
+        }
+        __syncthreads();
+        mx = block_max<NW>(mx, red);
+        bool local = true;
+        if constexpr (!SOLO) {
+            gu64* x0 = (gu64*)J.xbuf;
+            if (tid == 0) {
+                unsigned xcc;
+                __asm__ volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+                put_x<false>(x0, g, mx + 0.0);
+                put_x<false>(x0, G + g, (double)xcc);
+            }
+            double gm = 0.0, first = 0.0, last = 0.0;   // largest entry; 64 - smallest and 1 + largest id
+            for (int t = tid; t < 2 * G; t += T) {
+                uint64_t u = get_x(x0, t);
+                for (int polls = 0; u == kEmpty && !*failed; u = get_x(x0, t))
+                    if (++polls > kSpinLimit) *failed = 1;
+                const double x = __builtin_bit_cast(double, u);
+                if (t < G) gm = fmax(gm, x);
+                else {
+                    first = fmax(first, 64.0 - x);
+                    last = fmax(last, 1.0 + x);
+                }
+            }
+            mx = block_max<NW>(gm, red);
+            first = block_max<NW>(first, red);
+            last = block_max<NW>(last, red);
+            local = first + last == 65.0;   // every workgroup of the job on one XCD
+        }
+        const double sc = mx > 0.0 && isfinite(mx) ? ldexp(1.0, -ilogb(mx)) : 1.0;
+        if (g == 0 && tid == 0) *J.scale = sc;
+#pragma unroll
+        for (int s = 0; s < RW; ++s)
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                if (s < RR) a[min(s, RR - 1)][c] *= sc;
+                else rows[(s - RR) * NP + 64 * WC * c] *= sc;
+            }
+        columns(J, g, sm, a, sc, local);
+        __syncthreads();
+        if (tid == 0 && *failed) *J.status = 1;
+    }
+};
+
+// Register shapes of a job: (threads, waves across the columns, column slots
+// per lane, rows per wave, of them in LDS).  A variant takes orders up to
+// 64 WC CW; a workgroup holds RW waves / WC rows.  256-thread variants hold
+// whole rows per wave (no LDS round for a row sum); beyond n = 704 their
+// vectors and rows no longer fit the registers of four waves, and eight waves
+// share the columns.  RW is set so that a job of the variant's largest order
+// fits one XCD's 32 compute units up to n = 1024 (its exchange costs half of
+// one over all XCDs: 3.6 us per column at n = 1024, 4.6 us at 1100), above
+// that by the registers: more rows spill (n = 2624 with 15 rows all in
+// registers: 32.9 ms in all, with four of them in LDS 24.2 ms).  bmap[b] =
+// (job, rank) of workgroup b; job < 0: idle workgroup.  Dynamic LDS:
+// tridiag_lds.
+struct TridVariant {
+    int T, WC, CW, RW, RL;
+    int nmax() const { return 64 * WC * CW; }
+    int rows() const { return RW * (T / 64 / WC); }
+};
+const TridVariant kTridVariants[] = {
+    {256, 1, 2, 32, 0}, {256, 1, 3, 12, 0}, {256, 1, 4, 8, 0},  {256, 1, 6, 6, 0}, {256, 1, 8, 5, 0}, {256, 1, 11, 6, 0},
+    {512, 2, 8, 8, 0},  {512, 4, 6, 12, 0}, {512, 8, 4, 20, 0}, {512, 8, 6, 15, 4}, {512, 8, 7, 13, 3}};
+constexpr int kTridVariantsN = sizeof(kTridVariants) / sizeof(kTridVariants[0]);
+constexpr int kTridWide = 6;   // first 512-thread variant
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void tridiag_kernel(
+    const TridJob* __restrict__ jobs, const int2* __restrict__ bmap) {
     const int2 bm = bmap[blockIdx.x];
     if (bm.x < 0) return;
     const TridJob J = jobs[bm.x];
-    const int g = bm.y, G = J.G, n = J.n;
     extern __shared__ double sm[];
-    double* rows = sm;
-    double* vb = rows + (size_t)J.R * n;   // v of columns k (vb + (k & 1) n)
-    double* wb = vb + 2 * (size_t)n;       // w of columns k (wb + (k & 1) n)
-    double* red = wb + 2 * (size_t)n;      // 2 x kTriWaves
-    double* slot = red + 2 * kTriWaves;    // the column's diagonal entry and alpha
-    __shared__ int failed;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) failed = 0;
-    int epoch = 0, par = 0;
-    const int nloc = g < n ? (n - g + G - 1) / G : 0;   // rows i = g + r G
-    // exchange area: G maxima, G XCC ids, then per column k the published
-    // row k+1 (npad) and the p slices (npad)
-    const int64_t npad = (n + 15) & ~15;
-    const int64_t oR = (2 * G + 15) & ~15, oP = oR + (int64_t)n * npad;
-    Xchg X;
-    X.base = J.xbuf;
-    X.local = false;
-
-    double mx = 0.0;
-    for (int r = 0; r < nloc; ++r) {
-        const int i = g + r * G;
-        for (int j = tid; j < n; j += kTriThreads) {
-            const double a = J.A[j + (int64_t)i * J.lda];   // row i = column i
-            rows[(size_t)r * n + j] = a;
-            mx = fmax(mx, fabs(a));
-        }
+    switch (J.variant) {
+        case 0: Trid<256, 1, 2, 32>::job(J, bm.y, sm); break;
+        case 1: Trid<256, 1, 3, 12>::job(J, bm.y, sm); break;
+        case 2: Trid<256, 1, 4, 8>::job(J, bm.y, sm); break;
+        case 3: Trid<256, 1, 6, 6>::job(J, bm.y, sm); break;
+        case 4: Trid<256, 1, 8, 5>::job(J, bm.y, sm); break;
+        default: Trid<256, 1, 11, 6>::job(J, bm.y, sm); break;
     }
-    mx = block_max<kTriWaves>(mx, red);
-    if (tid == 0) {
-        unsigned xcc;
-        __asm__ volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-        X.st(g, mx);
-        X.st(G + g, (double)xcc);
+}
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void tridiag_wide_kernel(
+    const TridJob* __restrict__ jobs, const int2* __restrict__ bmap) {
+    const int2 bm = bmap[blockIdx.x];
+    if (bm.x < 0) return;
+    const TridJob J = jobs[bm.x];
+    extern __shared__ double sm[];
+    switch (J.variant) {
+        case 6: Trid<512, 2, 8, 8>::job(J, bm.y, sm); break;
+        case 7: Trid<512, 4, 6, 12>::job(J, bm.y, sm); break;
+        case 8: Trid<512, 8, 4, 20>::job(J, bm.y, sm); break;
+        case 9: Trid<512, 8, 6, 15, 4>::job(J, bm.y, sm); break;
+        default: Trid<512, 8, 7, 13, 3>::job(J, bm.y, sm); break;
     }
-    job_barrier(J.counter, epoch, G, &failed);
-    double gm = 0.0, other = 0.0;
-    const double x0 = X.ld(G);
-    for (int t = tid; t < G; t += kTriThreads) {
-        gm = fmax(gm, X.ld(t));
-        other = fmax(other, X.ld(G + t) != x0 ? 1.0 : 0.0);
-    }
-    gm = block_max<kTriWaves>(gm, red);
-    X.local = block_max<kTriWaves>(other, red) == 0.0;   // every workgroup of the job on one XCD
-    const double sc = (gm > 0.0 && isfinite(gm)) ? ldexp(1.0, -ilogb(gm)) : 1.0;
-    if (g == 0 && tid == 0) *J.scale = sc;
-    for (int r = 0; r < nloc; ++r)
-        for (int j = tid; j < n; j += kTriThreads) rows[(size_t)r * n + j] *= sc;
-    // the pending update of column -1 is zero
-    for (int j = tid; j < n; j += kTriThreads) {
-        vb[n + j] = 0.0;
-        wb[n + j] = 0.0;
-    }
-    double col[kSlots], vr[kSlots];
-    double part = 0.0;
-#pragma unroll
-    for (int q = 0; q < kSlots; ++q) {
-        const int j = tid + q * kTriThreads;
-        col[q] = j < n ? J.A[j] * sc : 0.0;   // column 0
-        if (j == 0) slot[0] = col[q];
-        if (j == 1) slot[1] = col[q];
-        if (j >= 2 && j < n) part += col[q] * col[q];
-    }
-    double xn2 = block_sum_x(part, red, par);
-    if (n == 1 && g == 0 && tid == 0) J.d[0] = slot[0];
-
-    for (int k = 0; k + 1 < n; ++k) {
-        // (a) Householder vector of column k
-        const double dk = slot[0], alpha = slot[1];
-        double tau = 0.0, beta = alpha, scal = 0.0;
-        if (xn2 > 0.0) {
-            beta = -copysign(sqrt(alpha * alpha + xn2), alpha);
-            tau = (beta - alpha) / beta;
-            scal = 1.0 / (alpha - beta);
-        }
-        double* v = vb + (size_t)(k & 1) * n;
-#pragma unroll
-        for (int q = 0; q < kSlots; ++q) {
-            const int j = tid + q * kTriThreads;
-            vr[q] = 0.0;
-            if (j > k && j < n) {
-                vr[q] = j == k + 1 ? 1.0 : col[q] * scal;
-                v[j] = vr[q];
-                if (g == 0) J.V[(size_t)k * n + j] = vr[q];
-            }
-        }
-        if (g == 0 && tid == 0) {
-            J.d[k] = dk;
-            J.e[k] = beta;
-            J.tau[k] = tau;
-        }
-        __syncthreads();
-        // (b) own rows i > k, one per wave at a time
-        const double* vp = vb + (size_t)((k + 1) & 1) * n;   // v, w of column k-1
-        const double* wp = wb + (size_t)((k + 1) & 1) * n;
-        const int64_t pofs = oP + k * npad, rofs = oR + k * npad;
-        const int r0 = k + 1 <= g ? 0 : (k + 1 - g + G - 1) / G;
-        for (int r = r0 + wave; r < nloc; r += kTriWaves) {
-            const int i = g + r * G;
-            double* row = rows + (size_t)r * n;
-            const double vpi = vp[i], wpi = wp[i];
-            const bool pub = i == k + 1;
-            double acc = 0.0;
-#pragma unroll 4
-            for (int j = k + 1 + lane; j < n; j += 64) {
-                const double a = row[j] - vpi * wp[j] - wpi * vp[j];
-                row[j] = a;
-                acc += a * v[j];
-                if (pub) X.st(rofs + j, a);
-            }
-            acc = wave_sum(acc);
-            if (lane == 0) X.st(pofs + i, tau * acc);
-        }
-        // (c)
-        job_barrier(J.counter, epoch, G, &failed);
-        // (d) p and row k+1, loaded together
-        double pr[kSlots], rr[kSlots];
-        const double p1 = X.ld(pofs + k + 1);
-        part = 0.0;
-#pragma unroll
-        for (int q = 0; q < kSlots; ++q) {
-            const int j = tid + q * kTriThreads;
-            pr[q] = rr[q] = 0.0;
-            if (j > k && j < n) {
-                pr[q] = X.ld(pofs + j);
-                rr[q] = X.ld(rofs + j);
-            }
-            part += pr[q] * vr[q];
-        }
-        const double c2 = 0.5 * tau * block_sum_x(part, red, par);
-        const double w1 = p1 - c2;   // w of entry k+1 (v's entry there is 1)
-        double* w = wb + (size_t)(k & 1) * n;
-        part = 0.0;
-#pragma unroll
-        for (int q = 0; q < kSlots; ++q) {
-            const int j = tid + q * kTriThreads;
-            if (j > k && j < n) {
-                const double wj = pr[q] - c2 * vr[q];
-                w[j] = wj;
-                const double c = rr[q] - vr[q] * w1 - wj;   // row k+1 with the update of column k
-                col[q] = c;
-                if (j == k + 1) slot[0] = c;
-                if (j == k + 2) slot[1] = c;
-                if (j >= k + 3) part += c * c;
-            }
-        }
-        xn2 = block_sum_x(part, red, par);
-        if (k + 2 == n && g == 0 && tid == 0) J.d[n - 1] = slot[0];
-    }
-    __syncthreads();
-    if (tid == 0 && failed) *J.status = 1;
 }
 
 struct BisJob {
@@ -459,18 +742,163 @@ __device__ inline double start_entry(int i, int m) {
     return ((double)h + 0.5) / 2147483648.0 - 1.0;
 }
 
-// Step 3: one wavefront per cluster.  Lane 0 runs the recurrences of the
-// LU factorisation and the solves on LDS arrays, carrying the values each
-// step depends on in registers; the whole wave does the vector operations.
-// Dynamic LDS: 8 n doubles.
-__global__ __launch_bounds__(64) void tdvec_kernel(const VecJob* __restrict__ jobs,
-                                                    const VecCluster* __restrict__ clusters) {
+// Step 3, every kept eigenvalue on a workgroup of its own: the eigenvector
+// straight from the twisted factorisation of T - lam I.  Wave 0
+// runs the top-down recurrence D+_i = (d_i - lam) - e_{i-1}^2 / D+_{i-1},
+// wave 1 the bottom-up one D-_i = (d_i - lam) - e_i^2 / D-_{i+1} at the same
+// time; the twist r minimises |gamma_i| = |D+_i + D-_i - (d_i - lam)| (ties:
+// the lower index); then z_r = 1, z_i = -e_i z_{i+1} / D+_i above r and
+// z_i = -e_{i-1} z_{i-1} / D-_i below it, normalised.  Its residual is
+// |gamma_r| / ||z||, which an eigenvalue accurate to 2 eps ||T|| keeps at
+// rounding level (no iteration).  Dynamic LDS: d, e, D+, D-, z (5 n).
+__global__ __launch_bounds__(128) void twist_kernel(const VecJob* __restrict__ jobs,
+                                                     const int2* __restrict__ bmap) {
+    const int2 bm = bmap[blockIdx.x];   // (job, rank of the eigenvalue, descending)
+    const VecJob J = jobs[bm.x];
+    const int n = J.n, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    extern __shared__ double sm[];
+    double *d = sm, *e = sm + n, *dp = sm + 2 * n, *dm = sm + 3 * n, *z = sm + 4 * n;
+    __shared__ double red_v[2];
+    __shared__ int red_i[2];
+    for (int i = tid; i < n; i += 128) {
+        d[i] = J.d[i];
+        e[i] = i + 1 < n ? J.e[i] : 0.0;
+    }
+    __syncthreads();
+    double tl = 0.0, em = 0.0;
+    for (int i = tid; i < n; i += 128) {
+        tl = fmax(tl, fabs(d[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0) + fabs(e[i]));
+        em = fmax(em, e[i] * e[i]);
+    }
+    tl = wave_max(tl);
+    em = wave_max(em);
+    if (lane == 0) red_v[wave] = tl;
+    __syncthreads();
+    const double tnorm = fmax(red_v[0], red_v[1]);
+    __syncthreads();
+    const int jr = bm.y;
+    double* zo = J.Zt + (size_t)jr * n;
+    if (n == 1 || tnorm == 0.0) {   // T = 0: the unit vectors
+        for (int i = tid; i < n; i += 128) zo[i] = i == jr ? 1.0 : 0.0;
+        return;
+    }
+    const double lam = J.w[n - 1 - jr] * *J.scale;
+    // pivots below this are raised to it (keeping the sign): never zero
+    const double piv = DBL_MIN * fmax(1.0, em) / DBL_EPSILON;
+    auto guard = [&](double q) { return fabs(q) < piv ? (q < 0.0 ? -piv : piv) : q; };
+    auto rcp = [&](double q) {
+        const double r0 = __builtin_amdgcn_rcp(q);
+        return fma(r0, fma(-q, r0, 1.0), r0);
+    };
+    if (lane == 0 && wave == 0) {
+        double q = guard(d[0] - lam);
+        dp[0] = q;
+        double dn = d[1], ep = e[0];
+        for (int i = 1; i < n; ++i) {
+            const double a = dn - lam, e2 = ep * ep;
+            if (i + 1 < n) {
+                dn = d[i + 1];
+                ep = e[i];
+            }
+            q = guard(a - e2 * rcp(q));
+            dp[i] = q;
+        }
+    } else if (lane == 0 && wave == 1) {
+        double q = guard(d[n - 1] - lam);
+        dm[n - 1] = q;
+        double dn = d[n - 2], ep = e[n - 2];
+        for (int i = n - 2; i >= 0; --i) {
+            const double a = dn - lam, e2 = ep * ep;
+            if (i > 0) {
+                dn = d[i - 1];
+                ep = e[i - 1];
+            }
+            q = guard(a - e2 * rcp(q));
+            dm[i] = q;
+        }
+    }
+    __syncthreads();
+    // twist: argmin |gamma| (lowest index on ties)
+    double bv = INFINITY;
+    int bi = n;
+    for (int i = tid; i < n; i += 128) {
+        const double g = fabs(dp[i] + dm[i] - (d[i] - lam));
+        if (g < bv) {
+            bv = g;
+            bi = i;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double ov = __shfl_xor(bv, o, 64);
+        const int oi = __shfl_xor(bi, o, 64);
+        if (ov < bv || (ov == bv && oi < bi)) {
+            bv = ov;
+            bi = oi;
+        }
+    }
+    if (lane == 0) {
+        red_v[wave] = bv;
+        red_i[wave] = bi;
+    }
+    __syncthreads();
+    const int r = (red_v[1] < red_v[0] || (red_v[1] == red_v[0] && red_i[1] < red_i[0])) ? red_i[1] : red_i[0];
+    // ratios in parallel, then the two product chains at once, wave 0 upwards
+    // from r, wave 1 downwards: each lane multiplies a run of consecutive
+    // ratios, the runs' products are scanned across the lanes, and each lane
+    // goes through its run again
+    for (int i = tid; i < n; i += 128) {
+        if (i < r) z[i] = -e[i] / dp[i];
+        else if (i > r) z[i] = -e[i - 1] / dm[i];
+        else z[i] = 1.0;
+    }
+    __syncthreads();
+    {
+        const int len = wave == 0 ? r : n - 1 - r;      // ratios of this wave's chain
+        const int step = wave == 0 ? -1 : 1;
+        const int run = (len + 63) / 64, f0 = min(lane * run, len), f1 = min(f0 + run, len);
+        double prod = 1.0;
+        for (int f = f0; f < f1; ++f) prod *= z[r + step * (f + 1)];
+        double before = __shfl_up(prod, 1, 64);
+        if (lane == 0) before = 1.0;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const double up = __shfl_up(before, o, 64);
+            if (lane >= o) before *= up;
+        }
+        for (int f = f0; f < f1; ++f) {
+            before *= z[r + step * (f + 1)];
+            z[r + step * (f + 1)] = before;
+        }
+    }
+    __syncthreads();
+    double part = 0.0;
+    for (int i = tid; i < n; i += 128) part += z[i] * z[i];
+    part = wave_sum(part);
+    if (lane == 0) red_v[wave] = part;
+    __syncthreads();
+    const double inv = 1.0 / sqrt(red_v[0] + red_v[1]);
+    for (int i = tid; i < n; i += 128) zo[i] = z[i] * inv;
+}
+
+// Step 3 for eigenvalues closer than the clustering bound: one wavefront per
+// cluster goes through its members' vectors (from twist_kernel) in order and
+// projects the earlier ones out; unless little is left (a value degenerate
+// with an earlier one) that is the vector, else it comes from inverse
+// iteration.  There lane 0 runs the recurrences of the LU factorisation and
+// the solves, carrying the values each step depends on in registers; the
+// whole wave does the vector operations.  INLDS: the factors (5 n doubles)
+// in LDS after z, d, e, else in the job's work space.
+template <bool INLDS>
+__global__ __launch_bounds__(64) void cluster_kernel(const VecJob* __restrict__ jobs,
+                                                      const VecCluster* __restrict__ clusters) {
     const VecCluster C = clusters[blockIdx.x];
     const VecJob J = jobs[C.job];
     const int n = J.n, lane = threadIdx.x;
     extern __shared__ double sm[];
-    double *d = sm, *e = sm + n, *dl = sm + 2 * n, *du = sm + 3 * n, *du2 = sm + 4 * n, *rdd = sm + 5 * n,
-           *piv = sm + 6 * n, *z = sm + 7 * n;
+    double *z = sm, *d = sm + n, *e = sm + 2 * n;
+    double *dl = INLDS ? sm + 3 * n : J.work + C.woff, *du = dl + n, *du2 = dl + 2 * n, *rdd = dl + 3 * n,
+           *piv = dl + 4 * n;
     double tl = 0.0;
     for (int i = lane; i < n; i += 64) {
         d[i] = J.d[i];
@@ -480,99 +908,32 @@ __global__ __launch_bounds__(64) void tdvec_kernel(const VecJob* __restrict__ jo
     for (int i = lane; i < n; i += 64)
         tl = fmax(tl, fabs(d[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0) + fabs(e[i]));
     const double tnorm = wave_max(tl);
+    if (n == 1 || tnorm == 0.0) return;             // the unit vectors stand
     const double small = DBL_EPSILON * tnorm;
     const double sc = *J.scale;
-    for (int m = 0; m < C.count; ++m) {
+    for (int m = 1; m < C.count; ++m) {             // the first vector stands
         const int jr = C.first + m;                 // rank (descending)
         const double lam = J.w[n - 1 - jr] * sc;    // scaled eigenvalue
         double* zo = J.Zt + (size_t)jr * n;
-        if (n == 1 || tnorm == 0.0) {               // T = 0: the unit vectors
-            for (int i = lane; i < n; i += 64) zo[i] = i == jr ? 1.0 : 0.0;
-            __syncthreads();
+        for (int i = lane; i < n; i += 64) z[i] = zo[i];
+        for (int q = 0; q < m; ++q) {
+            const double* y = J.Zt + (size_t)(C.first + q) * n;
+            double pq = 0.0;
+            for (int i = lane; i < n; i += 64) pq += y[i] * z[i];
+            const double dot = wave_sum(pq);
+            for (int i = lane; i < n; i += 64) z[i] -= dot * y[i];
+        }
+        double part = 0.0;
+        for (int i = lane; i < n; i += 64) part += z[i] * z[i];
+        const double left = wave_sum(part);
+        if (left >= 0.25) {
+            const double inv = 1.0 / sqrt(left);
+            for (int i = lane; i < n; i += 64) zo[i] = z[i] * inv;
+            __threadfence_block();
+            __syncthreads();   // later members of the cluster read this vector
             continue;
         }
-        {
-            // first the twisted factorisation (as in twist_kernel, both
-            // recurrences on lane 0, dl and du holding D+ and D-), then the
-            // cluster's earlier vectors projected out; unless little is left
-            // (the value degenerate with an earlier one), that is the vector
-            const double pv = DBL_MIN * fmax(1.0, tnorm * tnorm) / DBL_EPSILON;
-            auto guard = [&](double q) { return fabs(q) < pv ? (q < 0.0 ? -pv : pv) : q; };
-            auto rcp = [&](double q) {
-                const double r0 = __builtin_amdgcn_rcp(q);
-                return fma(r0, fma(-q, r0, 1.0), r0);
-            };
-            if (lane == 0) {
-                double q = guard(d[0] - lam);
-                dl[0] = q;
-                for (int i = 1; i < n; ++i) {
-                    q = guard((d[i] - lam) - e[i - 1] * e[i - 1] * rcp(q));
-                    dl[i] = q;
-                }
-                q = guard(d[n - 1] - lam);
-                du[n - 1] = q;
-                for (int i = n - 2; i >= 0; --i) {
-                    q = guard((d[i] - lam) - e[i] * e[i] * rcp(q));
-                    du[i] = q;
-                }
-            }
-            __syncthreads();
-            double bv = INFINITY;
-            int bi = n;
-            for (int i = lane; i < n; i += 64) {
-                const double gv = fabs(dl[i] + du[i] - (d[i] - lam));
-                if (gv < bv) {
-                    bv = gv;
-                    bi = i;
-                }
-            }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                const double ov = __shfl_xor(bv, o, 64);
-                const int oi = __shfl_xor(bi, o, 64);
-                if (ov < bv || (ov == bv && oi < bi)) {
-                    bv = ov;
-                    bi = oi;
-                }
-            }
-            const int r = bi;
-            for (int i = lane; i < n; i += 64) z[i] = i < r ? -e[i] / dl[i] : (i > r ? -e[i - 1] / du[i] : 1.0);
-            __syncthreads();
-            if (lane == 0) {
-                double c = 1.0;
-                for (int i = r - 1; i >= 0; --i) {
-                    c *= z[i];
-                    z[i] = c;
-                }
-                c = 1.0;
-                for (int i = r + 1; i < n; ++i) {
-                    c *= z[i];
-                    z[i] = c;
-                }
-            }
-            __syncthreads();
-            double part = 0.0;
-            for (int i = lane; i < n; i += 64) part += z[i] * z[i];
-            double inv = 1.0 / sqrt(wave_sum(part));
-            for (int i = lane; i < n; i += 64) z[i] *= inv;
-            for (int q = 0; q < m; ++q) {
-                const double* y = J.Zt + (size_t)(C.first + q) * n;
-                double pq = 0.0;
-                for (int i = lane; i < n; i += 64) pq += y[i] * z[i];
-                const double dot = wave_sum(pq);
-                for (int i = lane; i < n; i += 64) z[i] -= dot * y[i];
-            }
-            part = 0.0;
-            for (int i = lane; i < n; i += 64) part += z[i] * z[i];
-            const double left = wave_sum(part);
-            if (left >= 0.25) {
-                inv = 1.0 / sqrt(left);
-                for (int i = lane; i < n; i += 64) zo[i] = z[i] * inv;
-                __syncthreads();   // later members of the cluster read this vector
-                continue;
-            }
-            __syncthreads();
-        }
+        __syncthreads();
         if (lane == 0) {
             // LU with partial pivoting of T - lam I (LAPACK's tridiagonal
             // scheme; row interchanges recorded in piv, tiny pivots raised
@@ -680,139 +1041,9 @@ __global__ __launch_bounds__(64) void tdvec_kernel(const VecJob* __restrict__ jo
             __syncthreads();
         }
         for (int i = lane; i < n; i += 64) zo[i] = z[i];
+        __threadfence_block();
         __syncthreads();   // later members of the cluster read this vector
     }
-}
-
-// Step 3 for an eigenvalue apart from the others (a cluster of one): the
-// eigenvector straight from the twisted factorisation of T - lam I.  Wave 0
-// runs the top-down recurrence D+_i = (d_i - lam) - e_{i-1}^2 / D+_{i-1},
-// wave 1 the bottom-up one D-_i = (d_i - lam) - e_i^2 / D-_{i+1} at the same
-// time; the twist r minimises |gamma_i| = |D+_i + D-_i - (d_i - lam)| (ties:
-// the lower index); then z_r = 1, z_i = -e_i z_{i+1} / D+_i above r and
-// z_i = -e_{i-1} z_{i-1} / D-_i below it, normalised.  Its residual is
-// |gamma_r| / ||z||, which an eigenvalue accurate to 2 eps ||T|| keeps at
-// rounding level (no iteration).  Dynamic LDS: d, e, D+, D-, z (5 n).
-__global__ __launch_bounds__(128) void twist_kernel(const VecJob* __restrict__ jobs,
-                                                     const VecCluster* __restrict__ clusters) {
-    const VecCluster C = clusters[blockIdx.x];
-    const VecJob J = jobs[C.job];
-    const int n = J.n, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    extern __shared__ double sm[];
-    double *d = sm, *e = sm + n, *dp = sm + 2 * n, *dm = sm + 3 * n, *z = sm + 4 * n;
-    __shared__ double red_v[2];
-    __shared__ int red_i[2];
-    for (int i = tid; i < n; i += 128) {
-        d[i] = J.d[i];
-        e[i] = i + 1 < n ? J.e[i] : 0.0;
-    }
-    __syncthreads();
-    double tl = 0.0, em = 0.0;
-    for (int i = tid; i < n; i += 128) {
-        tl = fmax(tl, fabs(d[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0) + fabs(e[i]));
-        em = fmax(em, e[i] * e[i]);
-    }
-    tl = wave_max(tl);
-    em = wave_max(em);
-    if (lane == 0) red_v[wave] = tl;
-    __syncthreads();
-    const double tnorm = fmax(red_v[0], red_v[1]);
-    __syncthreads();
-    const int jr = C.first;
-    double* zo = J.Zt + (size_t)jr * n;
-    if (n == 1 || tnorm == 0.0) {   // T = 0: the unit vectors
-        for (int i = tid; i < n; i += 128) zo[i] = i == jr ? 1.0 : 0.0;
-        return;
-    }
-    const double lam = J.w[n - 1 - jr] * *J.scale;
-    // pivots below this are raised to it (keeping the sign): never zero
-    const double piv = DBL_MIN * fmax(1.0, em) / DBL_EPSILON;
-    auto guard = [&](double q) { return fabs(q) < piv ? (q < 0.0 ? -piv : piv) : q; };
-    auto rcp = [&](double q) {
-        const double r0 = __builtin_amdgcn_rcp(q);
-        return fma(r0, fma(-q, r0, 1.0), r0);
-    };
-    if (lane == 0 && wave == 0) {
-        double q = guard(d[0] - lam);
-        dp[0] = q;
-        double dn = d[1], ep = e[0];
-        for (int i = 1; i < n; ++i) {
-            const double a = dn - lam, e2 = ep * ep;
-            if (i + 1 < n) {
-                dn = d[i + 1];
-                ep = e[i];
-            }
-            q = guard(a - e2 * rcp(q));
-            dp[i] = q;
-        }
-    } else if (lane == 0 && wave == 1) {
-        double q = guard(d[n - 1] - lam);
-        dm[n - 1] = q;
-        double dn = d[n - 2], ep = e[n - 2];
-        for (int i = n - 2; i >= 0; --i) {
-            const double a = dn - lam, e2 = ep * ep;
-            if (i > 0) {
-                dn = d[i - 1];
-                ep = e[i - 1];
-            }
-            q = guard(a - e2 * rcp(q));
-            dm[i] = q;
-        }
-    }
-    __syncthreads();
-    // twist: argmin |gamma| (lowest index on ties)
-    double bv = INFINITY;
-    int bi = n;
-    for (int i = tid; i < n; i += 128) {
-        const double g = fabs(dp[i] + dm[i] - (d[i] - lam));
-        if (g < bv) {
-            bv = g;
-            bi = i;
-        }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const double ov = __shfl_xor(bv, o, 64);
-        const int oi = __shfl_xor(bi, o, 64);
-        if (ov < bv || (ov == bv && oi < bi)) {
-            bv = ov;
-            bi = oi;
-        }
-    }
-    if (lane == 0) {
-        red_v[wave] = bv;
-        red_i[wave] = bi;
-    }
-    __syncthreads();
-    const int r = (red_v[1] < red_v[0] || (red_v[1] == red_v[0] && red_i[1] < red_i[0])) ? red_i[1] : red_i[0];
-    // ratios in parallel, then the two product chains at once
-    for (int i = tid; i < n; i += 128) {
-        if (i < r) z[i] = -e[i] / dp[i];
-        else if (i > r) z[i] = -e[i - 1] / dm[i];
-        else z[i] = 1.0;
-    }
-    __syncthreads();
-    if (lane == 0 && wave == 0) {
-        double c = 1.0;
-        for (int i = r - 1; i >= 0; --i) {
-            c *= z[i];
-            z[i] = c;
-        }
-    } else if (lane == 0 && wave == 1) {
-        double c = 1.0;
-        for (int i = r + 1; i < n; ++i) {
-            c *= z[i];
-            z[i] = c;
-        }
-    }
-    __syncthreads();
-    double part = 0.0;
-    for (int i = tid; i < n; i += 128) part += z[i] * z[i];
-    part = wave_sum(part);
-    if (lane == 0) red_v[wave] = part;
-    __syncthreads();
-    const double inv = 1.0 / sqrt(red_v[0] + red_v[1]);
-    for (int i = tid; i < n; i += 128) zo[i] = z[i] * inv;
 }
 
 struct BackJob {
@@ -821,105 +1052,82 @@ struct BackJob {
     int n, kv;
 };
 
-// Step 4.  One workgroup per eigenvector (bmap[b] = (job, vector)); thread
-// t owns the rows i = t + kBackThreads s.  The reflectors are applied one at
-// a time (one block-wide reduction each, its scratch alternating between two
-// halves so that one barrier per reflector suffices).  They are streamed
-// through LDS in chunks of up to kChunk consecutive reflectors (contiguous
-// in V, read as 16-byte pairs): the loads of the next chunk are issued into
-// registers before the current chunk is applied, so their latency overlaps
-// its work.  Entries a reflector does not store (rows i <= j) are never
-// read.  Dynamic LDS: the vector, tau, one chunk.  A cut keeps few vectors
-// (one workgroup each, on a fraction of the compute units), so the
-// per-reflector latency sets the time: eight waves (0.43 ms for the 65
-// vectors of the D = 6, chi = 64 cut) beat four (0.50) and sixteen (0.50).
-constexpr int kBackThreads = 512;
-constexpr int kBackWaves = kBackThreads / 64;
-constexpr int kChunk = 16;        // reflectors per chunk at most
-constexpr int kChunkLoads = 8;    // 16-byte loads per thread per chunk at most (the chunk size follows)
-__global__ __launch_bounds__(kBackThreads) void backtr_kernel(const BackJob* __restrict__ jobs,
-                                                               const int2* __restrict__ bmap, int ch) {
+// Step 4.  NW waves per eigenvector (bmap[b] = (job, vector)), which stays in
+// registers: lane entries i = tid + 64 NW q, q < SL.  The reflectors are read
+// straight from memory (L2: all vectors go through them at about the same
+// time) kBackAhead of them ahead; each costs one dot product, one wavefront
+// sum and one update, so the dependent chain of the sum bounds it (0.1 us per
+// reflector at n = 696 with one wave, against 0.6 us with the vector in LDS
+// under eight waves and a workgroup barrier per reflector).  One wave while a
+// vector's entries and the reflectors ahead fit its registers; beyond that
+// four waves, whose partial sums meet in LDS.
+constexpr int kBackAhead = 4;
+template <int NW, int SL>
+__global__ __launch_bounds__(64 * NW) void backtr_kernel(const BackJob* __restrict__ jobs,
+                                                          const int2* __restrict__ bmap) {
     const int2 bm = bmap[blockIdx.x];
     const BackJob J = jobs[bm.x];
-    const int n = J.n, c0 = bm.y;
-    extern __shared__ double z[];
-    double* taus = z + n;
-    double* vb = taus + n;   // the chunk as loaded: V's doubles from index 2 p0 on
-    __shared__ double red[2][kBackWaves];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < n; i += kBackThreads) {
-        z[i] = J.Zt[(size_t)c0 * n + i];
-        taus[i] = J.tau[i];
+    const int n = J.n, ldv = v_stride(n), tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ double red[2][NW];
+    double z[SL], v[kBackAhead][SL], tj[kBackAhead];
+    const double* zt = J.Zt + (size_t)bm.y * n;
+#pragma unroll
+    for (int q = 0; q < SL; ++q) {
+        const int i = tid + 64 * NW * q;
+        z[q] = i < n ? zt[i] : 0.0;
     }
-    const double2* V2 = reinterpret_cast<const double2*>(J.V);
-    // chunk with last reflector jb covers reflectors max(jb - kChunk + 1, 0) .. jb,
-    // rows jl .. jb of V: doubles [jl n, (jb + 1) n) read as whole 16-byte pairs
-    auto chunk_range = [&](int jb, int64_t& p0, int& np) {
-        const int jl = max(jb - ch + 1, 0);
-        p0 = ((int64_t)jl * n) >> 1;
-        np = (int)((((int64_t)(jb + 1) * n + 1) >> 1) - p0);
+    auto load = [&](int j, double (&vj)[SL], double& t) {
+        const double* row = J.V + (size_t)max(j, 0) * ldv;
+        t = j >= 0 ? J.tau[j] : 0.0;
+#pragma unroll
+        for (int q = 0; q < SL; ++q) {
+            const int i = tid + 64 * NW * q;
+            vj[q] = i < ldv ? row[i] : 0.0;
+        }
     };
-    double2 rg[kChunkLoads];
-    int64_t p0 = 0;
-    int np = 0;
-    if (n >= 2) {
-        chunk_range(n - 2, p0, np);
 #pragma unroll
-        for (int u = 0; u < kChunkLoads; ++u) {
-            const int e = tid + u * kBackThreads;
-            rg[u] = e < np ? V2[p0 + e] : make_double2(0.0, 0.0);
-        }
-    }
+    for (int u = 0; u < kBackAhead; ++u) load(n - 2 - u, v[u], tj[u]);
     int par = 0;
-    for (int jb = n - 2; jb >= 0; jb -= ch) {
-        __syncthreads();   // the previous chunk is applied
-        chunk_range(jb, p0, np);
-        const int64_t base = 2 * p0;   // V index of vb[0]
+    for (int j0 = n - 2; j0 >= 0; j0 -= kBackAhead) {
 #pragma unroll
-        for (int u = 0; u < kChunkLoads; ++u) {
-            const int e = tid + u * kBackThreads;
-            if (e < np) reinterpret_cast<double2*>(vb)[e] = rg[u];
-        }
-        if (jb - ch >= 0) {
-            int64_t p1;
-            int np1;
-            chunk_range(jb - ch, p1, np1);
+        for (int u = 0; u < kBackAhead; ++u) {
+            double part = 0.0, part2 = 0.0;
 #pragma unroll
-            for (int u = 0; u < kChunkLoads; ++u) {
-                const int e = tid + u * kBackThreads;
-                rg[u] = e < np1 ? V2[p1 + e] : make_double2(0.0, 0.0);
+            for (int q = 0; q < SL; q += 2) {
+                part += v[u][q] * z[q];
+                if (q + 1 < SL) part2 += v[u][q + 1] * z[q + 1];
             }
-        }
-        __syncthreads();
-        const int jl = max(jb - ch + 1, 0);
-        for (int j = jb; j >= jl; --j) {
-            const double tj = taus[j];
-            if (tj == 0.0) continue;
-            const double* v = vb + ((int64_t)j * n - base);
-            double part = 0.0;
+            part = wave_sum(part + part2);
+            if constexpr (NW > 1) {
+                if (lane == 0) red[par][wave] = part;
+                __syncthreads();
+                part = 0.0;
 #pragma unroll
-            for (int q = 0; q < kSlots * (kTriThreads / kBackThreads); ++q) {
-                const int i = tid + q * kBackThreads;
-                if (i > j && i < n) part += v[i] * z[i];
+                for (int q = 0; q < NW; ++q) part += red[par][q];
+                par ^= 1;
             }
-            part = wave_sum(part);
-            if (lane == 0) red[par][wave] = part;
-            __syncthreads();
-            double f = 0.0;
+            const double f = part * tj[u];
 #pragma unroll
-            for (int q = 0; q < kBackWaves; ++q) f += red[par][q];
-            f *= tj;
-#pragma unroll
-            for (int q = 0; q < kSlots * (kTriThreads / kBackThreads); ++q) {
-                const int i = tid + q * kBackThreads;
-                if (i > j && i < n) z[i] -= f * v[i];
-            }
-            par ^= 1;
+            for (int q = 0; q < SL; ++q) z[q] -= f * v[u][q];
+            load(j0 - u - kBackAhead, v[u], tj[u]);
         }
     }
-    __syncthreads();
-    for (int i = tid; i < n; i += kBackThreads) J.Z[(size_t)c0 * n + i] = z[i];
+#pragma unroll
+    for (int q = 0; q < SL; ++q) {
+        const int i = tid + 64 * NW * q;
+        if (i < n) J.Z[(size_t)bm.y * n + i] = z[q];
+    }
 }
+// Shapes of the back-transformation by the largest order of a launch.
+struct BackShape {
+    int nmax, threads;
+    const void* fn;
+};
+const BackShape kBackShapes[] = {
+    {128, 64, (const void*)backtr_kernel<1, 2>},   {256, 64, (const void*)backtr_kernel<1, 4>},
+    {512, 64, (const void*)backtr_kernel<1, 8>},   {704, 64, (const void*)backtr_kernel<1, 11>},
+    {1024, 256, (const void*)backtr_kernel<4, 4>}, {2048, 256, (const void*)backtr_kernel<4, 8>},
+    {3328, 256, (const void*)backtr_kernel<4, 13>}};
 
 struct DevInfo {
     int lds = 0, cus = 0;
@@ -942,17 +1150,22 @@ DevInfo dev_info() {
     return di;
 }
 
-// LDS rows per workgroup and workgroups of a job of order n (0, 0 if it
-// does not fit the chip's LDS).
-void tridiag_shape(int n, const DevInfo& di, int& R, int& G) {
-    R = G = 0;
-    const int64_t doubles = di.lds / 8 - 4LL * n - 2 * kTriWaves - 2;
-    if (n <= 0 || doubles < n) return;
-    R = (int)std::min<int64_t>(doubles / n, n);
-    G = (n + R - 1) / R;
-    // the vector steps' limits: rows per back-transformation thread and the
-    // LDS of their blocks of vectors
-    if (G > di.cus || n > kSlots * kTriThreads || 8LL * (3 * n + 4) > di.lds) R = G = 0;
+// Variant and workgroups of a job of order n (G = 0: it does not fit).
+size_t tridiag_lds(const TridVariant& v) {   // Trid::LDS
+    const int nw = v.T / 64, wr = nw / v.WC, nq = v.T * ((v.CW + wr - 1) / wr), np = v.nmax();
+    return 8 * (size_t)(2 * nq + 2 * (v.rows() + 64) + (wr > 1 ? 2 * nq : 0) + (v.rows() >= np ? 2 * np : 0) + 2 * nw +
+                        (v.WC > 1 ? nw * (v.RW + 3) : 0) + 2 + wr * v.RL * np);
+}
+void tridiag_shape(int n, const DevInfo& di, int& variant, int& G) {
+    variant = G = 0;
+    if (n <= 0) return;
+    while (variant < kTridVariantsN && kTridVariants[variant].nmax() < n) ++variant;
+    if (variant == kTridVariantsN) return;
+    const TridVariant& v = kTridVariants[variant];
+    const int g = (n + v.rows() - 1) / v.rows();
+    // the vector steps hold T and its factorisations (5 n) in LDS
+    if (g > di.cus || tridiag_lds(v) > (size_t)di.lds || 40LL * n > di.lds) return;
+    G = g;
 }
 
 // Descriptors go to the device through a ring of pinned host memory and an
@@ -1032,10 +1245,11 @@ void set_lds_limits(const DevInfo& di) {
     HIPCHK(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lk(mu);
     if (done.count(dev)) return;
-    const char* names[] = {"tridiag", "bisect", "backtr", "tdvec", "twist"};
-    const void* fns[] = {(const void*)tridiag_kernel, (const void*)bisect_kernel, (const void*)backtr_kernel,
-                         (const void*)tdvec_kernel, (const void*)twist_kernel};
-    for (int i = 0; i < 5; ++i) {
+    const char* names[] = {"tridiag", "tridiag_wide", "bisect", "cluster", "cluster", "twist"};
+    const void* fns[] = {(const void*)tridiag_kernel, (const void*)tridiag_wide_kernel, (const void*)bisect_kernel,
+                         (const void*)cluster_kernel<true>, (const void*)cluster_kernel<false>,
+                         (const void*)twist_kernel};
+    for (int i = 0; i < 6; ++i) {
         const hipError_t e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, di.lds);
         if (e != hipSuccess)
             fail(SYMTEN_E_HIP, std::string("eigh: dynamic LDS limit of the ") + names[i] + " kernel: " +
@@ -1044,11 +1258,11 @@ void set_lds_limits(const DevInfo& di) {
     done.insert(dev);
 }
 
-// Doubles of a job's exchange area: maxima and XCC ids, then two regions
-// of n rounded up to 16 doubles per column.
-size_t xbuf_doubles(int n, int G) {
-    const size_t npad = ((size_t)n + 15) & ~(size_t)15;
-    return (((size_t)2 * G + 15) & ~(size_t)15) + 2 * (size_t)n * npad;
+// Doubles of a job's exchange area: maxima and XCC ids, then per column the
+// p slices of its workgroups and the published row.
+size_t xbuf_doubles(int n, const TridVariant& v, int G) {
+    const size_t npad = v.nmax(), gr = ((size_t)G * v.rows() + 15) & ~(size_t)15;
+    return (((size_t)2 * G + 15) & ~(size_t)15) + (size_t)n * (npad + gr);
 }
 
 }  // namespace
@@ -1087,30 +1301,34 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
     const int np = (int)probs.size();
     if (np == 0) return wk;
     const DevInfo di = dev_info();
-    std::vector<int> Rs(np), Gs(np);
-    size_t doubles = 0;
+    std::vector<int> Vs(np), Gs(np);
+    size_t doubles = 0, xdoubles = 0;
     int nmax = 0;
     for (int p = 0; p < np; ++p) {
         const int n = probs[p].n;
         if (n < 1 || probs[p].lda < n || !probs[p].A || !probs[p].w) fail(SYMTEN_E_INVAL, "eigh: bad problem");
-        tridiag_shape(n, di, Rs[p], Gs[p]);
-        if (Gs[p] == 0) fail(SYMTEN_E_CAPACITY, "eigh: matrix of order " + std::to_string(n) + " exceeds the LDS of the chip");
-        doubles += 3 * (size_t)n + (size_t)n * n + 1 + xbuf_doubles(n, Gs[p]);
+        tridiag_shape(n, di, Vs[p], Gs[p]);
+        if (Gs[p] == 0) fail(SYMTEN_E_CAPACITY, "eigh: matrix of order " + std::to_string(n) + " exceeds the registers of the chip");
+        xdoubles += xbuf_doubles(n, kTridVariants[Vs[p]], Gs[p]);
+        doubles += 3 * (size_t)n + (size_t)n * v_stride(n) + 1;
         nmax = std::max(nmax, n);
     }
+    doubles += xdoubles;
     BufferPtr buf = device_alloc(8 * doubles + 8 * (size_t)np * 2);
-    BufferPtr ibuf = device_alloc(sizeof(int) * 2 * (size_t)np);
-    launch_fill_zero(ibuf->ptr, sizeof(int) * 2 * (int64_t)np, s);
+    BufferPtr ibuf = device_alloc(sizeof(int) * (size_t)np);
+    launch_fill_zero(ibuf->ptr, sizeof(int) * (int64_t)np, s);
     wk->keep = {buf, ibuf};
-    int* counters = (int*)ibuf->ptr;
-    wk->status = counters + np;
+    wk->status = (int*)ibuf->ptr;
     std::vector<TridJob> tj(np);
     // the exchange areas first (each a multiple of 16 doubles, so each
     // starts on a 128-byte line of the pool's aligned block), then the rest
     double* q = (double*)buf->ptr;
+    hipLaunchKernelGGL(fill_empty_kernel, dim3((unsigned)std::min<size_t>((xdoubles + 255) / 256, 4096)), dim3(256), 0,
+                       s, (uint64_t*)buf->ptr, (int64_t)xdoubles);
+    HIPCHK(hipGetLastError());
     for (int p = 0; p < np; ++p) {
         tj[p].xbuf = q;
-        q += xbuf_doubles(probs[p].n, Gs[p]);
+        q += xbuf_doubles(probs[p].n, kTridVariants[Vs[p]], Gs[p]);
     }
     for (int p = 0; p < np; ++p) {
         const int n = probs[p].n;
@@ -1119,13 +1337,12 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
         J.n = n;
         J.lda = probs[p].lda;
         J.G = Gs[p];
-        J.R = Rs[p];
+        J.variant = Vs[p];
+        J.V = q; q += (size_t)n * v_stride(n);
         J.d = q; q += n;
         J.e = q; q += n;
         J.tau = q; q += n;
-        J.V = q; q += (size_t)n * n;
         J.scale = q; q += 1;
-        J.counter = counters + p;
         J.status = probs[p].status ? probs[p].status : wk->status + p;
         wk->d.push_back(J.d);
         wk->e.push_back(J.e);
@@ -1139,22 +1356,25 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
     // workgroups) takes blocks b = x (mod 8) of one XCD x
     std::vector<int> order(np);
     for (int p = 0; p < np; ++p) order[p] = p;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return Gs[a] > Gs[b]; });
+    auto wide = [&](int p) { return Vs[p] >= kTridWide; };   // 512-thread jobs are launched apart
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        return wide(a) != wide(b) ? wide(a) : Gs[a] > Gs[b];
+    });
     const int per_xcd = std::max(1, di.cus / 8);
     std::vector<std::vector<int>> launches;
     {
-        std::vector<int> cur;
-        int used = 0;
+        // largest first, each into the first launch of its kind with room
+        std::vector<int> used;
         for (int p : order) {
-            if (used + Gs[p] > di.cus) {
-                launches.push_back(cur);
-                cur.clear();
-                used = 0;
+            size_t l = 0;
+            while (l < launches.size() && (wide(launches[l][0]) != wide(p) || used[l] + Gs[p] > di.cus)) ++l;
+            if (l == launches.size()) {
+                launches.emplace_back();
+                used.push_back(0);
             }
-            cur.push_back(p);
-            used += Gs[p];
+            launches[l].push_back(p);
+            used[l] += Gs[p];
         }
-        if (!cur.empty()) launches.push_back(cur);
     }
     const size_t lds_bytes = (size_t)di.lds;
     set_lds_limits(di);
@@ -1199,8 +1419,10 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
         int64_t flops = 0;   // Householder tridiagonalisation: 4/3 n^3 (FP64)
         for (int p : L) flops += 4 * (int64_t)probs[p].n * probs[p].n * probs[p].n / 3;
         profile_launch("eigh_tridiag", flops, flops, 0, s, [&] {
-            HIPCHK(hipLaunchCooperativeKernel((const void*)tridiag_kernel, dim3((unsigned)bmap.size()),
-                                              dim3(kTriThreads), args, (unsigned)lds_bytes, s));
+            const bool wd = wide(L[0]);
+            HIPCHK(hipLaunchCooperativeKernel(wd ? (const void*)tridiag_wide_kernel : (const void*)tridiag_kernel,
+                                              dim3((unsigned)bmap.size()), dim3(wd ? 512 : 256), args,
+                                              (unsigned)lds_bytes, s));
         });
     }
     // ---- step 2: one wave per eigenvalue, four per workgroup
@@ -1247,7 +1469,8 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
         fail(SYMTEN_E_INVAL, "eigh_vectors: one entry per problem");
     // clusters of close eigenvalues (descending), from the host copy of w
     std::vector<VecCluster> cl;
-    size_t ztot = 0;
+    size_t ztot = 0, worktot = 0;
+    int nvec = 0, nmax = 0, ncmax = 0;
     for (int p = 0; p < np; ++p) {
         const int n = wk.probs[p].n, k = kv[p];
         if (k < 0 || k > n) fail(SYMTEN_E_INVAL, "eigh_vectors: vector count out of range");
@@ -1255,26 +1478,24 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
         const double* w = w_host[p];
         const double tn = std::max(std::fabs(w[0]), std::fabs(w[n - 1]));
         const double ortol = 1e-3 * tn;
+        nvec += k;
+        nmax = std::max(nmax, n);
         int j = 0;
         while (j < k) {
             int c = 1;
             while (j + c < k && w[n - 1 - (j + c - 1)] - w[n - 1 - (j + c)] <= ortol) ++c;
-            cl.push_back(VecCluster{p, j, c, 0});
+            if (c > 1) {
+                cl.push_back(VecCluster{p, j, c, 0, (int64_t)worktot});
+                worktot += 5 * (size_t)n;
+                ncmax = std::max(ncmax, n);
+            }
             j += c;
         }
         ztot += (size_t)n * k;
     }
-    if (cl.empty()) return;
-    std::stable_partition(cl.begin(), cl.end(), [](const VecCluster& c) { return c.count == 1; });
-    int n_single = 0;
-    for (auto& c : cl) n_single += c.count == 1;
-    size_t worktot = 0;
-    for (auto& c : cl) {
-        c.woff = (int64_t)worktot;
-        worktot += 5 * (size_t)wk.probs[c.job].n;
-    }
+    if (nvec == 0) return;
     BufferPtr zt = device_alloc(8 * ztot);
-    BufferPtr work = device_alloc(8 * worktot);
+    BufferPtr work = device_alloc(8 * std::max<size_t>(worktot, 1));
     std::vector<VecJob> vj(np);
     std::vector<BackJob> bj(np);
     std::vector<int2> bmap;
@@ -1296,38 +1517,35 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
     BufferPtr db;
     upload_async(db, host.data(), host.size(), s);
     const char* base = (const char*)db->ptr;
-    int nmax = 0;
-    for (auto& pr : wk.probs) nmax = std::max(nmax, pr.n);
     const DevInfo di = dev_info();
     set_lds_limits(di);
-    const size_t lv = 8 * 8 * (size_t)nmax;
-    // reflectors per chunk: the registers of a chunk's loads (its doubles,
-    // plus one pair at each end) and LDS bound it
-    const int ch = (int)std::max<int64_t>(1, std::min<int64_t>(kChunk, (2LL * kChunkLoads * kBackThreads - 4) / nmax));
-    const size_t lb = 8 * ((size_t)(ch + 2) * nmax + 4);
-    if (lb > (size_t)di.lds || lv > (size_t)di.lds || nmax > kSlots * kTriThreads)
-        fail(SYMTEN_E_CAPACITY, "eigh: vectors exceed LDS");
-    // clusters of one first in the list (the twisted factorisation), then
-    // the rest (inverse iteration with reorthogonalisation)
-    const int nsingle = n_single;
-    if (nsingle > 0)
-        profile_launch("eigh_twist", 0, 0, 0, s, [&] {
-            hipLaunchKernelGGL(twist_kernel, dim3((unsigned)nsingle), dim3(128), 8 * 5 * (size_t)nmax, s,
-                               (const VecJob*)base, (const VecCluster*)(base + b1));
-            HIPCHK(hipGetLastError());
-        });
-    if ((int)cl.size() > nsingle)
-        profile_launch("eigh_tdvec", 0, 0, 0, s, [&] {
-            hipLaunchKernelGGL(tdvec_kernel, dim3((unsigned)(cl.size() - nsingle)), dim3(64), lv, s,
-                               (const VecJob*)base, (const VecCluster*)(base + b1) + nsingle);
+    const BackShape* bs = nullptr;
+    for (auto& x : kBackShapes)
+        if (!bs && x.nmax >= nmax) bs = &x;
+    if (!bs || 40 * (size_t)nmax > (size_t)di.lds) fail(SYMTEN_E_CAPACITY, "eigh: vectors exceed the registers or LDS");
+    const VecJob* dvj = (const VecJob*)base;
+    const int2* dmap = (const int2*)(base + b1 + b2 + b3);
+    profile_launch("eigh_twist", 0, 0, 0, s, [&] {
+        hipLaunchKernelGGL(twist_kernel, dim3((unsigned)nvec), dim3(128), 40 * (size_t)nmax, s, dvj, dmap);
+        HIPCHK(hipGetLastError());
+    });
+    if (!cl.empty())
+        profile_launch("eigh_cluster", 0, 0, 0, s, [&] {
+            const VecCluster* dcl = (const VecCluster*)(base + b1);
+            if (64 * (size_t)ncmax <= (size_t)di.lds)
+                hipLaunchKernelGGL(cluster_kernel<true>, dim3((unsigned)cl.size()), dim3(64), 64 * (size_t)ncmax, s,
+                                   dvj, dcl);
+            else
+                hipLaunchKernelGGL(cluster_kernel<false>, dim3((unsigned)cl.size()), dim3(64), 24 * (size_t)ncmax, s,
+                                   dvj, dcl);
             HIPCHK(hipGetLastError());
         });
     int64_t bflops = 0;   // back-transformation: 2 n^2 per vector
     for (int p = 0; p < np; ++p) bflops += 2 * (int64_t)wk.probs[p].n * wk.probs[p].n * kv[p];
     profile_launch("eigh_backtr", bflops, bflops, 0, s, [&] {
-        hipLaunchKernelGGL(backtr_kernel, dim3((unsigned)bmap.size()), dim3(kBackThreads), lb, s,
-                           (const BackJob*)(base + b1 + b2), (const int2*)(base + b1 + b2 + b3), ch);
-        HIPCHK(hipGetLastError());
+        const BackJob* dbj = (const BackJob*)(base + b1 + b2);
+        void* args[] = {(void*)&dbj, (void*)&dmap};
+        HIPCHK(hipLaunchKernel(bs->fn, dim3((unsigned)nvec), dim3((unsigned)bs->threads), args, 0, s));
     });
     wk.keep.push_back(zt);
     wk.keep.push_back(work);
