@@ -501,19 +501,6 @@ __global__ void vec_to_uv_kernel(const double* __restrict__ Zk, int NE, int k, i
     if (jw)
         for (int r = threadIdx.x; r < rd; r += blockDim.x) V[r + (int64_t)j * rd] = f * Zk[ru + r + (int64_t)j * NE];
 }
-// Compact Jordan-Wielandt matrix [[0, Y], [Y^T, 0]] of order ru + rd from
-// Y (ru x rd, column-major, ld ru).
-__global__ void jw_build_compact_kernel(const double* __restrict__ Y, int ru, int rd, double* __restrict__ J) {
-    const int N = ru + rd;
-    const int64_t tot = (int64_t)N * N;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < tot; i += (int64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(i % N), c = (int)(i / N);
-        double v = 0.0;
-        if (r < ru && c >= ru) v = Y[r + (int64_t)(c - ru) * ru];
-        else if (r >= ru && c < ru) v = Y[c + (int64_t)(r - ru) * ru];
-        J[i] = v;
-    }
-}
 // Non-finite entries of X (NaN, Inf) are replaced by 0 and reported in
 // *flag, so that the eigensolver only ever sees finite matrices; the move
 // then fails after the read-back (SYMTEN_E_LINALG).
@@ -586,12 +573,6 @@ void launch_eigval_to_s(const double* w, int NE, int mn, bool jw, double* S, hip
 void launch_vec_to_uv(const double* Zk, int NE, int k, int ru, int rd, bool jw, double* U, double* V, hipStream_t st) {
     if (k <= 0) return;
     hipLaunchKernelGGL(vec_to_uv_kernel, dim3((unsigned)k), dim3(256), 0, st, Zk, NE, k, ru, rd, jw ? 1 : 0, U, V);
-    HIPCHK(hipGetLastError());
-}
-void launch_jw_build_compact(const double* Y, int ru, int rd, double* J, hipStream_t st) {
-    const int64_t N = (int64_t)ru + rd;
-    if (N <= 0) return;
-    hipLaunchKernelGGL(jw_build_compact_kernel, dim3((unsigned)g1d(N * N)), dim3(256), 0, st, Y, ru, rd, J);
     HIPCHK(hipGetLastError());
 }
 void launch_pad_blocks(const PadArgs& a, double* dst, hipStream_t st) {
@@ -799,9 +780,8 @@ void solve_class(const std::vector<CutSector>& secs, std::vector<ProjWork>& w, c
 
 // The library's own eigensolver (every eigenproblem of the given cuts fits
 // its LDS): per sector, H_u^T and H_d^T as FP64 col-major blocks, Y = H_u^T
-// H_d (ru x rd, compact), its Gram or compact Jordan-Wielandt matrix; then
-// one set of launches tridiagonalises every matrix of every cut and finds
-// all eigenvalues, and each sector's singular values are taken from them.
+// H_d (ru x rd, compact) and, but in FP64 moves, its Gram matrix; then one set
+// of launches reduces every matrix of every cut and finds all eigenvalues, and each sector's singular values are taken from them.
 // Everything is enqueued on s; no host thread, no side stream.
 std::vector<ProjPending> issue_solves_own(ctm_env* env, const std::vector<std::vector<CutSector>*>& cuts, bool f64,
                                           hipStream_t s) {
@@ -860,24 +840,29 @@ std::vector<ProjPending> issue_solves_own(ctm_env* env, const std::vector<std::v
             x.nonfinite = head;
             launch_nonfinite_guard(x.Y, (int64_t)b.mu * b.md, x.nonfinite, s);
             x.ne = f64 ? b.mu + b.md : b.mu;
-            BufferPtr Ab = device_alloc(8 * (size_t)x.ne * x.ne);
-            if (f64)
-                launch_jw_build_compact(x.Y, b.mu, b.md, (double*)Ab->ptr, s);
-            else
+            BufferPtr Ab;
+            if (!f64) {
+                Ab = device_alloc(8 * (size_t)x.ne * x.ne);
                 rb_check(rocblas_dgemm(env->rb, rocblas_operation_none, rocblas_operation_transpose, b.mu, b.mu, b.md,
                                        &one, x.Y, x.ldy, x.Y, x.ldy, &zero, (double*)Ab->ptr, x.ne),
                          "rocblas_dgemm(YY^T)");
+            }
             x.w = area + pc.w_off[i];
             x.sdev = area + pc.s_off[i];
             x.prob = (int)probs.size();
             EighProblem ep;
             ep.n = x.ne;
-            ep.lda = x.ne;
-            ep.A = (const double*)Ab->ptr;
+            ep.lda = f64 ? x.ldy : x.ne;
+            ep.A = f64 ? x.Y : (const double*)Ab->ptr;
+            if (f64) {   // the Jordan-Wielandt matrix of Y, never formed
+                ep.ru = b.mu;
+                ep.rd = b.md;
+            }
             ep.w = x.w;
             ep.status = head + 1 + i;
             probs.push_back(ep);
-            for (auto& k : {Hb, Yb, Ab}) pc.keep_alive.push_back(k);
+            for (auto& k : {Hb, Yb, Ab})
+                if (k) pc.keep_alive.push_back(k);
         }
     }
     auto wk = eigh_values(probs, s);
@@ -895,7 +880,7 @@ std::vector<ProjPending> issue_solves_own(ctm_env* env, const std::vector<std::v
 bool own_solver_fits(const std::vector<std::vector<CutSector>*>& cuts, bool f64) {
     for (auto* secs : cuts)
         for (auto& b : *secs)
-            if (!eigh_fits(f64 ? b.mu + b.md : b.mu)) return false;
+            if (f64 ? !eigh_jw_fits(b.mu, b.md) : !eigh_fits(b.mu)) return false;
     return true;
 }
 

@@ -30,6 +30,7 @@
 // The matrix is scaled by a power of two (exact) so that its largest entry
 // is in [1, 2); eigenvalues are returned unscaled.
 #include <algorithm>
+#include <array>
 #include <cfloat>
 #include <cmath>
 #include <cstring>
@@ -642,10 +643,371 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
+// Step 1 for a Jordan-Wielandt matrix [[0, Y], [Y^T, 0]] (FP64 moves).  With
+// its states in the order u_0, v_0, u_1, v_1, ... the reduction above keeps the
+// zero blocks: column 2i (state u_i) has entries on the v side only, its
+// reflector acts on v_i .. , p = tau M v lives on the u side, so p . v = 0,
+// w = p, and T has a zero diagonal (the Golub-Kahan form of Y).  Held as such
+// it takes Y and Y^T (2 m^2 values instead of 4 m^2 for the joint matrix) and
+// one sum per column.  Column 2i+1 (state v_i) mirrors it: reflector on
+// u_(i+1) .., p on the v side.
+struct BidJob {
+    const double* Y;                   // nu x nv, column-major (ld ldy)
+    int nu, nv, ldy, G, variant;
+    double *d, *e, *scale;             // T of order nu + nv, scaled by *scale
+    double *V[2], *tau[2];             // reflectors and factors of the v side (0) and the u side (1)
+    double* xbuf;                      // exchange area (bid_xbuf_doubles), filled with kEmpty
+    int* status;
+};
+// Columns of T that are formed (the last one without an exchange); the rest of
+// the states (of the longer side) are decoupled zeros.
+__host__ __device__ inline int bid_columns(int nu, int nv) { return nu > nv ? 2 * nv : 2 * nu - 1; }
+
+// One workgroup of a job: rows i = g + G (wr + WR s) of Y (lanes along v) and
+// of Y^T (lanes along u), both in registers.  Per column h (i = h / 2, side
+// s = h & 1; "here" the reflector's side, "there" the other one):
+//  (a) the reflector, each thread its entries; {w, v} here to every wave;
+//  (b) the owner publishes the next column as its rows hold it, which is
+//      before the updates of columns h-1 and h;
+//  (c) one pass over the rows > i there: the updates of columns h-2 and h-1,
+//      then p = tau row . v;
+//  (d) every thread polls p and the next column and applies the two updates.
+// Row scalars of a pass are the pairs that (a) of column h-1 shared.  Bound
+// like the symmetric reduction by its serial chain, two LDS rounds and one
+// exchange per column: 2.4 us per column at m = 696 (29 workgroups of one XCD).
+template <int WC, int CW, int RW>
+struct Bid {
+    static constexpr int T = 512, NW = T / 64, WR = NW / WC, R = RW * WR;
+    static constexpr int NP = 64 * WC * CW;
+    static constexpr int PQ = (CW + WR - 1) / WR, NQ = T * PQ;
+    static constexpr bool SOLO = R >= NP;
+    // LDS, in doubles: the next column; {w, v} of both sides; one workgroup:
+    // raw p and next column; sums; partial row sums
+    static constexpr int PAIRS = 2 * (NQ > NP + R ? NQ : NP + R);
+    static constexpr int LX = 0, LVW = LX + NQ, LRAW = LVW + 2 * PAIRS, LRED = LRAW + (SOLO ? 2 * NP : 0),
+                         LPART = LRED + NW, LFAIL = LPART + (WC > 1 ? NW * (RW + 3) : 0), LDS = LFAIL + 2;
+
+    struct State {
+        const BidJob& J;
+        double* sm;
+        gu64* reg;
+        double sc;
+        double x[PQ], part;            // the column here, its squared norm below the leading entry (this thread's share)
+        double wq[2][PQ], vq[2][PQ];   // w and v per side at this thread's columns (0: v side)
+        double v[2][CW];               // v per side at this lane's columns
+        uint32_t place[PQ];
+        int g, G, region, gr, own_r, own;   // row i + s of the side here: workgroup own, local row own_r
+        bool local;
+    };
+
+    template <int S>
+    static __device__ __forceinline__ void column(State& z, const int i, const bool last, double (&a)[RW][CW],
+                                                  double (&at)[RW][CW]) {
+        // a: rows there (lanes here); at: rows here (lanes there)
+        const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int wc = w % WC, wr = w / WC;
+        double* sm = z.sm;
+        const int n = S ? z.J.nu : z.J.nv, no = S ? z.J.nv : z.J.nu;   // entries here, there
+        const int L = i + S;                                         // leading entry here
+        auto* failed = (LOCAL_MEM volatile int*)(sm + LFAIL);
+        // (a)
+#pragma unroll
+        for (int q = 0; q < PQ; ++q) sm[LX + tid + T * q] = z.x[q];
+        const double ps = wave_sum(z.part);
+        if (lane == 0) sm[LRED + w] = ps;
+        __syncthreads();
+        double xn2 = 0.0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) xn2 += sm[LRED + q];
+        double beta, tau, scal;
+        householder(sm[LX + L], xn2, beta, tau, scal);
+#pragma unroll
+        for (int q = 0; q < PQ; ++q) {
+            const int j = tid + T * q;
+            z.vq[S][q] = j > L && (T * (q + 1) <= NP || j < NP) ? z.x[q] * scal : (j == L ? 1.0 : 0.0);
+            *(double2*)(sm + LVW + S * PAIRS + 2 * j) = make_double2(z.wq[S][q], z.vq[S][q]);
+        }
+        __syncthreads();
+        const int ldv = v_stride(n);
+        if (SOLO || z.g == z.own) {   // the owner of row L here stores the reflector
+            gf64* V = (gf64*)z.J.V[S] + (size_t)i * ldv;
+#pragma unroll
+            for (int q = 0; q < PQ; ++q)
+                if (64 * w + T * q < ldv) *at8(V, tid + T * q) = z.vq[S][q];
+            if (tid == 0) {
+                ((gf64*)z.J.tau[S])[i] = tau;
+                ((gf64*)z.J.e)[2 * i + S] = beta;
+            }
+        }
+        if (last) return;
+        // (b) row L here holds the next column
+        if ((SOLO || z.g == z.own) && z.own_r % WR == wr) {
+            const int sp = z.own_r / WR;
+#pragma unroll
+            for (int s = 0; s < RW; ++s) {
+                if (s == sp) {
+                    if (SOLO) {
+#pragma unroll
+                        for (int c = 0; c < CW; ++c) sm[LRAW + NP + lane + 64 * (wc + WC * c)] = at[s][c];
+                    } else if (z.local) {
+#pragma unroll
+                        for (int c = 0; c < CW; ++c) put_x<true>(z.reg + z.gr, lane + 64 * (wc + WC * c), at[s][c]);
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < CW; ++c) put_x<false>(z.reg + z.gr, lane + 64 * (wc + WC * c), at[s][c]);
+                    }
+                }
+            }
+        }
+        // (c)
+        const int c_lo = max(L - 64 * wc, 0) / (64 * WC);
+        double vA[CW], wA[CW];
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+            const double2 t = *(const double2*)(sm + LVW + S * PAIRS + 2 * (lane + 64 * (wc + WC * c)));
+            vA[c] = z.v[S][c];
+            wA[c] = t.x;
+            z.v[S][c] = t.y;
+        }
+        // rows > i there: local rows >= rmin
+        const int ri = S ? z.own_r : z.own_r, rmin = S ? (z.g < z.own ? ri + 1 : ri) : (z.g <= z.own ? ri + 1 : ri);
+        const int s_lo = (max(rmin - wr, 0) + WR - 1) / WR;
+        double* part_s = sm + LPART;
+#pragma unroll
+        for (int s0 = 0; s0 < RW; s0 += kRowGroup) {
+            if (s0 + kRowGroup > s_lo) {
+                double vu[kRowGroup], wu[kRowGroup], acc[kRowGroup];
+#pragma unroll
+                for (int u = 0; u < kRowGroup; ++u) {
+                    acc[u] = 0.0;
+                    if (s0 + u < RW) {
+                        const double2 t = *(const double2*)(sm + LVW + (1 - S) * PAIRS +
+                                                            2 * (z.g + z.G * (wr + WR * (s0 + u))));
+                        wu[u] = t.x;   // w of column h-2, v of column h-1
+                        vu[u] = t.y;
+                    }
+                }
+#pragma unroll
+                for (int c0 = 0; c0 < CW; c0 += kColGroup) {
+                    if (c0 + kColGroup > c_lo) {
+#pragma unroll
+                        for (int c = c0; c < c0 + kColGroup && c < CW; ++c) {
+#pragma unroll
+                            for (int u = 0; u < kRowGroup && s0 + u < RW; ++u) {
+                                double y = a[s0 + u][c];
+                                y = fma(-wu[u], vA[c], y);
+                                y = fma(-vu[u], wA[c], y);
+                                a[s0 + u][c] = y;
+                                acc[u] = fma(y, z.v[S][c], acc[u]);
+                            }
+                        }
+                    }
+                }
+                const double t = four_sums(acc);
+                const int s = s0 + reduced_row(lane >> 4);
+                if ((lane & 15) == 0 && s < RW) {
+                    if constexpr (WC > 1) part_s[w * (RW + 3) + s] = t;
+                    else if constexpr (SOLO) sm[LRAW + wr + WR * s] = tau * t;
+                    else put_x(z.reg, z.g * R + wr + WR * s, tau * t, z.local);
+                }
+            }
+        }
+        if constexpr (WC > 1) {
+            __syncthreads();
+            if (tid < R) {
+                double y = 0.0;
+#pragma unroll
+                for (int q = 0; q < WC; ++q) y += part_s[((tid % WR) * WC + q) * (RW + 3) + tid / WR];
+                put_x(z.reg, z.g * R + tid, tau * y, z.local);
+            }
+        }
+        // (d)
+        double pr[PQ], rr[PQ];
+        if constexpr (SOLO) {
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < PQ; ++q) {
+                pr[q] = sm[LRAW + min(tid + T * q, NP - 1)];
+                rr[q] = sm[LRAW + NP + min(tid + T * q, NP - 1)];
+            }
+        } else {
+            uint64_t pu[PQ], ru[PQ];
+#pragma unroll
+            for (int q = 0; q < PQ; ++q) pu[q] = ru[q] = 0;
+            for (int polls = 0;;) {
+                bool empty = false;
+#pragma unroll
+                for (int q = 0; q < PQ; ++q) {
+                    if (T * q + 64 * w + 63 > i && T * q + 64 * w < no) {
+                        pu[q] = get_x(z.reg, z.place[q]);
+                        ru[q] = get_x(z.reg + z.gr, tid + T * q);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < PQ; ++q)
+                    empty |= (pu[q] == kEmpty && (unsigned)(tid + T * q - i - 1) < (unsigned)(no - i - 1)) ||
+                             ru[q] == kEmpty;
+                if (!__any(empty) || *failed) break;
+                if (++polls > kSpinLimit) {
+                    *failed = 1;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < PQ; ++q) {
+                pr[q] = __builtin_bit_cast(double, pu[q]);
+                rr[q] = __builtin_bit_cast(double, ru[q]);
+            }
+            z.reg += z.region;
+        }
+        const double wl = sm[LVW + S * PAIRS + 2 * L];   // w of column h-1 at row L here
+        z.part = 0.0;
+#pragma unroll
+        for (int q = 0; q < PQ; ++q) {
+            const int j = tid + T * q;
+            const double p = (unsigned)(j - i - 1) < (unsigned)(no - i - 1) ? pr[q] : 0.0;
+            z.wq[1 - S][q] = p;
+            z.x[q] = fma(-wl, z.vq[1 - S][q], rr[q]) - p;
+            const double y = j >= i + 2 && (T * (q + 1) <= NP || j < NP) ? z.x[q] : 0.0;
+            z.part = fma(y, y, z.part);
+        }
+        if (S == 0) {   // row i + 1 comes next
+            if (++z.own == z.G) {
+                z.own = 0;
+                ++z.own_r;
+            }
+        }
+    }
+
+    static __device__ __forceinline__ void job(const BidJob& J, const int g, double* sm) {
+        const int nu = J.nu, nv = J.nv, G = SOLO ? 1 : J.G, N = nu + nv;
+        const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int wc = w % WC, wr = w / WC;
+        auto* failed = (LOCAL_MEM volatile int*)(sm + LFAIL);
+        const gf64* Y = (const gf64*)J.Y;
+        if (tid == 0) *failed = 0;
+        for (int j = tid; j < 2 * PAIRS; j += T) sm[LVW + j] = 0.0;
+        if (g == 0) {
+            gf64 *d = (gf64*)J.d, *e = (gf64*)J.e;
+            for (int j = tid; j < N; j += T) {
+                d[j] = 0.0;
+                if (j >= bid_columns(nu, nv)) e[j] = 0.0;
+            }
+        }
+        double au[RW][CW], av[RW][CW];   // rows of Y, rows of Y^T
+        double mx = 0.0;
+#pragma unroll
+        for (int s = 0; s < RW; ++s) {
+            const int i = g + G * (wr + WR * s);
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                const int j = lane + 64 * (wc + WC * c);
+                au[s][c] = i < nu && j < nv ? Y[i + (int64_t)j * J.ldy] : 0.0;
+                av[s][c] = i < nv && j < nu ? Y[j + (int64_t)i * J.ldy] : 0.0;
+                mx = fmax(mx, fmax(fabs(au[s][c]), fabs(av[s][c])));
+            }
+        }
+        __syncthreads();
+        mx = block_max<NW>(mx, sm + LRED);
+        bool local = true;
+        if constexpr (!SOLO) {
+            gu64* x0 = (gu64*)J.xbuf;
+            if (tid == 0) {
+                unsigned xcc;
+                __asm__ volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+                put_x<false>(x0, g, mx + 0.0);
+                put_x<false>(x0, G + g, (double)xcc);
+            }
+            double gm = 0.0, first = 0.0, lastx = 0.0;   // largest entry; 64 - smallest and 1 + largest id
+            for (int t = tid; t < 2 * G; t += T) {
+                uint64_t u = get_x(x0, t);
+                for (int polls = 0; u == kEmpty && !*failed; u = get_x(x0, t))
+                    if (++polls > kSpinLimit) *failed = 1;
+                const double x = __builtin_bit_cast(double, u);
+                if (t < G) gm = fmax(gm, x);
+                else {
+                    first = fmax(first, 64.0 - x);
+                    lastx = fmax(lastx, 1.0 + x);
+                }
+            }
+            mx = block_max<NW>(gm, sm + LRED);
+            first = block_max<NW>(first, sm + LRED);
+            lastx = block_max<NW>(lastx, sm + LRED);
+            local = first + lastx == 65.0;   // every workgroup of the job on one XCD
+        }
+        const double sc = mx > 0.0 && isfinite(mx) ? ldexp(1.0, -ilogb(mx)) : 1.0;
+        if (g == 0 && tid == 0) *(gf64*)J.scale = sc;
+#pragma unroll
+        for (int s = 0; s < RW; ++s)
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+                au[s][c] *= sc;
+                av[s][c] *= sc;
+            }
+        State z{J, sm};
+        z.g = g;
+        z.G = G;
+        z.gr = (G * R + 15) & ~15;
+        z.region = z.gr + NP;
+        z.reg = (gu64*)J.xbuf + ((2 * G + 15) & ~15);
+        z.local = local;
+        z.own = z.own_r = 0;
+        z.part = 0.0;
+#pragma unroll
+        for (int q = 0; q < PQ; ++q) {
+            const int j = tid + T * q, r = min(j, NP - 1) / G;
+            z.place[q] = min((min(j, NP - 1) - r * G) * R + r, G * R - 1);
+            z.x[q] = j < nv ? Y[(int64_t)j * J.ldy] * sc : 0.0;   // row 0 of Y
+            const double y = j >= 1 ? z.x[q] : 0.0;
+            z.part = fma(y, y, z.part);
+            z.wq[0][q] = z.wq[1][q] = z.vq[0][q] = z.vq[1][q] = 0.0;
+        }
+#pragma unroll
+        for (int c = 0; c < CW; ++c) z.v[0][c] = z.v[1][c] = 0.0;
+        const int H = bid_columns(nu, nv);
+#pragma unroll 1
+        for (int h = 0; h < H; h += 2) {
+            __asm__("" : "+s"(z.reg));
+            column<0>(z, h >> 1, h + 1 == H, au, av);
+            if (h + 1 < H) column<1>(z, h >> 1, h + 2 == H, av, au);
+        }
+        __syncthreads();
+        if (tid == 0 && *failed) *J.status = 1;
+    }
+};
+
+// Register shapes: (waves across the columns, column slots per lane, rows of Y
+// and of Y^T per wave), sides up to 64 WC CW.  Up to 768 a job fits one XCD.
+struct BidVariant {
+    int WC, CW, RW;
+    int nmax() const { return 64 * WC * CW; }
+    int rows() const { return RW * (8 / WC); }
+};
+const BidVariant kBidVariants[] = {{1, 2, 16}, {2, 2, 8}, {2, 3, 6}, {4, 2, 10}, {4, 3, 12}, {8, 2, 16}, {8, 3, 12}, {8, 4, 9}};
+constexpr int kBidVariantsN = sizeof(kBidVariants) / sizeof(kBidVariants[0]);
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void bidiag_kernel(
+    const BidJob* __restrict__ jobs, const int2* __restrict__ bmap) {
+    const int2 bm = bmap[blockIdx.x];
+    if (bm.x < 0) return;
+    const BidJob J = jobs[bm.x];
+    extern __shared__ double sm[];
+    switch (J.variant) {
+        case 0: Bid<1, 2, 16>::job(J, bm.y, sm); break;
+        case 1: Bid<2, 2, 8>::job(J, bm.y, sm); break;
+        case 2: Bid<2, 3, 6>::job(J, bm.y, sm); break;
+        case 3: Bid<4, 2, 10>::job(J, bm.y, sm); break;
+        case 4: Bid<4, 3, 12>::job(J, bm.y, sm); break;
+        case 5: Bid<8, 2, 16>::job(J, bm.y, sm); break;
+        case 6: Bid<8, 3, 12>::job(J, bm.y, sm); break;
+        default: Bid<8, 4, 9>::job(J, bm.y, sm); break;
+    }
+}
+
 struct BisJob {
     const double *d, *e, *scale;
     double* w;      // n eigenvalues, ascending, unscaled
     int n;
+    int half;       // > 0: spectrum +-, the `half` largest are found, the rest mirrored or zero
 };
 
 // Step 2.  bmap[b] = (job, first index); wave q of the workgroup finds the
@@ -680,8 +1042,15 @@ __global__ __launch_bounds__(kEigThreads) void bisect_kernel(const BisJob* __res
     hi += 2.0 * eps * tnorm * n + pivmin;
     const int j = bm.y + wave;
     if (j >= n) return;   // no block-wide synchronisation below
+    // the mirrored values: their places, and zeros between the two halves
+    const bool mirror = J.half > 0;
+    if (mirror && j == n - 1)
+        for (int i = J.half + lane; i < n - J.half; i += 64) J.w[i] = 0.0;
     if (tnorm == 0.0) {   // T = 0
-        if (lane == 0) J.w[j] = 0.0;
+        if (lane == 0) {
+            J.w[j] = 0.0;
+            if (mirror) J.w[n - 1 - j] = 0.0;
+        }
         return;
     }
     double a = lo, b = hi;
@@ -711,7 +1080,11 @@ __global__ __launch_bounds__(kEigThreads) void bisect_kernel(const BisJob* __res
         b = nb;
         if (stuck || b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)), eps * tnorm)) break;
     }
-    if (lane == 0) J.w[j] = 0.5 * (a + b) / *J.scale;
+    if (lane == 0) {
+        const double x = 0.5 * (a + b) / *J.scale;
+        J.w[j] = x;
+        if (mirror) J.w[n - 1 - j] = -x;
+    }
 }
 
 // Inverse iteration solves per eigenvector: from a random start, the first
@@ -1047,9 +1420,14 @@ __global__ __launch_bounds__(64) void cluster_kernel(const VecJob* __restrict__ 
 }
 
 struct BackJob {
-    const double *V, *tau, *Zt;
-    double* Z;      // n x kv, column-major
-    int n, kv;
+    const double *V, *tau, *Zt;   // reflectors; vectors of T (column j at Zt + j ldt)
+    double* Z;                    // column j at Z + j ldz, n entries
+    int n, count, ldt, ldz;       // entries, reflectors, strides
+    // entry j of the vector is row_of(j) of T's: all rows, or the u (side 0)
+    // or v (side 1) states of a Jordan-Wielandt matrix, `other` the size of
+    // the other side (their order alternates until one side ends)
+    int side, other;
+    __device__ int row_of(int j) const { return side < 0 ? j : (j < other + 1 - side ? 2 * j + side : other + j); }
 };
 
 // Step 4.  NW waves per eigenvector (bmap[b] = (job, vector)), which stays in
@@ -1070,11 +1448,11 @@ __global__ __launch_bounds__(64 * NW) void backtr_kernel(const BackJob* __restri
     const int n = J.n, ldv = v_stride(n), tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __shared__ double red[2][NW];
     double z[SL], v[kBackAhead][SL], tj[kBackAhead];
-    const double* zt = J.Zt + (size_t)bm.y * n;
+    const double* zt = J.Zt + (size_t)bm.y * J.ldt;
 #pragma unroll
     for (int q = 0; q < SL; ++q) {
         const int i = tid + 64 * NW * q;
-        z[q] = i < n ? zt[i] : 0.0;
+        z[q] = i < n ? zt[J.row_of(i)] : 0.0;
     }
     auto load = [&](int j, double (&vj)[SL], double& t) {
         const double* row = J.V + (size_t)max(j, 0) * ldv;
@@ -1086,9 +1464,9 @@ __global__ __launch_bounds__(64 * NW) void backtr_kernel(const BackJob* __restri
         }
     };
 #pragma unroll
-    for (int u = 0; u < kBackAhead; ++u) load(n - 2 - u, v[u], tj[u]);
+    for (int u = 0; u < kBackAhead; ++u) load(J.count - 1 - u, v[u], tj[u]);
     int par = 0;
-    for (int j0 = n - 2; j0 >= 0; j0 -= kBackAhead) {
+    for (int j0 = J.count - 1; j0 >= 0; j0 -= kBackAhead) {
 #pragma unroll
         for (int u = 0; u < kBackAhead; ++u) {
             double part = 0.0, part2 = 0.0;
@@ -1115,7 +1493,7 @@ __global__ __launch_bounds__(64 * NW) void backtr_kernel(const BackJob* __restri
 #pragma unroll
     for (int q = 0; q < SL; ++q) {
         const int i = tid + 64 * NW * q;
-        if (i < n) J.Z[(size_t)bm.y * n + i] = z[q];
+        if (i < n) J.Z[(size_t)bm.y * J.ldz + i] = z[q];
     }
 }
 // Shapes of the back-transformation by the largest order of a launch.
@@ -1165,6 +1543,23 @@ void tridiag_shape(int n, const DevInfo& di, int& variant, int& G) {
     const int g = (n + v.rows() - 1) / v.rows();
     // the vector steps hold T and its factorisations (5 n) in LDS
     if (g > di.cus || tridiag_lds(v) > (size_t)di.lds || 40LL * n > di.lds) return;
+    G = g;
+}
+
+size_t bid_lds(const BidVariant& v) {   // Bid::LDS
+    const int wr = 8 / v.WC, nq = 512 * ((v.CW + wr - 1) / wr), np = v.nmax();
+    return 8 * (size_t)(nq + 4 * std::max(nq, np + v.rows()) + (v.rows() >= np ? 2 * np : 0) + 8 +
+                        (v.WC > 1 ? 8 * (v.RW + 3) : 0) + 2);
+}
+void bid_shape(int ru, int rd, const DevInfo& di, int& variant, int& G) {
+    variant = G = 0;
+    const int m = std::max(ru, rd);
+    if (std::min(ru, rd) <= 0) return;
+    while (variant < kBidVariantsN && kBidVariants[variant].nmax() < m) ++variant;
+    if (variant == kBidVariantsN) return;
+    const BidVariant& v = kBidVariants[variant];
+    const int g = (m + v.rows() - 1) / v.rows();
+    if (g > di.cus || bid_lds(v) > (size_t)di.lds || 40LL * (ru + rd) > di.lds) return;
     G = g;
 }
 
@@ -1245,11 +1640,11 @@ void set_lds_limits(const DevInfo& di) {
     HIPCHK(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lk(mu);
     if (done.count(dev)) return;
-    const char* names[] = {"tridiag", "tridiag_wide", "bisect", "cluster", "cluster", "twist"};
-    const void* fns[] = {(const void*)tridiag_kernel, (const void*)tridiag_wide_kernel, (const void*)bisect_kernel,
-                         (const void*)cluster_kernel<true>, (const void*)cluster_kernel<false>,
-                         (const void*)twist_kernel};
-    for (int i = 0; i < 6; ++i) {
+    const char* names[] = {"tridiag", "tridiag_wide", "bidiag", "bisect", "cluster", "cluster", "twist"};
+    const void* fns[] = {(const void*)tridiag_kernel, (const void*)tridiag_wide_kernel, (const void*)bidiag_kernel,
+                         (const void*)bisect_kernel, (const void*)cluster_kernel<true>,
+                         (const void*)cluster_kernel<false>, (const void*)twist_kernel};
+    for (int i = 0; i < 7; ++i) {
         const hipError_t e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, di.lds);
         if (e != hipSuccess)
             fail(SYMTEN_E_HIP, std::string("eigh: dynamic LDS limit of the ") + names[i] + " kernel: " +
@@ -1260,6 +1655,10 @@ void set_lds_limits(const DevInfo& di) {
 
 // Doubles of a job's exchange area: maxima and XCC ids, then per column the
 // p slices of its workgroups and the published row.
+size_t bid_xbuf_doubles(int ru, int rd, const BidVariant& v, int G) {
+    const size_t gr = ((size_t)G * v.rows() + 15) & ~(size_t)15;
+    return (((size_t)2 * G + 15) & ~(size_t)15) + (size_t)bid_columns(ru, rd) * (v.nmax() + gr);
+}
 size_t xbuf_doubles(int n, const TridVariant& v, int G) {
     const size_t npad = v.nmax(), gr = ((size_t)G * v.rows() + 15) & ~(size_t)15;
     return (((size_t)2 * G + 15) & ~(size_t)15) + (size_t)n * (npad + gr);
@@ -1270,13 +1669,20 @@ size_t xbuf_doubles(int n, const TridVariant& v, int G) {
 struct EighWork {
     std::vector<EighProblem> probs;
     std::vector<BufferPtr> keep;
-    std::vector<double*> d, e, tau, V, scale, w;
+    std::vector<double*> d, e, scale, w;
+    std::vector<std::array<double*, 2>> tau, V;   // Jordan-Wielandt: v side, u side
     int* status = nullptr;               // one per problem
 };
 
 bool eigh_fits(int n) {
     int R, G;
     tridiag_shape(n, dev_info(), R, G);
+    return G > 0;
+}
+
+bool eigh_jw_fits(int ru, int rd) {
+    int v, G;
+    bid_shape(ru, rd, dev_info(), v, G);
     return G > 0;
 }
 
@@ -1302,15 +1708,25 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
     if (np == 0) return wk;
     const DevInfo di = dev_info();
     std::vector<int> Vs(np), Gs(np);
+    auto jw = [&](int p) { return probs[p].rd > 0; };
+    auto xbuf_of = [&](int p) {
+        return jw(p) ? bid_xbuf_doubles(probs[p].ru, probs[p].rd, kBidVariants[Vs[p]], Gs[p])
+                     : xbuf_doubles(probs[p].n, kTridVariants[Vs[p]], Gs[p]);
+    };
     size_t doubles = 0, xdoubles = 0;
     int nmax = 0;
     for (int p = 0; p < np; ++p) {
-        const int n = probs[p].n;
-        if (n < 1 || probs[p].lda < n || !probs[p].A || !probs[p].w) fail(SYMTEN_E_INVAL, "eigh: bad problem");
-        tridiag_shape(n, di, Vs[p], Gs[p]);
+        const EighProblem& P = probs[p];
+        const int n = P.n;
+        if (n < 1 || !P.A || !P.w || (jw(p) ? P.ru < 1 || P.ru + P.rd != n || P.lda < P.ru : P.lda < n))
+            fail(SYMTEN_E_INVAL, "eigh: bad problem");
+        if (jw(p)) bid_shape(P.ru, P.rd, di, Vs[p], Gs[p]);
+        else tridiag_shape(n, di, Vs[p], Gs[p]);
         if (Gs[p] == 0) fail(SYMTEN_E_CAPACITY, "eigh: matrix of order " + std::to_string(n) + " exceeds the registers of the chip");
-        xdoubles += xbuf_doubles(n, kTridVariants[Vs[p]], Gs[p]);
-        doubles += 3 * (size_t)n + (size_t)n * v_stride(n) + 1;
+        xdoubles += xbuf_of(p);
+        doubles += 2 * (size_t)n + 1;
+        doubles += jw(p) ? ((size_t)P.ru + P.rd) + (size_t)std::min(P.ru, P.rd) * (v_stride(P.ru) + v_stride(P.rd))
+                         : (size_t)n + (size_t)n * v_stride(n);
         nmax = std::max(nmax, n);
     }
     doubles += xdoubles;
@@ -1320,45 +1736,54 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
     wk->keep = {buf, ibuf};
     wk->status = (int*)ibuf->ptr;
     std::vector<TridJob> tj(np);
+    std::vector<BidJob> gj(np);
     // the exchange areas first (each a multiple of 16 doubles, so each
     // starts on a 128-byte line of the pool's aligned block), then the rest
     double* q = (double*)buf->ptr;
     hipLaunchKernelGGL(fill_empty_kernel, dim3((unsigned)std::min<size_t>((xdoubles + 255) / 256, 4096)), dim3(256), 0,
                        s, (uint64_t*)buf->ptr, (int64_t)xdoubles);
     HIPCHK(hipGetLastError());
+    std::vector<double*> xb(np);
     for (int p = 0; p < np; ++p) {
-        tj[p].xbuf = q;
-        q += xbuf_doubles(probs[p].n, kTridVariants[Vs[p]], Gs[p]);
+        xb[p] = q;
+        q += xbuf_of(p);
     }
     for (int p = 0; p < np; ++p) {
-        const int n = probs[p].n;
-        TridJob& J = tj[p];
-        J.A = probs[p].A;
-        J.n = n;
-        J.lda = probs[p].lda;
-        J.G = Gs[p];
-        J.variant = Vs[p];
-        J.V = q; q += (size_t)n * v_stride(n);
-        J.d = q; q += n;
-        J.e = q; q += n;
-        J.tau = q; q += n;
-        J.scale = q; q += 1;
-        J.status = probs[p].status ? probs[p].status : wk->status + p;
-        wk->d.push_back(J.d);
-        wk->e.push_back(J.e);
-        wk->tau.push_back(J.tau);
-        wk->V.push_back(J.V);
-        wk->scale.push_back(J.scale);
-        wk->w.push_back(probs[p].w);
+        const EighProblem& P = probs[p];
+        const int n = P.n;
+        std::array<double*, 2> V{}, tau{};
+        if (jw(p)) {
+            const int m = std::min(P.ru, P.rd);
+            V[0] = q; q += (size_t)m * v_stride(P.rd);
+            V[1] = q; q += (size_t)m * v_stride(P.ru);
+            tau[0] = q; q += P.rd;
+            tau[1] = q; q += P.ru;
+        } else {
+            V[0] = q; q += (size_t)n * v_stride(n);
+            tau[0] = q; q += n;
+        }
+        double* d = q; q += n;
+        double* e = q; q += n;
+        double* scale = q; q += 1;
+        int* status = P.status ? P.status : wk->status + p;
+        if (jw(p)) gj[p] = BidJob{P.A, P.ru, P.rd, P.lda, Gs[p], Vs[p], d, e, scale, {V[0], V[1]}, {tau[0], tau[1]}, xb[p], status};
+        else tj[p] = TridJob{P.A, n, P.lda, Gs[p], d, e, tau[0], V[0], scale, xb[p], status, Vs[p]};
+        wk->d.push_back(d);
+        wk->e.push_back(e);
+        wk->tau.push_back(tau);
+        wk->V.push_back(V);
+        wk->scale.push_back(scale);
+        wk->w.push_back(P.w);
     }
     // ---- launches of step 1: jobs by size, packed into launches of at most
     // one workgroup per compute unit; a job that fits one XCD (cus / 8
     // workgroups) takes blocks b = x (mod 8) of one XCD x
     std::vector<int> order(np);
     for (int p = 0; p < np; ++p) order[p] = p;
-    auto wide = [&](int p) { return Vs[p] >= kTridWide; };   // 512-thread jobs are launched apart
+    // Jordan-Wielandt jobs and jobs of 512 and of 256 threads have a kernel each
+    auto kind = [&](int p) { return jw(p) ? 2 : (Vs[p] >= kTridWide ? 1 : 0); };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        return wide(a) != wide(b) ? wide(a) : Gs[a] > Gs[b];
+        return kind(a) != kind(b) ? kind(a) > kind(b) : Gs[a] > Gs[b];
     });
     const int per_xcd = std::max(1, di.cus / 8);
     std::vector<std::vector<int>> launches;
@@ -1367,7 +1792,7 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
         std::vector<int> used;
         for (int p : order) {
             size_t l = 0;
-            while (l < launches.size() && (wide(launches[l][0]) != wide(p) || used[l] + Gs[p] > di.cus)) ++l;
+            while (l < launches.size() && (kind(launches[l][0]) != kind(p) || used[l] + Gs[p] > di.cus)) ++l;
             if (l == launches.size()) {
                 launches.emplace_back();
                 used.push_back(0);
@@ -1406,22 +1831,28 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
         for (int x = 0; x < 8; ++x)
             for (size_t t = 0; t < xcd[x].size(); ++t) bmap[x + 8 * t] = xcd[x][t];
         // the job descriptors and the block map in one upload
-        const size_t jb = sizeof(TridJob) * np, mb = sizeof(int2) * bmap.size();
+        const int kd = kind(L[0]);
+        const size_t jb = (kd == 2 ? sizeof(BidJob) : sizeof(TridJob)) * np, mb = sizeof(int2) * bmap.size();
         std::vector<char> host(jb + mb);
-        std::memcpy(host.data(), tj.data(), jb);
+        std::memcpy(host.data(), kd == 2 ? (const void*)gj.data() : (const void*)tj.data(), jb);
         std::memcpy(host.data() + jb, bmap.data(), mb);
         BufferPtr db;
         upload_async(db, host.data(), host.size(), s);
         descs.push_back(db);
-        const TridJob* djobs = (const TridJob*)db->ptr;
+        const void* djobs = db->ptr;
         const int2* dmap = (const int2*)((const char*)db->ptr + jb);
         void* args[] = {(void*)&djobs, (void*)&dmap};
-        int64_t flops = 0;   // Householder tridiagonalisation: 4/3 n^3 (FP64)
-        for (int p : L) flops += 4 * (int64_t)probs[p].n * probs[p].n * probs[p].n / 3;
-        profile_launch("eigh_tridiag", flops, flops, 0, s, [&] {
-            const bool wd = wide(L[0]);
-            HIPCHK(hipLaunchCooperativeKernel(wd ? (const void*)tridiag_wide_kernel : (const void*)tridiag_kernel,
-                                              dim3((unsigned)bmap.size()), dim3(wd ? 512 : 256), args,
+        // Householder reduction (FP64): 4/3 n^3, of Y to its Golub-Kahan form
+        // 4 (m n^2 - n^3 / 3), n <= m
+        int64_t flops = 0;
+        for (int p : L) {
+            const int64_t n = kd == 2 ? std::min(probs[p].ru, probs[p].rd) : probs[p].n,
+                          m = kd == 2 ? std::max(probs[p].ru, probs[p].rd) : 0;
+            flops += kd == 2 ? 4 * (m * n * n - n * n * n / 3) : 4 * n * n * n / 3;
+        }
+        const void* fn[] = {(const void*)tridiag_kernel, (const void*)tridiag_wide_kernel, (const void*)bidiag_kernel};
+        profile_launch(kd == 2 ? "eigh_bidiag" : "eigh_tridiag", flops, flops, 0, s, [&] {
+            HIPCHK(hipLaunchCooperativeKernel(fn[kd], dim3((unsigned)bmap.size()), dim3(kd ? 512 : 256), args,
                                               (unsigned)lds_bytes, s));
         });
     }
@@ -1430,8 +1861,9 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
         std::vector<BisJob> bj(np);
         std::vector<int2> bmap;
         for (int p = 0; p < np; ++p) {
-            bj[p] = BisJob{wk->d[p], wk->e[p], wk->scale[p], probs[p].w, probs[p].n};
-            for (int j = 0; j < probs[p].n; j += kEigWaves) bmap.push_back(make_int2(p, j));
+            const int n = probs[p].n, half = jw(p) ? std::min(probs[p].ru, probs[p].rd) : 0;
+            bj[p] = BisJob{wk->d[p], wk->e[p], wk->scale[p], probs[p].w, n, half};
+            for (int j = half ? n - half : 0; j < n; j += kEigWaves) bmap.push_back(make_int2(p, j));
         }
         const size_t jb = sizeof(BisJob) * np, mb = sizeof(int2) * bmap.size();
         std::vector<char> host(jb + mb);
@@ -1497,23 +1929,38 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
     BufferPtr zt = device_alloc(8 * ztot);
     BufferPtr work = device_alloc(8 * std::max<size_t>(worktot, 1));
     std::vector<VecJob> vj(np);
-    std::vector<BackJob> bj(np);
-    std::vector<int2> bmap;
+    std::vector<BackJob> bj;
+    std::vector<int2> bmap, tmap;   // (problem, vector), (back-transformation, vector)
     size_t zo = 0;
+    int nbmax = 0;
     for (int p = 0; p < np; ++p) {
-        const int n = wk.probs[p].n;
-        vj[p] = VecJob{wk.d[p], wk.e[p], wk.scale[p], wk.w[p], (double*)zt->ptr + zo, (double*)work->ptr, n, kv[p]};
-        bj[p] = BackJob{wk.V[p], wk.tau[p], (double*)zt->ptr + zo, Z[p], n, kv[p]};
+        const EighProblem& P = wk.probs[p];
+        const int n = P.n;
+        double* z = (double*)zt->ptr + zo;
+        vj[p] = VecJob{wk.d[p], wk.e[p], wk.scale[p], wk.w[p], z, (double*)work->ptr, n, kv[p]};
         for (int c = 0; c < kv[p]; ++c) bmap.push_back(make_int2(p, c));
+        const int first = (int)bj.size();
+        if (P.rd > 0) {   // the u and the v entries go back on their own
+            const int H = bid_columns(P.ru, P.rd);
+            bj.push_back(BackJob{wk.V[p][1], wk.tau[p][1], z, Z[p], P.ru, H / 2, n, n, 0, P.rd});
+            bj.push_back(BackJob{wk.V[p][0], wk.tau[p][0], z, Z[p] ? Z[p] + P.ru : nullptr, P.rd, (H + 1) / 2, n, n, 1, P.ru});
+        } else {
+            bj.push_back(BackJob{wk.V[p][0], wk.tau[p][0], z, Z[p], n, n - 1, n, n, -1, 0});
+        }
+        for (int b = first; b < (int)bj.size() && kv[p] > 0; ++b) {
+            nbmax = std::max(nbmax, bj[b].n);
+            for (int c = 0; c < kv[p]; ++c) tmap.push_back(make_int2(b, c));
+        }
         zo += (size_t)n * kv[p];
     }
-    const size_t b1 = sizeof(VecJob) * np, b2 = sizeof(VecCluster) * cl.size(), b3 = sizeof(BackJob) * np,
-                 b4 = sizeof(int2) * bmap.size();
-    std::vector<char> host(b1 + b2 + b3 + b4);
+    const size_t b1 = sizeof(VecJob) * np, b2 = sizeof(VecCluster) * cl.size(), b3 = sizeof(BackJob) * bj.size(),
+                 b4 = sizeof(int2) * bmap.size(), b5 = sizeof(int2) * tmap.size();
+    std::vector<char> host(b1 + b2 + b3 + b4 + b5);
     std::memcpy(host.data(), vj.data(), b1);
     std::memcpy(host.data() + b1, cl.data(), b2);
     std::memcpy(host.data() + b1 + b2, bj.data(), b3);
     std::memcpy(host.data() + b1 + b2 + b3, bmap.data(), b4);
+    std::memcpy(host.data() + b1 + b2 + b3 + b4, tmap.data(), b5);
     BufferPtr db;
     upload_async(db, host.data(), host.size(), s);
     const char* base = (const char*)db->ptr;
@@ -1521,7 +1968,7 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
     set_lds_limits(di);
     const BackShape* bs = nullptr;
     for (auto& x : kBackShapes)
-        if (!bs && x.nmax >= nmax) bs = &x;
+        if (!bs && x.nmax >= nbmax) bs = &x;
     if (!bs || 40 * (size_t)nmax > (size_t)di.lds) fail(SYMTEN_E_CAPACITY, "eigh: vectors exceed the registers or LDS");
     const VecJob* dvj = (const VecJob*)base;
     const int2* dmap = (const int2*)(base + b1 + b2 + b3);
@@ -1541,11 +1988,12 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
             HIPCHK(hipGetLastError());
         });
     int64_t bflops = 0;   // back-transformation: 2 n^2 per vector
-    for (int p = 0; p < np; ++p) bflops += 2 * (int64_t)wk.probs[p].n * wk.probs[p].n * kv[p];
+    for (auto& t : tmap) bflops += 2 * (int64_t)bj[t.x].n * bj[t.x].n;
     profile_launch("eigh_backtr", bflops, bflops, 0, s, [&] {
         const BackJob* dbj = (const BackJob*)(base + b1 + b2);
-        void* args[] = {(void*)&dbj, (void*)&dmap};
-        HIPCHK(hipLaunchKernel(bs->fn, dim3((unsigned)nvec), dim3((unsigned)bs->threads), args, 0, s));
+        const int2* dtmap = dmap + bmap.size();
+        void* args[] = {(void*)&dbj, (void*)&dtmap};
+        HIPCHK(hipLaunchKernel(bs->fn, dim3((unsigned)tmap.size()), dim3((unsigned)bs->threads), args, 0, s));
     });
     wk.keep.push_back(zt);
     wk.keep.push_back(work);

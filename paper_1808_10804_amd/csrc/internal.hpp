@@ -291,10 +291,15 @@ struct EighProblem {
     const double* A = nullptr;   // n x n, column-major, both triangles
     double* w = nullptr;         // n eigenvalues, ascending
     int* status = nullptr;       // optional, zeroed by the caller: set to 1 if
-                                 // the tridiagonalisation's barrier gave up
+                                 // the workgroups of the reduction did not meet
+    // rd > 0: A is Y (ru x rd, column-major, ld lda) and the problem its
+    // Jordan-Wielandt matrix [[0, Y], [Y^T, 0]] of order n = ru + rd; of its
+    // eigenvalues the min(ru, rd) largest are found and mirrored
+    int ru = 0, rd = 0;
 };
 struct EighWork;
 bool eigh_fits(int n);
+bool eigh_jw_fits(int ru, int rd);   // a Jordan-Wielandt problem of Y (ru x rd)
 int eigh_problems(const EighWork& wk);
 int eigh_max_order();
 std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hipStream_t s);
