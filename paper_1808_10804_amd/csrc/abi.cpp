@@ -888,14 +888,16 @@ bool own_solver_fits(const std::vector<std::vector<CutSector>*>& cuts, bool f64)
 // synchronisation).  Each cut's sectors are grouped into size classes
 // (largest first); the classes of all cuts go round robin over the caller's
 // stream and the side streams, so that the largest classes of several cuts
-// land on different streams.  `start` is recorded on s by the caller once the
-// halves of every cut are enqueued; side streams wait for it.  Enqueueing
+// land on different streams, which wait for what is queued on s (the halves of
+// every cut).  Enqueueing
 // rocSOLVER's eigensolver is host-bound (about two thirds of its device time
 // at n = 696), so every stream's classes are enqueued by a host thread of
 // their own, each with the stream's own rocBLAS handle.
 std::vector<ProjPending> issue_solves(ctm_env* env, const std::vector<std::vector<CutSector>*>& cuts, bool f64,
-                                      hipStream_t s, hipEvent_t start) {
+                                      hipStream_t s) {
     if (own_solver_fits(cuts, f64)) return issue_solves_own(env, cuts, f64, s);
+    const hipEvent_t start = env->ev_start;
+    HIPCHK(hipEventRecord(start, s));
     rb_check(rocblas_set_stream(env->rb, s), "rocblas_set_stream");
     constexpr int kSlots = ctm_env::kAux + 1;
     struct SolveClass {
@@ -1153,8 +1155,7 @@ ProjOut finish_projectors(ctm_env* env, std::vector<CutSector>& secs, ProjPendin
 }
 
 ProjOut cut_projectors(ctm_env* env, std::vector<CutSector>& secs, int chi, bool f64, hipStream_t s) {
-    HIPCHK(hipEventRecord(env->ev_start, s));
-    std::vector<ProjPending> pend = issue_solves(env, {&secs}, f64, s, env->ev_start);
+    std::vector<ProjPending> pend = issue_solves(env, {&secs}, f64, s);
     return finish_projectors(env, secs, pend[0], chi, f64, s);
 }
 
@@ -1287,13 +1288,7 @@ void normalise_su2(Tensor& X, bool f64, hipStream_t s) {
     if (tasks.empty()) return;
     BufferPtr tmp = device_alloc(pos * X.esize());
     validate_tasks(tasks, {X.elems, pos});
-    std::vector<int64_t> prefix;
-    copy_prefix(tasks, prefix);
-    BufferPtr dt, dp;
-    upload_sync(dt, tasks.data(), tasks.size() * sizeof(CopyTask));
-    upload_sync(dp, prefix.data(), prefix.size() * sizeof(int64_t));
-    copy_launch_arg((const CopyTask*)dt->ptr, (const int64_t*)dp->ptr, (int)tasks.size(), prefix.back(),
-                    {X.data(), tmp->ptr}, f64, f64 ? 1 : 0, s);
+    launch_tasks(tasks, {X.data(), tmp->ptr}, f64, f64 ? 1 : 0, s);
     BufferPtr red = device_alloc(8 * (1 + 512));
     launch_sumsq(tmp->ptr, f64, pos, (double*)red->ptr, s);
     launch_scale_by_inv_sqrt(X.data(), f64, X.elems, (const double*)red->ptr, s);
@@ -1764,15 +1759,7 @@ CutPrep cut_prepare(const CornerResult& k1, const CornerResult& k2, const Corner
         tasks.insert(tasks.end(), row_tasks[1].begin(), row_tasks[1].end());
         validate_tasks(tasks, {hu.t->elems, hd.t->elems, std::max<int64_t>(row_elems[0], 1),
                                std::max<int64_t>(row_elems[1], 1)});
-        std::vector<int64_t> prefix;
-        copy_prefix(tasks, prefix);
-        BufferPtr dt, dp;
-        upload_sync(dt, tasks.data(), tasks.size() * sizeof(CopyTask));
-        upload_sync(dp, prefix.data(), prefix.size() * sizeof(int64_t));
-        copy_launch_arg((const CopyTask*)dt->ptr, (const int64_t*)dp->ptr, (int)tasks.size(), prefix.back(),
-                        {hu.t->data(), hd.t->data(), ub[0]->ptr, ub[1]->ptr}, f64, f64 ? 1 : 0, s);
-        row_bufs.push_back(dt);
-        row_bufs.push_back(dp);
+        launch_tasks(tasks, {hu.t->data(), hd.t->data(), ub[0]->ptr, ub[1]->ptr}, f64, f64 ? 1 : 0, s);
         for (auto& pd : pending)
             (pd.side == 0 ? secs[pd.sec].hu : secs[pd.sec].hd) = (const char*)ub[pd.side]->ptr + pd.off * es;
     }
@@ -1984,10 +1971,9 @@ void cell_left_move(ctm_env* env, const std::vector<TensorPtr>& a, int chi, int 
         }
         // the cuts of a column are independent: their eigensolves are all
         // enqueued before the first read-back, spread over the streams
-        HIPCHK(hipEventRecord(env->ev_start, s));
         std::vector<std::vector<CutSector>*> cut_secs;
         for (int y = 0; y < Ly; ++y) cut_secs.push_back(&preps[y].secs);
-        std::vector<ProjPending> pend = issue_solves(env, cut_secs, preps[0].f64, s, env->ev_start);
+        std::vector<ProjPending> pend = issue_solves(env, cut_secs, preps[0].f64, s);
         for (int y = 0; y < Ly; ++y) {
             ProjOut po = finish_projectors(env, preps[y].secs, pend[y], chi, preps[y].f64, s);
             cuts[y] = cut_complete(preps[y], po, s);

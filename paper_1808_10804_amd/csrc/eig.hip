@@ -1563,75 +1563,6 @@ void bid_shape(int ru, int rd, const DevInfo& di, int& variant, int& G) {
     G = g;
 }
 
-// Descriptors go to the device through a ring of pinned host memory and an
-// asynchronous copy on the caller's stream (no host synchronisation inside a
-// move).  A range of the ring is reused once the event recorded after its
-// copy has completed.
-class PinnedRing {
-  public:
-    void upload(BufferPtr& dst, const void* src, size_t bytes, hipStream_t s) {
-        dst = device_alloc(std::max<size_t>(bytes, 16));
-        if (!bytes) return;
-        std::lock_guard<std::mutex> lk(mu_);
-        const size_t need = (bytes + 255) & ~(size_t)255;
-        if (need > kCap) {   // larger than the ring: a synchronous copy
-            HIPCHK(hipMemcpy(dst->ptr, src, bytes, hipMemcpyHostToDevice));
-            return;
-        }
-        if (!host_) HIPCHK(hipHostMalloc((void**)&host_, kCap, hipHostMallocDefault));
-        if (head_ + need > kCap) head_ = 0;
-        // wait for earlier copies out of [head_, head_ + need)
-        for (auto it = inflight_.begin(); it != inflight_.end();) {
-            if (it->off < head_ + need && head_ < it->off + it->len) {
-                HIPCHK(hipEventSynchronize(it->ev));
-                free_.push_back(it->ev);
-                it = inflight_.erase(it);
-            } else {
-                ++it;
-            }
-        }
-        std::memcpy(host_ + head_, src, bytes);
-        HIPCHK(hipMemcpyAsync(dst->ptr, host_ + head_, bytes, hipMemcpyHostToDevice, s));
-        hipEvent_t ev;
-        if (free_.empty()) {
-            HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-        } else {
-            ev = free_.back();
-            free_.pop_back();
-        }
-        HIPCHK(hipEventRecord(ev, s));
-        inflight_.push_back({head_, need, ev});
-        head_ += need;
-    }
-
-  private:
-    static constexpr size_t kCap = 4 << 20;
-    struct Range {
-        size_t off, len;
-        hipEvent_t ev;
-    };
-    std::mutex mu_;
-    char* host_ = nullptr;
-    size_t head_ = 0;
-    std::vector<Range> inflight_;
-    std::vector<hipEvent_t> free_;
-};
-
-void upload_async(BufferPtr& dst, const void* src, size_t bytes, hipStream_t s) {
-    static std::mutex mu;
-    static std::map<int, PinnedRing*> rings;   // one per device, kept for the process
-    int dev = 0;
-    HIPCHK(hipGetDevice(&dev));
-    PinnedRing* r;
-    {
-        std::lock_guard<std::mutex> lk(mu);
-        auto& slot = rings[dev];
-        if (!slot) slot = new PinnedRing();
-        r = slot;
-    }
-    r->upload(dst, src, bytes, s);
-}
-
 // Dynamic LDS limits of the solver's kernels, raised once per device.
 void set_lds_limits(const DevInfo& di) {
     static std::mutex mu;

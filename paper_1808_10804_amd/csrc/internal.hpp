@@ -2,6 +2,7 @@
 // device work descriptors and the kernel launch interface.
 #pragma once
 
+#include <cstring>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -64,10 +65,10 @@ bool call_stream_set();
 hipStream_t call_stream();
 
 // Caching device allocator (size-bucketed free lists).  A released block
-// records an event on the stream that released it: the stream of the call
-// running on the releasing thread, else the stream the block was allocated
-// on.  Handing the block to a call on another stream makes that stream wait
-// for the event, so work queued on two streams never shares a block.
+// belongs to the stream that released it: the stream of the call running on
+// the releasing thread, else the stream the block was allocated on.  Handing
+// the block to a call on another stream makes that stream wait for the first
+// one, so work queued on two streams never shares a block.
 struct DeviceBuffer;
 using BufferPtr = std::shared_ptr<DeviceBuffer>;
 BufferPtr device_alloc(size_t bytes);
@@ -80,6 +81,7 @@ struct DeviceBuffer {
     void (*user_free)(void* ptr, size_t bytes, void* ctx) = nullptr;
     void* user_ctx = nullptr;
     uint64_t user_gen = 0;  // registration that made it; a later one leaks it
+    bool used = true;       // work queued earlier may still touch the block
     ~DeviceBuffer();
 };
 // Caller-registered device allocator (null fns: the library's own pool).
@@ -406,7 +408,32 @@ std::vector<TensorPtr> run_contractions_batched(
     const std::vector<const Tensor*>& Bs, hipStream_t stream);
 
 // plan / descriptor helpers shared by the launch paths
+// Uploads into a new buffer: complete on return (descriptors kept for calls on
+// any stream), or in the order of stream s (buffers of one call).
 void upload_sync(BufferPtr& buf, const void* host, size_t bytes);
+void upload_async(BufferPtr& dst, const void* src, size_t bytes, hipStream_t s);
+// Tables of one launch, sent together in the order of its stream (a copy of
+// its own for each table cost 12 us of the host).
+class Tables {
+  public:
+    template <class V>
+    size_t add(const std::vector<V>& v) {   // offset of the table, for at()
+        const size_t o = host_.size(), n = v.size() * sizeof(V);
+        host_.resize(o + (n + 15) / 16 * 16);
+        if (n) std::memcpy(host_.data() + o, v.data(), n);
+        return o;
+    }
+    void send(hipStream_t s) { upload_async(dev_, host_.data(), host_.size(), s); }
+    template <class V>
+    const V* at(size_t off) const { return (const V*)((const char*)dev_->ptr + off); }
+
+  private:
+    std::vector<char> host_;
+    BufferPtr dev_;
+};
+// Gathers `tasks` (validated by the caller) on stream s.
+void launch_tasks(const std::vector<CopyTask>& tasks, const std::vector<void*>& bufs, bool src_f64, int dst_kind,
+                  hipStream_t s);
 // Work list of a launch; with allow_split, tiles of a launch that would not
 // fill the chip are split along K (see the definition).
 void build_tiles(const std::vector<GemmGroup>& groups, Prec prec, int cfg, TilePlan& tp, bool allow_split);

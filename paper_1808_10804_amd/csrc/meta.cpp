@@ -66,30 +66,46 @@ bool call_stream_set() { return tl_stream_set; }
 hipStream_t call_stream() { return tl_stream; }
 
 namespace {
+// Released blocks carry the stream that released them and no event: a call on
+// the same stream is ordered after their last users by the queue itself.  A
+// call on another stream records the event then (order_after), which covers
+// at least the work up to the release.  An event at every release cost 4 us of
+// the host and 6 us of the queue each (its barrier packet), three of them per
+// contraction and about 90 per move: 22.9 us for a kernel and three events
+// against 3.4 us for the kernel alone.
+// (A stream destroyed in between is idle: hipStreamDestroy returned after the
+// 71 ms of products queued on it, also where its handle is given out again.)
 struct FreeBlock {
     void* ptr;
     hipStream_t stream;   // stream that released it
-    hipEvent_t ev;        // recorded on `stream` at release (null: already idle)
 };
 struct Pool {
     std::mutex mu;
     std::multimap<size_t, FreeBlock> free_;   // capacity -> block
-    std::vector<hipEvent_t> idle_events;
     size_t held = 0;
-    hipEvent_t take_event() {   // under mu
-        if (!idle_events.empty()) {
-            hipEvent_t e = idle_events.back();
-            idle_events.pop_back();
-            return e;
-        }
-        hipEvent_t e = nullptr;
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        return e;
-    }
 };
+// Stream `cur` waits for the work queued on `from`; false where it cannot be
+// waited for (either of the two is being captured into a graph).
+bool order_after(hipStream_t cur, hipStream_t from) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    // a captured call may not wait for work outside of its graph
+    if (hipStreamIsCapturing(cur, &st) == hipSuccess && st != hipStreamCaptureStatusNone) return false;
+    (void)hipGetLastError();
+    if (const hipError_t e = hipStreamIsCapturing(from, &st); e != hipSuccess) {
+        (void)hipGetLastError();
+        if (e == hipErrorStreamCaptureImplicit) return false;   // the null stream while another one is captured
+        HIPCHK(hipDeviceSynchronize());                         // the stream no longer exists
+        return true;
+    }
+    if (st != hipStreamCaptureStatusNone) return false;
+    hipEvent_t ev = nullptr;
+    HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    hipError_t e = hipEventRecord(ev, from);
+    if (e == hipSuccess) e = hipStreamWaitEvent(cur, ev, 0);
+    (void)hipEventDestroy(ev);   // released once it has completed
+    HIPCHK(e);
+    return true;
+}
 Pool& pool() {
     static Pool* p = new Pool();   // leaked on purpose: buffers may outlive statics
     return *p;
@@ -158,16 +174,18 @@ BufferPtr device_alloc(size_t bytes) {
     {
         Pool& P = pool();
         std::lock_guard<std::mutex> lk(P.mu);
-        auto it = P.free_.lower_bound(cap);
-        if (it != P.free_.end() && it->first <= cap * 2) {
-            const FreeBlock fb = it->second;
-            if (fb.ev) {
-                // the block's last users were queued on fb.stream: a call on
-                // another stream waits for them (same stream: queue order)
-                if (fb.stream != cur) HIPCHK(hipStreamWaitEvent(cur, fb.ev, 0));
-                P.idle_events.push_back(fb.ev);
+        // a block of this stream if there is one, else one of another stream
+        auto it = P.free_.end(), other = P.free_.end();
+        for (auto k = P.free_.lower_bound(cap); k != P.free_.end() && k->first <= cap * 2; ++k) {
+            if (k->second.stream == cur) {
+                it = k;
+                break;
             }
-            b->ptr = fb.ptr;
+            if (other == P.free_.end()) other = k;
+        }
+        if (it == P.free_.end() && other != P.free_.end() && order_after(cur, other->second.stream)) it = other;
+        if (it != P.free_.end()) {
+            b->ptr = it->second.ptr;
             b->cap = it->first;
             P.free_.erase(it);
             P.held -= b->cap;
@@ -183,10 +201,7 @@ BufferPtr device_alloc(size_t bytes) {
         {
             std::lock_guard<std::mutex> lk(P.mu);
             (void)hipDeviceSynchronize();
-            for (auto& kv : P.free_) {
-                (void)hipFree(kv.second.ptr);
-                if (kv.second.ev) P.idle_events.push_back(kv.second.ev);
-            }
+            for (auto& kv : P.free_) (void)hipFree(kv.second.ptr);
             P.free_.clear();
             P.held = 0;
         }
@@ -198,6 +213,7 @@ BufferPtr device_alloc(size_t bytes) {
     }
     b->ptr = p;
     b->cap = cap;
+    b->used = false;
     return b;
 }
 
@@ -216,18 +232,7 @@ DeviceBuffer::~DeviceBuffer() {
     const hipStream_t rs = call_stream_set() ? call_stream() : stream;
     Pool& P = pool();
     std::lock_guard<std::mutex> lk(P.mu);
-    hipEvent_t ev = P.take_event();
-    if (ev && hipEventRecord(ev, rs) != hipSuccess) {
-        // no event on that stream (e.g. it no longer exists): wait for the
-        // device instead, after which the block is idle
-        (void)hipGetLastError();
-        (void)hipDeviceSynchronize();
-        P.idle_events.push_back(ev);
-        ev = nullptr;
-    } else if (!ev) {
-        (void)hipDeviceSynchronize();
-    }
-    P.free_.emplace(cap, FreeBlock{ptr, rs, ev});
+    P.free_.emplace(cap, FreeBlock{ptr, rs});
     P.held += cap;
 }
 
@@ -846,7 +851,104 @@ std::mutex g_devplan_mu;
 
 void upload_sync(BufferPtr& buf, const void* host, size_t bytes) {
     buf = device_alloc(bytes);
-    if (bytes) HIPCHK(hipMemcpy(buf->ptr, host, bytes, hipMemcpyHostToDevice));
+    if (!bytes) return;
+    if (buf->used) HIPCHK(hipStreamSynchronize(call_stream()));
+    HIPCHK(hipMemcpy(buf->ptr, host, bytes, hipMemcpyHostToDevice));
+}
+
+namespace {
+// Descriptors go to the device through a ring of pinned host memory and an
+// asynchronous copy on the caller's stream (no host synchronisation inside a
+// move).  The ring has two halves; when one is full, events record how far the
+// streams that copied out of it are, and it is written again once they have
+// passed (an event per copy would put a barrier packet of 6 us behind each).
+class PinnedRing {
+  public:
+    void upload(BufferPtr& dst, const void* src, size_t bytes, hipStream_t s) {
+        dst = device_alloc(std::max<size_t>(bytes, 16));
+        if (!bytes) return;
+        std::lock_guard<std::mutex> lk(mu_);
+        const size_t need = (bytes + 255) & ~(size_t)255;
+        if (need > kHalf) {   // larger than a half: a synchronous copy
+            HIPCHK(hipStreamSynchronize(s));   // the block's earlier users on this stream
+            HIPCHK(hipMemcpy(dst->ptr, src, bytes, hipMemcpyHostToDevice));
+            return;
+        }
+        if (!host_) HIPCHK(hipHostMalloc((void**)&host_, 2 * kHalf, hipHostMallocDefault));
+        if (head_ + need > kHalf) {
+            leave(half_[cur_]);
+            cur_ ^= 1;
+            head_ = 0;
+            enter(half_[cur_]);
+        }
+        char* p = host_ + cur_ * kHalf + head_;
+        std::memcpy(p, src, bytes);
+        Half& h = half_[cur_];
+        if (std::find(h.used.begin(), h.used.end(), s) == h.used.end()) h.used.push_back(s);
+        HIPCHK(hipMemcpyAsync(dst->ptr, p, bytes, hipMemcpyHostToDevice, s));
+        head_ += need;
+    }
+
+  private:
+    static constexpr size_t kHalf = 2 << 20;
+    struct Half {
+        std::vector<hipStream_t> used;   // streams that copy out of it
+        std::vector<hipEvent_t> done;
+    };
+    static void leave(Half& h) {
+        for (hipStream_t s : h.used) {
+            hipEvent_t ev = nullptr;
+            HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+            if (hipEventRecord(ev, s) != hipSuccess) {   // the stream no longer exists
+                (void)hipGetLastError();
+                (void)hipEventDestroy(ev);
+                HIPCHK(hipDeviceSynchronize());
+            } else {
+                h.done.push_back(ev);
+            }
+        }
+        h.used.clear();
+    }
+    static void enter(Half& h) {
+        for (hipEvent_t ev : h.done) {
+            HIPCHK(hipEventSynchronize(ev));
+            (void)hipEventDestroy(ev);
+        }
+        h.done.clear();
+    }
+    std::mutex mu_;
+    char* host_ = nullptr;
+    size_t head_ = 0;
+    int cur_ = 0;
+    Half half_[2];
+};
+
+}  // namespace
+
+void upload_async(BufferPtr& dst, const void* src, size_t bytes, hipStream_t s) {
+    static std::mutex mu;
+    static std::map<int, PinnedRing*> rings;   // one per device, kept for the process
+    int dev = 0;
+    HIPCHK(hipGetDevice(&dev));
+    PinnedRing* r;
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        auto& slot = rings[dev];
+        if (!slot) slot = new PinnedRing();
+        r = slot;
+    }
+    r->upload(dst, src, bytes, s);
+}
+
+void launch_tasks(const std::vector<CopyTask>& tasks, const std::vector<void*>& bufs, bool src_f64, int dst_kind,
+                  hipStream_t s) {
+    std::vector<int64_t> prefix;
+    copy_prefix(tasks, prefix);
+    Tables tab;
+    const size_t ot = tab.add(tasks), op = tab.add(prefix);
+    tab.send(s);
+    copy_launch_arg(tab.at<CopyTask>(ot), tab.at<int64_t>(op), (int)tasks.size(), prefix.back(), bufs, src_f64,
+                    dst_kind, s);
 }
 
 // ---------------------------------------------------------------- autotuner
@@ -1577,13 +1679,7 @@ TensorPtr double_layer(const Tensor& A, hipStream_t stream, const double* op) {
     }
     BufferPtr dense = device_alloc(dense_n * out->esize());
     launch_fill_zero(dense->ptr, dense_n * out->esize(), stream);
-    std::vector<int64_t> prefix;
-    copy_prefix(tasks, prefix);
-    BufferPtr dt, dp;
-    upload_sync(dt, tasks.data(), tasks.size() * sizeof(CopyTask));
-    upload_sync(dp, prefix.data(), prefix.size() * sizeof(int64_t));
-    copy_launch_arg((const CopyTask*)dt->ptr, (const int64_t*)dp->ptr, (int)tasks.size(), prefix.back(),
-                    {A.data(), dense->ptr}, f64, f64, stream);
+    launch_tasks(tasks, {A.data(), dense->ptr}, f64, f64, stream);
 
     // block tables
     const int nb = (int)out->blocks.size();
@@ -1610,24 +1706,22 @@ TensorPtr double_layer(const Tensor& A, hipStream_t stream, const double* op) {
     std::vector<int> kb_off(8);
     for (int l = 0; l < 4; ++l) { kb_off[l] = (int)kb.size(); kb.insert(kb.end(), ket_of[l].begin(), ket_of[l].end()); }
     for (int l = 0; l < 4; ++l) { kb_off[4 + l] = (int)kb.size(); kb.insert(kb.end(), bra_of[l].begin(), bra_of[l].end()); }
-    BufferPtr d_boff, d_bstart, d_bfirst, d_bshape, d_kb;
-    upload_sync(d_boff, boff.data(), boff.size() * 8);
-    upload_sync(d_bstart, bstart.data(), bstart.size() * 8);
-    upload_sync(d_bfirst, bfirst.data(), bfirst.size() * 4);
-    upload_sync(d_bshape, bshape.data(), bshape.size() * 4);
-    upload_sync(d_kb, kb.data(), kb.size() * 4);
+    Tables tab;
+    const size_t o_off = tab.add(boff), o_start = tab.add(bstart), o_first = tab.add(bfirst), o_shape = tab.add(bshape),
+                 o_kb = tab.add(kb);
+    tab.send(stream);
     DoubleLayerArgs a{};
     a.A_dense = dense->ptr;
     a.nphys = Dv[0];
     for (int l = 0; l < 4; ++l) {
         a.Dv[l] = Dv[l + 1];
-        a.ket_of[l] = (const int*)d_kb->ptr + kb_off[l];
-        a.bra_of[l] = (const int*)d_kb->ptr + kb_off[4 + l];
+        a.ket_of[l] = tab.at<int>(o_kb) + kb_off[l];
+        a.bra_of[l] = tab.at<int>(o_kb) + kb_off[4 + l];
     }
-    a.blk_off = (const int64_t*)d_boff->ptr;
-    a.blk_start = (const int*)d_bfirst->ptr;
-    a.blk_shape = (const int*)d_bshape->ptr;
-    a.blk_elem_start = (const int64_t*)d_bstart->ptr;
+    a.blk_off = tab.at<int64_t>(o_off);
+    a.blk_start = tab.at<int>(o_first);
+    a.blk_shape = tab.at<int>(o_shape);
+    a.blk_elem_start = tab.at<int64_t>(o_start);
     a.nblocks = nb;
     a.total = total;
     a.out = out->data();
@@ -1635,8 +1729,7 @@ TensorPtr double_layer(const Tensor& A, hipStream_t stream, const double* op) {
     a.has_op = op != nullptr;
     if (op) std::copy(op, op + np * np, a.op);
     launch_double_layer(a, stream);
-    // the temporaries go back to the pool; keep ordering by syncing (small)
-    HIPCHK(hipStreamSynchronize(stream));
+    HIPCHK(hipStreamSynchronize(stream));   // complete on return
     return out;
 }
 

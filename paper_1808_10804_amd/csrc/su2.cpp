@@ -592,21 +592,11 @@ TensorPtr su2_to_u1(const Tensor& in, hipStream_t stream) {
         }
     }
     const bool f64 = in.dtype == SYMTEN_F64;
-    std::vector<BufferPtr> keep;
     for (auto& tasks : layers) {
         if (tasks.empty()) continue;
         validate_tasks(tasks, {in.elems, out->elems});
-        std::vector<int64_t> prefix;
-        copy_prefix(tasks, prefix);
-        BufferPtr dt, dp;
-        upload_sync(dt, tasks.data(), tasks.size() * sizeof(CopyTask));
-        upload_sync(dp, prefix.data(), prefix.size() * sizeof(int64_t));
-        copy_launch_arg((const CopyTask*)dt->ptr, (const int64_t*)dp->ptr, (int)tasks.size(), prefix.back(),
-                        {in.data(), out->data()}, f64, /*accumulate*/ 4, stream);
-        keep.push_back(dt);
-        keep.push_back(dp);
+        launch_tasks(tasks, {in.data(), out->data()}, f64, /*accumulate*/ 4, stream);
     }
-    // the descriptor buffers return to the pool when `keep` goes: wait first
     HIPCHK(hipStreamSynchronize(stream));
     return out;
 }
@@ -693,19 +683,10 @@ TensorPtr u1_to_su2(const Tensor& U, const std::vector<Leg>& legs, hipStream_t s
         }
     }
     const bool f64 = U.dtype == SYMTEN_F64;
-    std::vector<BufferPtr> keep;
     for (auto& tasks : layers) {
         if (tasks.empty()) continue;
         validate_tasks(tasks, {U.elems, out->elems});
-        std::vector<int64_t> prefix;
-        copy_prefix(tasks, prefix);
-        BufferPtr dt, dp;
-        upload_sync(dt, tasks.data(), tasks.size() * sizeof(CopyTask));
-        upload_sync(dp, prefix.data(), prefix.size() * sizeof(int64_t));
-        copy_launch_arg((const CopyTask*)dt->ptr, (const int64_t*)dp->ptr, (int)tasks.size(), prefix.back(),
-                        {U.data(), out->data()}, f64, /*accumulate*/ 4, stream);
-        keep.push_back(dt);
-        keep.push_back(dp);
+        launch_tasks(tasks, {U.data(), out->data()}, f64, /*accumulate*/ 4, stream);
     }
     HIPCHK(hipStreamSynchronize(stream));
     return out;
@@ -920,14 +901,8 @@ TensorPtr su2_permute_flip(const Tensor& X, const std::vector<int>& perm, const 
     }
     if (!tasks.empty()) {
         validate_tasks(tasks, {U->elems, V->elems});
-        std::vector<int64_t> prefix;
-        copy_prefix(tasks, prefix);
-        BufferPtr dt, dp;
-        upload_sync(dt, tasks.data(), tasks.size() * sizeof(CopyTask));
-        upload_sync(dp, prefix.data(), prefix.size() * sizeof(int64_t));
         const bool f64 = U->dtype == SYMTEN_F64;
-        copy_launch_arg((const CopyTask*)dt->ptr, (const int64_t*)dp->ptr, (int)tasks.size(), prefix.back(),
-                        {U->data(), V->data()}, f64, f64 ? 1 : 0, s);
+        launch_tasks(tasks, {U->data(), V->data()}, f64, f64 ? 1 : 0, s);
         HIPCHK(hipStreamSynchronize(s));
     }
     return u1_to_su2(*V, legs, s);
@@ -946,14 +921,8 @@ TensorPtr su2_sign_half_integer(const Tensor& X, int leg, hipStream_t s) {
     }
     if (!tasks.empty()) {
         validate_tasks(tasks, {X.elems, X.elems});
-        std::vector<int64_t> prefix;
-        copy_prefix(tasks, prefix);
-        BufferPtr dt, dp;
-        upload_sync(dt, tasks.data(), tasks.size() * sizeof(CopyTask));
-        upload_sync(dp, prefix.data(), prefix.size() * sizeof(int64_t));
         const bool f64 = X.dtype == SYMTEN_F64;
-        copy_launch_arg((const CopyTask*)dt->ptr, (const int64_t*)dp->ptr, (int)tasks.size(), prefix.back(),
-                        {X.data(), out->data()}, f64, f64 ? 1 : 0, s);
+        launch_tasks(tasks, {X.data(), out->data()}, f64, f64 ? 1 : 0, s);
         HIPCHK(hipStreamSynchronize(s));
     }
     return out;
