@@ -171,7 +171,8 @@ struct CopyTask {
     // transposing copy (the destination's unit-stride dim is not the
     // source's): tiles of (1 << lg_out) x (1024 >> lg_out) elements staged
     // through LDS, read along dim tr_in, written along dim tr_out; -1: direct
-    int tr_in, tr_out, lg_out, pad2_;
+    int tr_in, tr_out, lg_out;
+    int run;   // direct copy: dim along which a thread takes runs of 4 elements; -1: none
 };
 // chunks of a copy task: 1024 elements, or one LDS tile of 1024
 int64_t copy_task_chunks(const CopyTask& t);

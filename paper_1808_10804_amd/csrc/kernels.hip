@@ -104,50 +104,93 @@ __device__ __forceinline__ void copy_store(void* dstv, int64_t dofs, int64_t lo_
 // Strided gather over a task list.  A task's elements are cut into chunks:
 // 1024 consecutive elements of a direct copy, or one tile of a transposing
 // copy (read along the source's unit-stride dim into LDS, written along the
-// destination's unit-stride dim).  Each workgroup takes one piece, up to
-// kCopyGroup consecutive chunks of one task: it finds the task by bisection
-// over the pieces' prefix sums, decodes it once and issues the loads of all
-// its chunks before the first store.  A task may sum several equally strided
-// sources with their scalars (SU(2) tree-sibling blocks).
+// destination's unit-stride dim).  A piece is up to kCopyGroup consecutive
+// chunks of one task; a workgroup takes a piece, or one chunk of it, and
+// issues the loads of all its chunks before the first store.  A task may sum
+// several equally strided sources with their scalars (SU(2) tree-sibling
+// blocks).
+// What bounds it: small launches the chain of dependent loads before the first
+// element (the task search, then the task: bisecting the prefix sums lane 0's
+// way took a load per level, x a at D = 5, chi = 53 16.7 us; now 64 candidates
+// per load and the task's fields in one round, 7.7 us), large ones the index
+// arithmetic per element.  So a thread takes runs of four along a dim other
+// than the destination's unit-stride one and computes one index for them
+// (T a and the other gathers of a move at D = 8, chi = 200, f32, 2.6 GB:
+// 1.96 ms to 1.23 ms by the placement below and to 0.99 ms by the runs).  Runs of
+// 2^kCopyXcdRun consecutive pieces go to one XCD: rows of a panel shorter than
+// a cache line are written, and source rows read, in parts by neighbouring
+// pieces, whose line stays in one L2 (single pieces in turn 1.69 ms, runs of 4
+// 1.31, of 16 1.23, of 64 1.26 ms, and then too few runs for small launches).
+constexpr int kCopyXcdRun = 4;
 constexpr int kCopyRun = kCopyChunk / kCopyThreads;   // elements per thread and chunk
 constexpr int kTileLds = kCopyChunk + 64;              // LDS elements of one tile
 
-template <typename TS, int DK, typename AT, typename G>
-__device__ __forceinline__ void copy_tiles(const CopyTask& T, int64_t first, int ng, void* dstv, AT* tile,
-                                           G gather) {
+// The fields of a task that index its elements, in registers (one round of
+// scalar loads instead of a dependent one per dim and chunk).
+struct TaskView {
+    int last, dims[kMaxCopyRank];
+    int64_t ss[kMaxCopyRank], ds[kMaxCopyRank];
+    double inv[kMaxCopyRank];   // 1 / dims[k]
+    // run >= 0: dim `run` counted in runs of kCopyRun
+    __device__ __forceinline__ TaskView(const CopyTask& T, int run) : last(T.rank - 1) {
+#pragma unroll
+        for (int k = 0; k < kMaxCopyRank; ++k) {
+            dims[k] = k == run ? (T.dims[k] + kCopyRun - 1) / kCopyRun : T.dims[k];
+            ss[k] = k == run ? T.sstride[k] * kCopyRun : T.sstride[k];
+            ds[k] = k == run ? T.dstride[k] * kCopyRun : T.dstride[k];
+        }
+#pragma unroll
+        for (int k = 0; k < kMaxCopyRank; ++k) {
+            const double d = dims[k];
+            double r = __builtin_amdgcn_rcp(d);
+            r = fma(r, fma(-d, r, 1.0), r);
+            inv[k] = fma(r, fma(-d, r, 1.0), r);
+        }
+    }
+    // r = (r / dims[k], remainder); exact for r < 2^31: (r + 1/2) / d is at
+    // least 1/(2d) > 2^-32 away from an integer and off by less than 2^-19 / d
+    __device__ __forceinline__ uint32_t split(uint32_t& r, int k) const {
+        const uint32_t q = (uint32_t)((r + 0.5) * inv[k]), rem = r - q * (uint32_t)dims[k];
+        r = q;
+        return rem;
+    }
+};
+
+template <typename TS, int DK, int GRP, typename AT, typename G>
+__device__ __forceinline__ void copy_tiles(const CopyTask& T, const TaskView& D, uint32_t first, int ng, void* dstv,
+                                           AT* tile, G gather) {
     // TO destination-contiguous x TI source-contiguous elements per tile
-    const int rank = T.rank;
     const int din = T.tr_in, dout = T.tr_out;
     const int lgo = T.lg_out, lgi = 10 - T.lg_out;
     const int TO = 1 << lgo, TI = 1 << lgi;
     const int LS = TI + 1;   // LDS row stride
     const int Din = T.dims[din], Dout = T.dims[dout];
-    const int nto = (Dout + TO - 1) >> lgo, nti = (Din + TI - 1) >> lgi;
+    const uint32_t nto = (Dout + TO - 1) >> lgo, nti = (Din + TI - 1) >> lgi;
     const int64_t ssi = T.sstride[din], sso = T.sstride[dout];
     const int64_t dsi = T.dstride[din], dso = T.dstride[dout];
-    int64_t dbase[kCopyGroup];
-    int ib[kCopyGroup], ob[kCopyGroup];
-    AT v[kCopyGroup][kCopyRun];
+    int64_t dbase[GRP];
+    int ib[GRP], ob[GRP];
+    AT v[GRP][kCopyRun];
     // loads of every tile of the piece
 #pragma unroll
-    for (int j = 0; j < kCopyGroup; ++j) {
+    for (int j = 0; j < GRP; ++j) {
         if (j >= ng) break;
-        int64_t r = first + j;
-        const int to = (int)(r % nto);
+        uint32_t r = first + j;
+        const uint32_t to = r % nto;
         r /= nto;
-        const int ti = (int)(r % nti);
+        const uint32_t ti = r % nti;
         r /= nti;
         int64_t so = T.src_off, dofs = T.dst_off;
-        for (int k = rank - 1; k >= 0; --k) {
-            if (k == din || k == dout) continue;
-            const int ik = (int)(r % T.dims[k]);
-            r /= T.dims[k];
-            so += (int64_t)ik * T.sstride[k];
-            dofs += (int64_t)ik * T.dstride[k];
+#pragma unroll
+        for (int k = kMaxCopyRank - 1; k >= 0; --k) {
+            if (k > D.last || k == din || k == dout) continue;
+            const uint32_t ik = D.split(r, k);
+            so += (int64_t)ik * D.ss[k];
+            dofs += (int64_t)ik * D.ds[k];
         }
         dbase[j] = dofs;
-        ib[j] = ti << lgi;
-        ob[j] = to << lgo;
+        ib[j] = (int)(ti << lgi);
+        ob[j] = (int)(to << lgo);
 #pragma unroll
         for (int q = 0; q < kCopyRun; ++q) {
             const int e = threadIdx.x + q * kCopyThreads;
@@ -156,7 +199,7 @@ __device__ __forceinline__ void copy_tiles(const CopyTask& T, int64_t first, int
         }
     }
 #pragma unroll
-    for (int j = 0; j < kCopyGroup; ++j) {
+    for (int j = 0; j < GRP; ++j) {
         if (j >= ng) break;
 #pragma unroll
         for (int q = 0; q < kCopyRun; ++q) {
@@ -167,7 +210,7 @@ __device__ __forceinline__ void copy_tiles(const CopyTask& T, int64_t first, int
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kCopyGroup; ++j) {
+    for (int j = 0; j < GRP; ++j) {
         if (j >= ng) break;
 #pragma unroll
         for (int q = 0; q < kCopyRun; ++q) {
@@ -181,60 +224,134 @@ __device__ __forceinline__ void copy_tiles(const CopyTask& T, int64_t first, int
     }
 }
 
-template <typename TS, int DK, typename AT, typename G>
-__device__ __forceinline__ void copy_runs(const CopyTask& T, int64_t first, int ng, bool have_src, void* dstv,
-                                          G gather) {
-    // per chunk, each thread copies kCopyRun consecutive elements: the
-    // multi-index is decomposed for the first and advanced along the
-    // innermost dim
-    const int last = T.rank - 1;
-    const int dl = T.dims[last];
-    const int64_t sl = T.sstride[last], dls = T.dstride[last];
-    AT v[kCopyGroup][kCopyRun];
-    int64_t dd[kCopyGroup][kCopyRun];
-    int n[kCopyGroup];
+template <typename TS, int DK, int GRP, typename AT, typename G>
+__device__ __forceinline__ void copy_runs(const CopyTask& T, const TaskView& D, uint32_t first, int ng,
+                                          const TS* src, void* dstv, G gather) {
+    const bool have_src = src != nullptr;
+    // offsets of element idx; sets its index along dim `along`
+    auto locate = [&](uint32_t r, int64_t& so, int64_t& dofs, int along, int& at) {
+        so = T.src_off;
+        dofs = T.dst_off;
+        if (along == 0) at = 0;
 #pragma unroll
-    for (int j = 0; j < kCopyGroup; ++j) {
-        n[j] = 0;
-        if (j >= ng) continue;
-        const int64_t idx0 = (first + j) * kCopyChunk + (int64_t)threadIdx.x * kCopyRun;
-        if (idx0 >= T.count) continue;
-        n[j] = (int)min<int64_t>(kCopyRun, T.count - idx0);
-        int inner = 0;
-        int64_t so = 0, dofs = 0;
-        auto locate = [&](int64_t idx) {
-            uint32_t r = (uint32_t)idx;
-            so = T.src_off;
-            dofs = T.dst_off;
-            for (int k = last; k >= 0; --k) {
-                const uint32_t dk = (uint32_t)T.dims[k];
-                const uint32_t q = r / dk;
-                const uint32_t ik = r - q * dk;
-                if (k == last) inner = (int)ik;
-                r = q;
-                so += (int64_t)ik * T.sstride[k];
-                dofs += (int64_t)ik * T.dstride[k];
+        for (int k = kMaxCopyRank - 1; k >= 1; --k) {
+            if (k > D.last) continue;
+            const uint32_t ik = D.split(r, k);
+            if (k == along) at = (int)ik;
+            so += (int64_t)ik * D.ss[k];
+            dofs += (int64_t)ik * D.ds[k];
+        }
+        if (along == 0) at = (int)r;
+        so += (int64_t)r * D.ss[0];
+        dofs += (int64_t)r * D.ds[0];
+    };
+    if constexpr (DK == kDstF32 || DK == kDstF64 || DK == kDstAcc) {
+        AT v[GRP][kCopyRun];
+        if (T.run >= 0) {
+            // lanes along the destination's unit-stride dim, each a run along
+            // another dim (one load where that is the source's unit-stride dim)
+            const int64_t rs = T.sstride[T.run], rd = T.dstride[T.run];
+            const int dr = T.dims[T.run];
+            uint32_t nruns = 1;
+#pragma unroll
+            for (int k = 0; k < kMaxCopyRank; ++k) nruns *= k <= D.last ? (uint32_t)D.dims[k] : 1u;
+            int64_t dd[GRP];
+            int n[GRP];
+#pragma unroll
+            for (int j = 0; j < GRP; ++j) {
+                const uint32_t idx = (first + j) * kCopyThreads + threadIdx.x;
+                n[j] = 0;
+                if (j >= ng || idx >= nruns) continue;
+                int64_t so;
+                int at = 0;
+                locate(idx, so, dd[j], T.run, at);
+                n[j] = min(kCopyRun, dr - at * kCopyRun);
+                if (!have_src) {
+#pragma unroll
+                    for (int u = 0; u < kCopyRun; ++u) v[j][u] = (AT)0;
+                } else if (rs == 1 && T.nextra == 0 && n[j] == kCopyRun) {
+                    TS x[kCopyRun];
+                    __builtin_memcpy(x, src + so, sizeof(x));   // element-aligned
+#pragma unroll
+                    for (int u = 0; u < kCopyRun; ++u) v[j][u] = (AT)x[u] * (AT)T.scale;
+                } else {
+#pragma unroll
+                    for (int u = 0; u < kCopyRun; ++u)
+                        if (u < n[j]) v[j][u] = gather(so + u * rs);
+                }
             }
-        };
-        locate(idx0);
 #pragma unroll
-        for (int u = 0; u < kCopyRun; ++u) {
-            if (u >= n[j]) break;
-            dd[j][u] = dofs;
-            v[j][u] = have_src ? gather(so) : (AT)0;
-            if (++inner < dl) {
-                so += sl;
-                dofs += dls;
-            } else if (u + 1 < n[j]) {
-                locate(idx0 + u + 1);
+            for (int j = 0; j < GRP; ++j)
+#pragma unroll
+                for (int u = 0; u < kCopyRun; ++u)
+                    if (u < n[j]) copy_store<TS, DK>(dstv, dd[j] + u * rd, T.lo_off, v[j][u], have_src);
+        } else {
+            int64_t dd[GRP][kCopyRun];
+#pragma unroll
+            for (int j = 0; j < GRP; ++j) {
+#pragma unroll
+                for (int u = 0; u < kCopyRun; ++u) {
+                    const uint32_t idx = (first + j) * kCopyChunk + threadIdx.x + u * kCopyThreads;
+                    if (j < ng && idx < (uint32_t)T.count) {
+                        int64_t so;
+                        int at;
+                        locate(idx, so, dd[j][u], -1, at);
+                        v[j][u] = have_src ? gather(so) : (AT)0;
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < GRP; ++j)
+#pragma unroll
+                for (int u = 0; u < kCopyRun; ++u)
+                    if (j < ng && (first + j) * kCopyChunk + threadIdx.x + u * kCopyThreads < (uint32_t)T.count)
+                        copy_store<TS, DK>(dstv, dd[j][u], T.lo_off, v[j][u], have_src);
+        }
+    } else {
+        // bf16 planes: each thread takes kCopyRun consecutive elements (one
+        // vector per plane); the multi-index is decomposed for the first and
+        // advanced along the innermost dim
+        AT v[GRP][kCopyRun];
+        int64_t dd[GRP][kCopyRun];
+        int n[GRP];
+        constexpr int PL = DK == kDstBF16 ? 1 : (DK == kDstSplit ? 2 : 3);
+        const int dl = T.dims[D.last];
+        const int64_t sl = T.sstride[D.last], dls = T.dstride[D.last];
+#pragma unroll
+        for (int j = 0; j < GRP; ++j) {
+            n[j] = 0;
+            const uint32_t idx0 = (first + j) * kCopyChunk + threadIdx.x * kCopyRun;
+            if (j >= ng || idx0 >= (uint32_t)T.count) continue;
+            n[j] = (int)min((uint32_t)kCopyRun, (uint32_t)T.count - idx0);
+            int64_t so, dofs;
+            int inner = 0;
+            locate(idx0, so, dofs, D.last, inner);
+            if (inner + kCopyRun <= dl && sl == 1 && T.nextra == 0 && have_src && ((uintptr_t)(src + so) & 15) == 0) {
+                const float4 x = *(const float4*)(src + so);
+                v[j][0] = x.x * (AT)T.scale;
+                v[j][1] = x.y * (AT)T.scale;
+                v[j][2] = x.z * (AT)T.scale;
+                v[j][3] = x.w * (AT)T.scale;
+#pragma unroll
+                for (int u = 0; u < kCopyRun; ++u) dd[j][u] = dofs + u * dls;
+                continue;
+            }
+#pragma unroll
+            for (int u = 0; u < kCopyRun; ++u) {
+                if (u >= n[j]) break;
+                dd[j][u] = dofs;
+                v[j][u] = have_src ? gather(so) : (AT)0;
+                if (++inner < dl) {
+                    so += sl;
+                    dofs += dls;
+                } else if (u + 1 < n[j]) {
+                    locate(idx0 + u + 1, so, dofs, D.last, inner);
+                }
             }
         }
-    }
 #pragma unroll
-    for (int j = 0; j < kCopyGroup; ++j) {
-        if constexpr (DK == kDstBF16 || DK == kDstSplit || DK == kDstSplit3) {
+        for (int j = 0; j < GRP; ++j) {
             // four consecutive, aligned destinations: one vector per plane
-            constexpr int PL = DK == kDstBF16 ? 1 : (DK == kDstSplit ? 2 : 3);
             if (n[j] == kCopyRun && (dd[j][0] & 3) == 0 && dd[j][1] == dd[j][0] + 1 && dd[j][2] == dd[j][0] + 2 &&
                 dd[j][3] == dd[j][0] + 3) {
                 unsigned short h[kCopyRun][3];
@@ -248,28 +365,41 @@ __device__ __forceinline__ void copy_runs(const CopyTask& T, int64_t first, int 
                 }
                 continue;
             }
-        }
 #pragma unroll
-        for (int u = 0; u < kCopyRun; ++u)
-            if (u < n[j]) copy_store<TS, DK>(dstv, dd[j][u], T.lo_off, v[j][u], have_src);
+            for (int u = 0; u < kCopyRun; ++u)
+                if (u < n[j]) copy_store<TS, DK>(dstv, dd[j][u], T.lo_off, v[j][u], have_src);
+        }
     }
 }
 
-template <class Ptrs, typename TS, int DK>
+template <class Ptrs, typename TS, int DK, int GRP>
 __global__ __launch_bounds__(kCopyThreads) void copy_kernel(const CopyTask* __restrict__ tasks,
                                                             const int64_t* __restrict__ piece_prefix,
-                                                            int ntasks, Ptrs ptrs) {
+                                                            int ntasks, int64_t npieces, Ptrs ptrs) {
     using AT = std::conditional_t<DK == kDstF64, double, TS>;   // arithmetic type
-    __shared__ AT tile[kCopyGroup * kTileLds];
-    const int64_t w = blockIdx.x;
-    int lo = 0, hi = ntasks - 1;
-    while (lo < hi) {                       // last task with prefix <= w
-        int mid = (lo + hi + 1) >> 1;
-        if (piece_prefix[mid] <= w) lo = mid; else hi = mid - 1;
+    __shared__ AT tile[GRP * kTileLds];
+    // workgroup b runs on XCD b mod 8
+    const uint32_t t = blockIdx.x >> 3;
+    const int64_t w = ((t >> kCopyXcdRun) * 8 + (blockIdx.x & 7)) << kCopyXcdRun | (t & ((1u << kCopyXcdRun) - 1));
+    if (w >= npieces) return;
+    // last task with prefix <= w, 64 candidates at a time (one per lane)
+    const int lane = threadIdx.x & 63;
+    int lo = 0;
+    int64_t base = 0;
+    for (int len = ntasks; len > 1;) {
+        const int step = (len + 63) >> 6, at = lane * step;
+        const int64_t p = at < len ? piece_prefix[lo + at] : INT64_MAX;
+        const int c = max(__popcll(__ballot(p <= w)), 1) - 1;
+        base = ((int64_t)__builtin_amdgcn_readlane((int)(p >> 32), c) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)p, c);
+        lo += c * step;
+        len = min(step, len - c * step);
     }
     const CopyTask& T = tasks[lo];
-    const int64_t first = (w - piece_prefix[lo]) * kCopyGroup;
-    const int ng = (int)min<int64_t>(kCopyGroup, (int64_t)T.nchunks - first);
+    const uint32_t first = (uint32_t)(w - base) * kCopyGroup + (GRP < kCopyGroup ? blockIdx.y * GRP : 0);
+    const int ng = min(GRP, (int)(T.nchunks - first));
+    if (GRP < kCopyGroup && ng <= 0) return;
+    const TaskView D(T, DK == kDstF32 || DK == kDstF64 || DK == kDstAcc ? T.run : -1);
     const TS* __restrict__ src = T.src_buf >= 0 ? (const TS*)ptrs.get(T.src_buf) : nullptr;
     void* dstv = ptrs.get(T.dst_buf);
     const double scale = T.scale;
@@ -280,9 +410,9 @@ __global__ __launch_bounds__(kCopyThreads) void copy_kernel(const CopyTask* __re
         return sv;
     };
     if (T.tr_in >= 0)
-        copy_tiles<TS, DK, AT>(T, first, ng, dstv, tile, gather);
+        copy_tiles<TS, DK, GRP, AT>(T, D, first, ng, dstv, tile, gather);
     else
-        copy_runs<TS, DK, AT>(T, first, ng, src != nullptr, dstv, gather);
+        copy_runs<TS, DK, GRP, AT>(T, D, first, ng, src, dstv, gather);
 }
 
 // ===================================================================== gemm
@@ -820,21 +950,37 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const TileWork* __restri
 
 // Split K: every output tile of `outs` is the sum of its parts' partial
 // tiles (workspace slots slot0 .. slot0 + nparts - 1), added in part order.
+// A workgroup takes 256 vectors of 16 bytes of a tile, so that the launch is
+// many short chains of loads: one workgroup per tile left 64x64 tiles with 16
+// rounds of dependent loads in a row (24 us on average over the
+// moves at D = 6, chi = 64, f32; now 5 us).
 template <class Ptrs, typename T>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const SplitOut* __restrict__ outs,
                                                             const GemmGroup* __restrict__ groups, Ptrs ptrs,
-                                                            const T* __restrict__ ws, int BM, int BN) {
+                                                            const T* __restrict__ ws, int BM, int lg_bn) {
+    constexpr int V = 16 / sizeof(T);
+    typedef T vec __attribute__((ext_vector_type(V)));
     const SplitOut so = outs[blockIdx.x];
     const GemmGroup g = groups[so.group];
     T* __restrict__ C = (T*)ptrs.get(g.c_buf) + g.c_off;
-    const int64_t tile = (int64_t)BM * BN;
-    for (int e = threadIdx.x; e < BM * BN; e += 256) {
-        const int row = so.tm * BM + e / BN, col = so.tn * BN + e % BN;
-        if (row >= g.M || col >= g.N) continue;
-        T sum = ws[so.slot0 * tile + e];
-        for (int p = 1; p < so.nparts; ++p) sum += ws[(so.slot0 + p) * tile + e];
-        C[(int64_t)row * g.ldc + col] = sum;
+    const int e = (blockIdx.y * 256 + threadIdx.x) * V, tile = BM << lg_bn;
+    const int row = so.tm * BM + (e >> lg_bn), col = (so.tn << lg_bn) + (e & ((1 << lg_bn) - 1));
+    if (row >= g.M || col >= g.N) return;
+    const vec* __restrict__ W = (const vec*)(ws + (int64_t)so.slot0 * tile + e);
+    vec sum = W[0];
+    int p = 1;
+    for (; p + 4 <= so.nparts; p += 4) {
+        vec x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = W[(int64_t)(p + u) * (tile / V)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sum += x[u];
     }
+    for (; p < so.nparts; ++p) sum += W[(int64_t)p * (tile / V)];
+    T* __restrict__ c = C + (int64_t)row * g.ldc + col;
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+        if (col + u < g.N) c[u] = sum[u];
 }
 
 // ================================================================ utilities
@@ -1056,13 +1202,22 @@ void launch_double_layer(const DoubleLayerArgs& a, hipStream_t s) {
     HIPCHK(hipGetLastError());
 }
 
+// Pieces below which a workgroup takes a single chunk instead of a whole piece:
+// x a at D = 5, chi = 53 (f32, 266 pieces) 7.7 us against 11.1 us, C T, T a and
+// x a of a corner at D = 6, chi = 64 (f32) 27 us against 40 us; above, the
+// index work shared by the chunks of a piece counts (SU(2) move, f32, up to
+// 9258 pieces: 1.26 ms with whole pieces, 1.57 ms with single chunks).
+constexpr int64_t kCopyFine = 1024;
 // ---- prepared launches: device descriptors owned by the caller ------------
 template <class Ptrs>
 static void copy_dispatch(const CopyTask* d_tasks, const int64_t* d_prefix, int ntasks, int64_t npieces, Ptrs P,
                           bool src_f64, int dst_kind, hipStream_t s) {
-    dim3 grid((unsigned)npieces), block(kCopyThreads);
-#define SYMTEN_COPY(TS, DK) \
-    hipLaunchKernelGGL((copy_kernel<Ptrs, TS, DK>), grid, block, 0, s, d_tasks, d_prefix, ntasks, P)
+    const bool fine = npieces < kCopyFine;
+    constexpr unsigned unit = 8u << kCopyXcdRun;
+    dim3 grid(((unsigned)npieces + unit - 1) / unit * unit, fine ? kCopyGroup : 1), block(kCopyThreads);
+#define SYMTEN_COPY(TS, DK)                                                                          \
+    hipLaunchKernelGGL((fine ? copy_kernel<Ptrs, TS, DK, 1> : copy_kernel<Ptrs, TS, DK, kCopyGroup>), \
+                       grid, block, 0, s, d_tasks, d_prefix, ntasks, npieces, P)
     if (src_f64) {
         switch (dst_kind) {
             case kDstF64: SYMTEN_COPY(double, kDstF64); break;
@@ -1219,13 +1374,14 @@ static void gemm_dispatch(const TileWork* d_tiles, int ntiles, const GemmGroup* 
                            P, (float*)partials);
     HIPCHK(hipGetLastError());
     if (sk.nsplits > 0) {
-        const int BM = gemm_tile_bm(prec, cfg), BN = gemm_tile_bn(prec, cfg);
+        const int BM = gemm_tile_bm(prec, cfg), BN = gemm_tile_bn(prec, cfg), lg = __builtin_ctz(BN);
+        const dim3 grid((unsigned)sk.nsplits, (unsigned)(BM * BN * (prec == Prec::F64 ? 8 : 4) / (256 * 16)));
         if (prec == Prec::F64)
-            hipLaunchKernelGGL((splitk_reduce_kernel<Ptrs, double>), dim3(sk.nsplits), dim3(256), 0, s, sk.splits,
-                               d_groups, P, (const double*)partials, BM, BN);
+            hipLaunchKernelGGL((splitk_reduce_kernel<Ptrs, double>), grid, dim3(256), 0, s, sk.splits, d_groups, P,
+                               (const double*)partials, BM, lg);
         else
-            hipLaunchKernelGGL((splitk_reduce_kernel<Ptrs, float>), dim3(sk.nsplits), dim3(256), 0, s, sk.splits,
-                               d_groups, P, (const float*)partials, BM, BN);
+            hipLaunchKernelGGL((splitk_reduce_kernel<Ptrs, float>), grid, dim3(256), 0, s, sk.splits, d_groups, P,
+                               (const float*)partials, BM, lg);
         HIPCHK(hipGetLastError());
     }
 }

@@ -400,9 +400,25 @@ static void simplify_task(CopyTask& t) {
             }
         }
     }
+    // A direct copy by runs of four elements along one of the outer dims needs
+    // one index computation per run: the source's unit-stride dim if it is
+    // one of them (its runs are single loads), else the dim that leaves the
+    // fewest places of its runs empty, at most a quarter of them.
+    t.run = -1;
+    if (t.tr_in < 0) {
+        double best = 0.75;
+        for (int k = m - 2; k >= 0; --k) {
+            const double used = t.dims[k] / (4.0 * ((t.dims[k] + 3) / 4));
+            if (used < best || (t.run >= 0 && used == best && t.sstride[k] != 1)) continue;
+            if (t.run >= 0 && t.sstride[t.run] == 1 && t.src_buf >= 0) continue;
+            t.run = k;
+            best = t.src_buf >= 0 && t.sstride[k] == 1 ? 2.0 : used;
+        }
+    }
 }
 
 int64_t copy_task_chunks(const CopyTask& t) {
+    if (t.tr_in < 0 && t.run >= 0) return ((int64_t)t.count / t.dims[t.run] * ((t.dims[t.run] + 3) / 4) + 255) / 256;
     if (t.tr_in < 0) return (t.count + 1023) / 1024;
     const int64_t to = 1 << t.lg_out, ti = 1024 >> t.lg_out;
     int64_t n = ((t.dims[t.tr_out] + to - 1) / to) * ((t.dims[t.tr_in] + ti - 1) / ti);
