@@ -14,9 +14,9 @@
 //      workgroups (its p slices and the next row, through global memory).
 //      The jobs of a launch sit on disjoint workgroups, each job on the
 //      workgroups of one XCD where it fits.
-//   2. All eigenvalues by multisection: one wavefront per eigenvalue, its 64
-//      lanes evaluating Sturm counts of T at 64 points of the current
-//      interval, about 9 passes to 2 ulp.
+//   2. All eigenvalues by multisection: counts on a grid common to all, then
+//      one wavefront per eigenvalue, its 64 lanes evaluating Sturm counts of T
+//      at 64 points of the current interval, about 7 passes to 2 ulp.
 //   3. Eigenvectors of T for the kept eigenvalues from the twisted
 //      factorisation of T - lam I (two recurrences at once, no iteration), a
 //      workgroup each.  Eigenvalues closer than 1e-3 ||T|| form a cluster,
@@ -24,7 +24,8 @@
 //      ones projected out, and if less than half of it is left (a degenerate
 //      value) it comes from inverse iteration instead (tridiagonal LU with
 //      partial pivoting, two solves from a fixed pseudo-random start,
-//      reorthogonalised in every solve).
+//      reorthogonalised in every solve).  What is left of the products of
+//      close vectors is taken out in one pass over all (polish_kernel).
 //   4. Back-transformation z <- Q z through the stored reflectors, a vector
 //      in the registers of one wavefront (four above n = 704).
 // The matrix is scaled by a power of two (exact) so that its largest entry
@@ -53,7 +54,7 @@ __host__ __device__ inline int v_stride(int n) { return (n + 63) & ~63; }
 struct TridJob {
     const double* A;                   // n x n, column-major (ld lda), both triangles
     int n, lda, G;                     // order, leading dim, workgroups
-    double *d, *e, *tau, *V, *scale;   // outputs (scaled by *scale); V: reflector k in row k, stride v_stride(n),
+    double *d, *e, *e2, *tau, *V, *scale;   // outputs (scaled by *scale; e2: coupling2 of e); V: reflector k in row k, stride v_stride(n),
                                        // zeros outside its entries k+1 .. n-1
     double* xbuf;                      // exchange area (xbuf_doubles), filled with kEmpty
     int* status;                       // set to 1 if an exchange gave up
@@ -234,6 +235,11 @@ __device__ inline void householder(double alpha, double xn2, double& beta, doubl
         scal = copysign(rcp_newton(fabs(alpha) + h), alpha);  // 1 / (alpha - beta)
     }
 }
+// Square of an off-diagonal entry of T as the Sturm counts take it: never
+// zero, so that a product that comes out as exactly zero does not end the
+// sequence (entries of T are at most 2^13, so 2^-100 is no change of T).
+__device__ inline double coupling2(double e) { return fmax(e * e, 0x1p-200); }
+
 __global__ void fill_empty_kernel(uint64_t* __restrict__ d, int64_t n) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         d[i] = kEmpty;
@@ -371,6 +377,7 @@ struct Trid {
                 if (tid == 0) {
                     Jd[k] = dk;
                     Je[k] = beta;
+                    ((gf64*)J.e2)[k] = coupling2(beta);
                     Jtau[k] = tau;
                 }
             }
@@ -654,7 +661,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 struct BidJob {
     const double* Y;                   // nu x nv, column-major (ld ldy)
     int nu, nv, ldy, G, variant;
-    double *d, *e, *scale;             // T of order nu + nv, scaled by *scale
+    double *d, *e, *e2, *scale;        // T of order nu + nv, scaled by *scale
     double *V[2], *tau[2];             // reflectors and factors of the v side (0) and the u side (1)
     double* xbuf;                      // exchange area (bid_xbuf_doubles), filled with kEmpty
     int* status;
@@ -737,6 +744,7 @@ struct Bid {
             if (tid == 0) {
                 ((gf64*)z.J.tau[S])[i] = tau;
                 ((gf64*)z.J.e)[2 * i + S] = beta;
+                ((gf64*)z.J.e2)[2 * i + S] = coupling2(beta);
             }
         }
         if (last) return;
@@ -888,10 +896,13 @@ struct Bid {
         if (tid == 0) *failed = 0;
         for (int j = tid; j < 2 * PAIRS; j += T) sm[LVW + j] = 0.0;
         if (g == 0) {
-            gf64 *d = (gf64*)J.d, *e = (gf64*)J.e;
+            gf64 *d = (gf64*)J.d, *e = (gf64*)J.e, *e2 = (gf64*)J.e2;
             for (int j = tid; j < N; j += T) {
                 d[j] = 0.0;
-                if (j >= bid_columns(nu, nv)) e[j] = 0.0;
+                if (j >= bid_columns(nu, nv)) {
+                    e[j] = 0.0;
+                    e2[j] = coupling2(0.0);
+                }
             }
         }
         double au[RW][CW], av[RW][CW];   // rows of Y, rows of Y^T
@@ -1004,82 +1015,152 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 struct BisJob {
-    const double *d, *e, *scale;
+    const double *d, *e, *e2, *scale;
     double* w;      // n eigenvalues, ascending, unscaled
-    int n;
+    double* range;  // lower end, upper end and norm of the spectrum's interval
+    int* count;     // eigenvalues below grid points 1 .. points of the interval
+    int n, points;
     int half;       // > 0: spectrum +-, the `half` largest are found, the rest mirrored or zero
 };
 
-// Step 2.  bmap[b] = (job, first index); wave q of the workgroup finds the
-// eigenvalue of index first + q (ascending).  Dynamic LDS: d and e^2.
+// Number of eigenvalues of T below x: sign changes of the leading principal
+// minors p_i = (d_i - x) p_{i-1} - e2_{i-1} p_{i-2}, which carries the same
+// kind of relative errors in d_i - x and e2 as the quotients p_i / p_{i-1}, but
+// needs no division: 24 + 18 instructions per eight steps, where a reciprocal
+// with a Newton step and the guard of the quotient took twice the time per
+// step.  T is wave-uniform and comes through the scalar cache (d and e^2 in LDS
+// took two broadcast reads per step).  The pair is scaled back every eight
+// steps: entries of T are below 2^13 and coupling2 is at least 2^-200, so
+// eight steps stay within the exponents.  With three to thirteen wavefronts per
+// SIMD the instructions bound it: all values of the seven matrices of a move at
+// D = 6, chi = 64 (3.3e3 in all) 393 -> 175 us in FP32, 775 -> 329 us in FP64,
+// of the sixteen at D = 8, chi = 200 6.9 -> 2.3 ms, with the grid below.
+#ifdef __HIP_DEVICE_COMPILE__
+#define UNIFORM_MEM __attribute__((address_space(4)))
+#else
+#define UNIFORM_MEM
+#endif
+typedef UNIFORM_MEM const double cf64;
+__device__ inline uint32_t high_word(double x) { return (uint32_t)(__builtin_bit_cast(uint64_t, x) >> 32); }
+__device__ inline int sturm_count(cf64* d, cf64* e2, int n, double x) {
+    double p0 = 1.0, p1 = d[0] - x;
+    uint32_t signs = high_word(p1) >> 31;   // bit 0: the last minor's sign
+    int cnt = (int)signs, i = 1;
+    auto step = [&](double di, double ei) {
+        const double p2 = fma(di - x, p1, -(ei * p0));
+        p0 = p1;
+        p1 = p2;
+        signs = signs << 1 | high_word(p2) >> 31;
+    };
+    for (; i + 8 <= n; i += 8) {
+        double D[8], E[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            D[u] = d[i + u];
+            E[u] = e2[i + u - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) step(D[u], E[u]);
+        cnt += __popc((signs ^ signs >> 1) & 0xff);
+        const int ex = 1023 - (int)max(high_word(p0) >> 20 & 0x7ff, high_word(p1) >> 20 & 0x7ff);
+        p0 = __builtin_amdgcn_ldexp(p0, ex);
+        p1 = __builtin_amdgcn_ldexp(p1, ex);
+    }
+    for (; i < n; ++i) {
+        step(d[i], e2[i - 1]);
+        cnt += (signs ^ signs >> 1) & 1;
+    }
+    return cnt;
+}
+
+// Step 2, first part: counts at equally spaced points of the interval, 64 per
+// wave; bmap[b] = (job, first group of 64 points).  They serve all eigenvalues
+// of the job: with 8 points per eigenvalue (kGridShare) each starts from an
+// interval two multisection passes small, for an eighth of one pass.
+constexpr int kGridShare = 8;
+__host__ __device__ inline int grid_points(int n) { return 64 * ((n + kGridShare - 1) / kGridShare); }
+__global__ __launch_bounds__(kEigThreads) void bisect_grid_kernel(const BisJob* __restrict__ jobs,
+                                                                   const int2* __restrict__ bmap) {
+    const int2 bm = bmap[blockIdx.x];
+    const BisJob J = jobs[bm.x];
+    const int n = J.n;
+    __shared__ double red[kEigWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double lo = INFINITY, hi = -INFINITY;
+    for (int i = tid; i < n; i += kEigThreads) {
+        const double di = J.d[i];
+        const double el = i > 0 ? fabs(J.e[i - 1]) : 0.0, er = i + 1 < n ? fabs(J.e[i]) : 0.0;
+        lo = fmin(lo, di - el - er);
+        hi = fmax(hi, di + el + er);
+    }
+    // (block_max is a maximum of values >= 0: of the distances from an entry)
+    const double d0 = J.d[0];
+    lo = d0 - block_max<kEigWaves>(d0 - fmin(lo, d0), red);
+    hi = d0 + block_max<kEigWaves>(fmax(hi, d0) - d0, red);
+    const double tnorm = fmax(fabs(lo), fabs(hi));
+    lo -= 4.0 * DBL_EPSILON * tnorm * n;
+    hi += 4.0 * DBL_EPSILON * tnorm * n;
+    const int t = (bm.y + wave) * 64 + lane;
+    if (tnorm > 0.0 && (bm.y + wave) * 64 < J.points)
+        J.count[t] = sturm_count((cf64*)J.d, (cf64*)J.e2, n, lo + (hi - lo) * (double)(t + 1) / (double)(J.points + 1));
+    if (bm.y == 0 && tid == 0) {
+        J.range[0] = lo;
+        J.range[1] = hi;
+        J.range[2] = tnorm;
+    }
+}
+
+// Second part.  bmap[b] = (job, first index); wave q of the workgroup finds the
+// eigenvalue of index first + q (ascending): its interval from the grid's
+// counts, then passes of 64 counts each, about 7, to 2 ulp.
 __global__ __launch_bounds__(kEigThreads) void bisect_kernel(const BisJob* __restrict__ jobs,
                                                               const int2* __restrict__ bmap) {
     const int2 bm = bmap[blockIdx.x];
     const BisJob J = jobs[bm.x];
     const int n = J.n;
-    extern __shared__ double sm[];
-    double* d = sm;
-    double* e2 = sm + n;
-    __shared__ double red[kEigWaves];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double lo = INFINITY, hi = -INFINITY, em = 0.0;
-    for (int i = tid; i < n; i += kEigThreads) {
-        const double di = J.d[i];
-        const double el = i > 0 ? fabs(J.e[i - 1]) : 0.0, er = i + 1 < n ? fabs(J.e[i]) : 0.0;
-        d[i] = di;
-        e2[i] = er * er;   // e2[i] couples i and i+1
-        lo = fmin(lo, di - el - er);
-        hi = fmax(hi, di + el + er);
-        em = fmax(em, er * er);
-    }
-    lo = -block_max<kEigWaves>(-lo, red);
-    hi = block_max<kEigWaves>(hi, red);
-    em = block_max<kEigWaves>(em, red);
-    const double tnorm = fmax(fabs(lo), fabs(hi));
-    const double pivmin = DBL_MIN * fmax(1.0, em);
+    const int lane = threadIdx.x & 63, j = __builtin_amdgcn_readfirstlane(bm.y + (int)(threadIdx.x >> 6));
+    if (j >= n) return;
+    const double lo = J.range[0], hi = J.range[1], tnorm = J.range[2];
     const double eps = DBL_EPSILON;
-    lo -= 2.0 * eps * tnorm * n + pivmin;
-    hi += 2.0 * eps * tnorm * n + pivmin;
-    const int j = bm.y + wave;
-    if (j >= n) return;   // no block-wide synchronisation below
-    // the mirrored values: their places, and zeros between the two halves
     const bool mirror = J.half > 0;
+    double a = lo, b = hi;
+    if (!(tnorm > 0.0)) {   // T = 0
+        a = b = 0.0;
+    } else {
+        // first grid point with more than j eigenvalues below it
+        int first = 0, len = J.points;
+        while (len > 0) {
+            const int step = (len + 63) >> 6, at = min(lane * step + step - 1, len - 1);   // last of the lane's part
+            const unsigned long long above = __ballot(J.count[first + at] > j);
+            if (!above) {
+                first += len;
+                break;
+            }
+            const int c = __ffsll((long long)above) - 1;
+            first += c * step;
+            len = min(step, len - c * step);
+            if (step == 1) break;
+        }
+        const double h = hi - lo, np = (double)(J.points + 1);
+        if (first > 0) a = lo + h * (double)first / np;
+        if (first < J.points) b = lo + h * (double)(first + 1) / np;
+        for (int pass = 0; pass < 64; ++pass) {
+            const double x = a + (b - a) * (double)(lane + 1) / 65.0;
+            const int cnt = sturm_count((cf64*)J.d, (cf64*)J.e2, n, x);
+            const unsigned long long above = __ballot(cnt > j);
+            const int m = above ? __ffsll((long long)above) - 1 : 64;
+            const double xm1 = __shfl(x, m > 0 ? m - 1 : 0, 64);
+            const double xm = __shfl(x, m < 64 ? m : 63, 64);
+            const double na = m > 0 ? xm1 : a, nb = m < 64 ? xm : b;
+            const bool stuck = na == a && nb == b;
+            a = na;
+            b = nb;
+            if (stuck || b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)), eps * tnorm)) break;
+        }
+    }
+    // the mirrored values: their places, and zeros between the two halves
     if (mirror && j == n - 1)
         for (int i = J.half + lane; i < n - J.half; i += 64) J.w[i] = 0.0;
-    if (tnorm == 0.0) {   // T = 0
-        if (lane == 0) {
-            J.w[j] = 0.0;
-            if (mirror) J.w[n - 1 - j] = 0.0;
-        }
-        return;
-    }
-    double a = lo, b = hi;
-    for (int pass = 0; pass < 64; ++pass) {
-        const double x = a + (b - a) * (double)(lane + 1) / 65.0;
-        int cnt = 0;
-        double q = d[0] - x;
-        if (fabs(q) < pivmin) q = -pivmin;
-        cnt += q < 0.0;
-        for (int i = 1; i < n; ++i) {
-            // e2 / q with the hardware reciprocal and one Newton step
-            // (full precision in two fused operations instead of a
-            // division's sequence)
-            const double r0 = __builtin_amdgcn_rcp(q);
-            const double r1 = fma(r0, fma(-q, r0, 1.0), r0);
-            q = (d[i] - x) - e2[i - 1] * r1;
-            if (fabs(q) < pivmin) q = -pivmin;
-            cnt += q < 0.0;
-        }
-        const unsigned long long above = __ballot(cnt > j);
-        const int m = above ? __ffsll((long long)above) - 1 : 64;
-        const double xm1 = __shfl(x, m > 0 ? m - 1 : 0, 64);
-        const double xm = __shfl(x, m < 64 ? m : 63, 64);
-        const double na = m > 0 ? xm1 : a, nb = m < 64 ? xm : b;
-        const bool stuck = na == a && nb == b;
-        a = na;
-        b = nb;
-        if (stuck || b - a <= fmax(2.0 * eps * fmax(fabs(a), fabs(b)), eps * tnorm)) break;
-    }
     if (lane == 0) {
         const double x = 0.5 * (a + b) / *J.scale;
         J.w[j] = x;
@@ -1096,6 +1177,7 @@ constexpr int kInvIters = 2;
 struct VecJob {
     const double *d, *e, *scale, *w;   // w: eigenvalues ascending, unscaled
     double* Zt;                        // n x kv eigenvectors of T (column j: j-th largest)
+    double* Zp;                        // the same after polish_kernel
     double* work;                      // 5 n per cluster slot
     int n, kv;
 };
@@ -1419,6 +1501,54 @@ __global__ __launch_bounds__(64) void cluster_kernel(const VecJob* __restrict__ 
     }
 }
 
+// Vectors of eigenvalues a gap g ||T|| apart are orthogonal to about eps / g,
+// 2e-13 at the 1e-3 where clusters end: each gives up half of its product with
+// the kNear vectors on either side of it that are less than 1e-2 ||T|| away
+// (all products before any change), which leaves them orthogonal to rounding.
+constexpr int kNear = 3;
+__global__ __launch_bounds__(kEigThreads) void polish_kernel(const VecJob* __restrict__ jobs,
+                                                              const int2* __restrict__ bmap) {
+    const int2 bm = bmap[blockIdx.x];
+    const VecJob J = jobs[bm.x];
+    const int n = J.n, jr = bm.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ double red[2 * kNear][kEigWaves];
+    const double near = 1e-2 * fmax(fabs(J.w[0]), fabs(J.w[n - 1])), wj = J.w[n - 1 - jr];
+    const double* z = J.Zt + (size_t)jr * n;
+    const double* y[2 * kNear];
+    double dot[2 * kNear];
+#pragma unroll
+    for (int q = 0; q < 2 * kNear; ++q) {
+        const int i = jr + (q < kNear ? q - kNear : q - kNear + 1);
+        y[q] = i >= 0 && i < J.kv && fabs(J.w[n - 1 - i] - wj) < near ? J.Zt + (size_t)i * n : nullptr;
+        dot[q] = 0.0;
+    }
+    for (int r = tid; r < n; r += kEigThreads) {
+        const double x = z[r];
+#pragma unroll
+        for (int q = 0; q < 2 * kNear; ++q)
+            if (y[q]) dot[q] = fma(y[q][r], x, dot[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 2 * kNear; ++q) {
+        const double t = wave_sum(dot[q]);
+        if (lane == 0) red[q][wave] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2 * kNear; ++q) {
+        dot[q] = 0.0;
+#pragma unroll
+        for (int u = 0; u < kEigWaves; ++u) dot[q] += red[q][u];
+    }
+    for (int r = tid; r < n; r += kEigThreads) {
+        double x = z[r];
+#pragma unroll
+        for (int q = 0; q < 2 * kNear; ++q)
+            if (y[q]) x = fma(-0.5 * dot[q], y[q][r], x);
+        J.Zp[(size_t)jr * n + r] = x;
+    }
+}
+
 struct BackJob {
     const double *V, *tau, *Zt;   // reflectors; vectors of T (column j at Zt + j ldt)
     double* Z;                    // column j at Z + j ldz, n entries
@@ -1571,11 +1701,11 @@ void set_lds_limits(const DevInfo& di) {
     HIPCHK(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lk(mu);
     if (done.count(dev)) return;
-    const char* names[] = {"tridiag", "tridiag_wide", "bidiag", "bisect", "cluster", "cluster", "twist"};
+    const char* names[] = {"tridiag", "tridiag_wide", "bidiag", "cluster", "cluster", "twist"};
     const void* fns[] = {(const void*)tridiag_kernel, (const void*)tridiag_wide_kernel, (const void*)bidiag_kernel,
-                         (const void*)bisect_kernel, (const void*)cluster_kernel<true>,
-                         (const void*)cluster_kernel<false>, (const void*)twist_kernel};
-    for (int i = 0; i < 7; ++i) {
+                         (const void*)cluster_kernel<true>, (const void*)cluster_kernel<false>,
+                         (const void*)twist_kernel};
+    for (int i = 0; i < 6; ++i) {
         const hipError_t e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, di.lds);
         if (e != hipSuccess)
             fail(SYMTEN_E_HIP, std::string("eigh: dynamic LDS limit of the ") + names[i] + " kernel: " +
@@ -1600,7 +1730,7 @@ size_t xbuf_doubles(int n, const TridVariant& v, int G) {
 struct EighWork {
     std::vector<EighProblem> probs;
     std::vector<BufferPtr> keep;
-    std::vector<double*> d, e, scale, w;
+    std::vector<double*> d, e, e2, scale, w;
     std::vector<std::array<double*, 2>> tau, V;   // Jordan-Wielandt: v side, u side
     int* status = nullptr;               // one per problem
 };
@@ -1655,7 +1785,7 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
         else tridiag_shape(n, di, Vs[p], Gs[p]);
         if (Gs[p] == 0) fail(SYMTEN_E_CAPACITY, "eigh: matrix of order " + std::to_string(n) + " exceeds the registers of the chip");
         xdoubles += xbuf_of(p);
-        doubles += 2 * (size_t)n + 1;
+        doubles += 3 * (size_t)n + 1;
         doubles += jw(p) ? ((size_t)P.ru + P.rd) + (size_t)std::min(P.ru, P.rd) * (v_stride(P.ru) + v_stride(P.rd))
                          : (size_t)n + (size_t)n * v_stride(n);
         nmax = std::max(nmax, n);
@@ -1695,12 +1825,14 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
         }
         double* d = q; q += n;
         double* e = q; q += n;
+        double* e2 = q; q += n;
         double* scale = q; q += 1;
         int* status = P.status ? P.status : wk->status + p;
-        if (jw(p)) gj[p] = BidJob{P.A, P.ru, P.rd, P.lda, Gs[p], Vs[p], d, e, scale, {V[0], V[1]}, {tau[0], tau[1]}, xb[p], status};
-        else tj[p] = TridJob{P.A, n, P.lda, Gs[p], d, e, tau[0], V[0], scale, xb[p], status, Vs[p]};
+        if (jw(p)) gj[p] = BidJob{P.A, P.ru, P.rd, P.lda, Gs[p], Vs[p], d, e, e2, scale, {V[0], V[1]}, {tau[0], tau[1]}, xb[p], status};
+        else tj[p] = TridJob{P.A, n, P.lda, Gs[p], d, e, e2, tau[0], V[0], scale, xb[p], status, Vs[p]};
         wk->d.push_back(d);
         wk->e.push_back(e);
+        wk->e2.push_back(e2);
         wk->tau.push_back(tau);
         wk->V.push_back(V);
         wk->scale.push_back(scale);
@@ -1787,27 +1919,33 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
                                               (unsigned)lds_bytes, s));
         });
     }
-    // ---- step 2: one wave per eigenvalue, four per workgroup
+    // ---- step 2: 64 points of the grid, then one eigenvalue, per wave; four
+    // waves per workgroup
     {
+        size_t points = 0;
+        for (int p = 0; p < np; ++p) points += grid_points(probs[p].n);
+        BufferPtr grid = device_alloc(8 * 3 * (size_t)np + sizeof(int) * points);
+        double* range = (double*)grid->ptr;
+        int* count = (int*)(range + 3 * (size_t)np);
         std::vector<BisJob> bj(np);
-        std::vector<int2> bmap;
+        std::vector<int2> gmap, bmap;
         for (int p = 0; p < np; ++p) {
             const int n = probs[p].n, half = jw(p) ? std::min(probs[p].ru, probs[p].rd) : 0;
-            bj[p] = BisJob{wk->d[p], wk->e[p], wk->scale[p], probs[p].w, n, half};
+            const int pts = grid_points(n);
+            bj[p] = BisJob{wk->d[p], wk->e[p], wk->e2[p], wk->scale[p], probs[p].w, range + 3 * p, count, n, pts, half};
+            count += pts;
+            for (int t = 0; t < pts / 64; t += kEigWaves) gmap.push_back(make_int2(p, t));
             for (int j = half ? n - half : 0; j < n; j += kEigWaves) bmap.push_back(make_int2(p, j));
         }
-        const size_t jb = sizeof(BisJob) * np, mb = sizeof(int2) * bmap.size();
-        std::vector<char> host(jb + mb);
-        std::memcpy(host.data(), bj.data(), jb);
-        std::memcpy(host.data() + jb, bmap.data(), mb);
-        BufferPtr db;
-        upload_async(db, host.data(), host.size(), s);
-        descs.push_back(db);
-        const size_t lb = 16 * (size_t)nmax;
-        if (lb > lds_bytes) fail(SYMTEN_E_CAPACITY, "eigh: tridiagonal matrix exceeds LDS");
+        Tables tab;
+        const size_t oj = tab.add(bj), og = tab.add(gmap), ob = tab.add(bmap);
+        tab.send(s);
         profile_launch("eigh_bisect", 0, 0, 0, s, [&] {
-            hipLaunchKernelGGL(bisect_kernel, dim3((unsigned)bmap.size()), dim3(kEigThreads), lb, s,
-                               (const BisJob*)db->ptr, (const int2*)((const char*)db->ptr + jb));
+            hipLaunchKernelGGL(bisect_grid_kernel, dim3((unsigned)gmap.size()), dim3(kEigThreads), 0, s,
+                               tab.at<BisJob>(oj), tab.at<int2>(og));
+            HIPCHK(hipGetLastError());
+            hipLaunchKernelGGL(bisect_kernel, dim3((unsigned)bmap.size()), dim3(kEigThreads), 0, s,
+                               tab.at<BisJob>(oj), tab.at<int2>(ob));
             HIPCHK(hipGetLastError());
         });
     }
@@ -1857,7 +1995,7 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
         ztot += (size_t)n * k;
     }
     if (nvec == 0) return;
-    BufferPtr zt = device_alloc(8 * ztot);
+    BufferPtr zt = device_alloc(8 * 2 * ztot);   // as they come, then polished
     BufferPtr work = device_alloc(8 * std::max<size_t>(worktot, 1));
     std::vector<VecJob> vj(np);
     std::vector<BackJob> bj;
@@ -1867,8 +2005,8 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
     for (int p = 0; p < np; ++p) {
         const EighProblem& P = wk.probs[p];
         const int n = P.n;
-        double* z = (double*)zt->ptr + zo;
-        vj[p] = VecJob{wk.d[p], wk.e[p], wk.scale[p], wk.w[p], z, (double*)work->ptr, n, kv[p]};
+        double *zr = (double*)zt->ptr + zo, *z = zr + ztot;
+        vj[p] = VecJob{wk.d[p], wk.e[p], wk.scale[p], wk.w[p], zr, z, (double*)work->ptr, n, kv[p]};
         for (int c = 0; c < kv[p]; ++c) bmap.push_back(make_int2(p, c));
         const int first = (int)bj.size();
         if (P.rd > 0) {   // the u and the v entries go back on their own
@@ -1918,6 +2056,10 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
                                    dvj, dcl);
             HIPCHK(hipGetLastError());
         });
+    profile_launch("eigh_polish", 0, 0, 0, s, [&] {
+        hipLaunchKernelGGL(polish_kernel, dim3((unsigned)nvec), dim3(kEigThreads), 0, s, dvj, dmap);
+        HIPCHK(hipGetLastError());
+    });
     int64_t bflops = 0;   // back-transformation: 2 n^2 per vector
     for (auto& t : tmap) bflops += 2 * (int64_t)bj[t.x].n * bj[t.x].n;
     profile_launch("eigh_backtr", bflops, bflops, 0, s, [&] {
