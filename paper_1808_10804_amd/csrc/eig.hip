@@ -616,9 +616,16 @@ struct TridVariant {
 };
 const TridVariant kTridVariants[] = {
     {256, 1, 2, 32, 0}, {256, 1, 3, 12, 0}, {256, 1, 4, 8, 0},  {256, 1, 6, 6, 0}, {256, 1, 8, 5, 0}, {256, 1, 11, 6, 0},
-    {512, 2, 8, 8, 0},  {512, 4, 6, 12, 0}, {512, 8, 4, 20, 0}, {512, 8, 6, 15, 4}, {512, 8, 7, 13, 3}};
-constexpr int kTridVariantsN = sizeof(kTridVariants) / sizeof(kTridVariants[0]);
-constexpr int kTridWide = 6;   // first 512-thread variant
+    {512, 2, 8, 8, 0},  {512, 4, 6, 12, 0}, {512, 8, 4, 20, 0}, {512, 8, 6, 15, 4}, {512, 8, 7, 13, 3},
+    {512, 1, 6, 4, 0}, {512, 2, 6, 6, 0}};
+constexpr int kTridVariantsN = 11;   // chosen by the order alone
+constexpr int kTridWide = 6;         // first 512-thread variant
+// Two more of 512 threads for orders that have 256-thread variants, so that
+// jobs of both kinds share a launch (cooperative launches run one after
+// another): the smaller jobs then end with the larger ones instead of after them
+// (SU(2) move, f32, orders up to 1024:
+// 3.85 ms in two launches, 2.40 ms in one).
+constexpr int kTridJoint = kTridVariantsN, kTridJointN = 2;
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void tridiag_kernel(
     const TridJob* __restrict__ jobs, const int2* __restrict__ bmap) {
@@ -646,7 +653,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         case 7: Trid<512, 4, 6, 12>::job(J, bm.y, sm); break;
         case 8: Trid<512, 8, 4, 20>::job(J, bm.y, sm); break;
         case 9: Trid<512, 8, 6, 15, 4>::job(J, bm.y, sm); break;
-        default: Trid<512, 8, 7, 13, 3>::job(J, bm.y, sm); break;
+        case 10: Trid<512, 8, 7, 13, 3>::job(J, bm.y, sm); break;
+        case 11: Trid<512, 1, 6, 4>::job(J, bm.y, sm); break;
+        default: Trid<512, 2, 6, 6>::job(J, bm.y, sm); break;
     }
 }
 
@@ -1664,11 +1673,13 @@ size_t tridiag_lds(const TridVariant& v) {   // Trid::LDS
     return 8 * (size_t)(2 * nq + 2 * (v.rows() + 64) + (wr > 1 ? 2 * nq : 0) + (v.rows() >= np ? 2 * np : 0) + 2 * nw +
                         (v.WC > 1 ? nw * (v.RW + 3) : 0) + 2 + wr * v.RL * np);
 }
-void tridiag_shape(int n, const DevInfo& di, int& variant, int& G) {
-    variant = G = 0;
+void tridiag_shape(int n, const DevInfo& di, int& variant, int& G, bool joint = false) {
+    const int end = joint ? kTridJoint + kTridJointN : kTridVariantsN;
+    variant = joint ? kTridJoint : 0;
+    G = 0;
     if (n <= 0) return;
-    while (variant < kTridVariantsN && kTridVariants[variant].nmax() < n) ++variant;
-    if (variant == kTridVariantsN) return;
+    while (variant < end && kTridVariants[variant].nmax() < n) ++variant;
+    if (variant == end) return;
     const TridVariant& v = kTridVariants[variant];
     const int g = (n + v.rows() - 1) / v.rows();
     // the vector steps hold T and its factorisations (5 n) in LDS
@@ -1774,8 +1785,6 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
         return jw(p) ? bid_xbuf_doubles(probs[p].ru, probs[p].rd, kBidVariants[Vs[p]], Gs[p])
                      : xbuf_doubles(probs[p].n, kTridVariants[Vs[p]], Gs[p]);
     };
-    size_t doubles = 0, xdoubles = 0;
-    int nmax = 0;
     for (int p = 0; p < np; ++p) {
         const EighProblem& P = probs[p];
         const int n = P.n;
@@ -1784,11 +1793,62 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
         if (jw(p)) bid_shape(P.ru, P.rd, di, Vs[p], Gs[p]);
         else tridiag_shape(n, di, Vs[p], Gs[p]);
         if (Gs[p] == 0) fail(SYMTEN_E_CAPACITY, "eigh: matrix of order " + std::to_string(n) + " exceeds the registers of the chip");
+    }
+    // ---- launches of step 1: jobs by size, packed into launches of at most
+    // one workgroup per compute unit, Jordan-Wielandt jobs and jobs of 512 and of
+    // 256 threads in launches of their own
+    auto kind = [&](int p) { return jw(p) ? 2 : (Vs[p] >= kTridWide ? 1 : 0); };
+    auto pack = [&] {
+        std::vector<int> order(np);
+        for (int p = 0; p < np; ++p) order[p] = p;
+        std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+            return kind(a) != kind(b) ? kind(a) > kind(b) : Gs[a] > Gs[b];
+        });
+        // largest first, each into the first launch of its kind with room
+        std::vector<std::vector<int>> out;
+        std::vector<int> used;
+        for (int p : order) {
+            size_t l = 0;
+            while (l < out.size() && (kind(out[l][0]) != kind(p) || used[l] + Gs[p] > di.cus)) ++l;
+            if (l == out.size()) {
+                out.emplace_back();
+                used.push_back(0);
+            }
+            out[l].push_back(p);
+            used[l] += Gs[p];
+        }
+        return out;
+    };
+    std::vector<std::vector<int>> launches = pack();
+    {   // all in 512-thread variants if that saves a launch
+        bool kinds[3] = {false, false, false};
+        for (int p = 0; p < np; ++p) kinds[kind(p)] = true;
+        if (kinds[0] && kinds[1]) {
+            const std::vector<int> v0 = Vs, g0 = Gs;
+            bool fits = true;
+            for (int p = 0; p < np; ++p)
+                if (kind(p) == 0) {
+                    tridiag_shape(probs[p].n, di, Vs[p], Gs[p], true);
+                    fits = fits && Gs[p] > 0;
+                }
+            std::vector<std::vector<int>> joint;
+            if (fits) joint = pack();
+            if (fits && joint.size() < launches.size()) {
+                launches = std::move(joint);
+            } else {
+                Vs = v0;
+                Gs = g0;
+            }
+        }
+    }
+    size_t doubles = 0, xdoubles = 0;
+    for (int p = 0; p < np; ++p) {
+        const EighProblem& P = probs[p];
+        const int n = P.n;
         xdoubles += xbuf_of(p);
         doubles += 3 * (size_t)n + 1;
         doubles += jw(p) ? ((size_t)P.ru + P.rd) + (size_t)std::min(P.ru, P.rd) * (v_stride(P.ru) + v_stride(P.rd))
                          : (size_t)n + (size_t)n * v_stride(n);
-        nmax = std::max(nmax, n);
     }
     doubles += xdoubles;
     BufferPtr buf = device_alloc(8 * doubles + 8 * (size_t)np * 2);
@@ -1838,32 +1898,9 @@ std::shared_ptr<EighWork> eigh_values(const std::vector<EighProblem>& probs, hip
         wk->scale.push_back(scale);
         wk->w.push_back(P.w);
     }
-    // ---- launches of step 1: jobs by size, packed into launches of at most
-    // one workgroup per compute unit; a job that fits one XCD (cus / 8
-    // workgroups) takes blocks b = x (mod 8) of one XCD x
-    std::vector<int> order(np);
-    for (int p = 0; p < np; ++p) order[p] = p;
-    // Jordan-Wielandt jobs and jobs of 512 and of 256 threads have a kernel each
-    auto kind = [&](int p) { return jw(p) ? 2 : (Vs[p] >= kTridWide ? 1 : 0); };
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        return kind(a) != kind(b) ? kind(a) > kind(b) : Gs[a] > Gs[b];
-    });
+    // a job that fits one XCD (cus / 8 workgroups) takes blocks b = x (mod 8) of
+    // one XCD x
     const int per_xcd = std::max(1, di.cus / 8);
-    std::vector<std::vector<int>> launches;
-    {
-        // largest first, each into the first launch of its kind with room
-        std::vector<int> used;
-        for (int p : order) {
-            size_t l = 0;
-            while (l < launches.size() && (kind(launches[l][0]) != kind(p) || used[l] + Gs[p] > di.cus)) ++l;
-            if (l == launches.size()) {
-                launches.emplace_back();
-                used.push_back(0);
-            }
-            launches[l].push_back(p);
-            used[l] += Gs[p];
-        }
-    }
     const size_t lds_bytes = (size_t)di.lds;
     set_lds_limits(di);
     std::vector<BufferPtr> descs;

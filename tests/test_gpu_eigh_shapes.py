@@ -48,3 +48,10 @@ def test_jobs_spread_over_xcds_and_launches():
     get workgroups of several; thirteen more jobs take a second launch."""
     _check([400] * 12, 3, 5)
     _check([400] * 13 + [90], 2, 6)
+
+
+@pytest.mark.parametrize("sizes", [
+    [705, 704, 385, 384, 383, 65, 1], [1025, 257, 256, 192, 2], [1537, 703, 511, 64]])
+def test_jobs_of_all_sizes_in_one_launch(sizes):
+    """Orders of the 256-thread variants beside larger ones, all held by 512."""
+    _check(sizes, 4, 77 + sizes[0])
