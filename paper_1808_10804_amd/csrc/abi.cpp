@@ -32,8 +32,6 @@ void copy_prefix(const std::vector<CopyTask>& tasks, std::vector<int64_t>& prefi
 void copy_launch_dev(const CopyTask* d_tasks, const int64_t* d_prefix, int ntasks, int64_t npieces,
                      void* const* d_ptrs, bool src_f64, int dst_kind, hipStream_t s);
 int choose_tile_cfg(const ContractPlan& p);
-void launch_scale_cols(double* X, int ld, int rows, int cols, const double* s, double e, hipStream_t st);
-void launch_scale_rows(double* X, int ld, int rows, int cols, const double* s, double e, hipStream_t st);
 void launch_eig_to_svd(const double* Z, int NE, const double* w, int voff, int mn, int ru, int rd, bool jw,
                        double* S, double* U, double* V, hipStream_t st);
 // zero-padded batches of col-major blocks for the projector factorizations
@@ -445,22 +443,113 @@ struct ctm_env {
 // ============================================================ kernels used
 // by the projector stage (small, FP64)
 namespace symten {
-// X[:, j] *= s[j]^e  (col-major, ld)
-__global__ void scale_cols_kernel(double* __restrict__ X, int ld, int rows, int cols, const double* __restrict__ s,
-                                  double e) {
-    const int64_t tot = (int64_t)rows * cols;
+// One sector of the projector stage, for kernels that go over all sectors of a
+// move in one launch (grid.y).  A launch per sector and step, some 55 in a move
+// of seven sectors, cost its start each time: a full step at D = 4, chi = 16 in
+// FP64 5.47 -> 4.96 ms, a move at D = 6, chi = 64 3.96 -> 3.72 ms (FP32).
+struct SectorJob {
+    const float *hu, *hd;        // FP32 moves: sources of H_u^T (mu x n) and H_d^T (md x n)
+    double *HuT, *HdT, *Y;
+    int* flag;
+    const double* w;             // eigenvalues, ascending, ne of them
+    double* S;                   // mn singular values
+    int mu, md, n, ne, mn, jw;
+    int k;                       // kept
+    const double* Z;             // ne x k eigenvectors, column j for the j-th largest
+    double *U, *V, *P, *Pt;      // mu x k, md x k, n x k, k x n
+};
+__global__ void sector_cast_kernel(const SectorJob* __restrict__ jobs) {
+    const SectorJob J = jobs[blockIdx.y >> 1];
+    const bool d = blockIdx.y & 1;
+    const float* __restrict__ src = d ? J.hd : J.hu;
+    double* __restrict__ dst = d ? J.HdT : J.HuT;
+    const int64_t tot = (int64_t)(d ? J.md : J.mu) * J.n;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < tot; i += (int64_t)gridDim.x * blockDim.x)
+        dst[i] = (double)src[i];
+}
+// Non-finite entries of Y (NaN, Inf) are replaced by 0 and reported in
+// *flag, so that the eigensolver only ever sees finite matrices; the move
+// then fails after the read-back (SYMTEN_E_LINALG).
+__global__ void sector_guard_kernel(const SectorJob* __restrict__ jobs) {
+    const SectorJob J = jobs[blockIdx.y];
+    const int64_t tot = (int64_t)J.mu * J.md;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < tot; i += (int64_t)gridDim.x * blockDim.x) {
-        const int row = (int)(i % rows), col = (int)(i / rows);
-        X[row + (int64_t)col * ld] *= pow(s[col], e);
+        if (!isfinite(J.Y[i])) {
+            J.Y[i] = 0.0;
+            *J.flag = 1;
+        }
     }
 }
-// X[i, :] *= s[i]^e
-__global__ void scale_rows_kernel(double* __restrict__ X, int ld, int rows, int cols, const double* __restrict__ s,
-                                  double e) {
-    const int64_t tot = (int64_t)rows * cols;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < tot; i += (int64_t)gridDim.x * blockDim.x) {
-        const int row = (int)(i % rows), col = (int)(i / rows);
-        X[row + (int64_t)col * ld] *= pow(s[row], e);
+// Singular values from the eigenvalues of the Jordan-Wielandt (s = lambda) or
+// Gram (s = sqrt(lambda)) matrix: the mn largest, descending, negatives
+// (rounding) clamped to 0.
+__global__ void sector_values_kernel(const SectorJob* __restrict__ jobs) {
+    const SectorJob J = jobs[blockIdx.y];
+    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < J.mn; j += gridDim.x * blockDim.x) {
+        const double lam = fmax(J.w[J.ne - 1 - j], 0.0);
+        J.S[j] = J.jw ? lam : sqrt(lam);
+    }
+}
+// Left (and, Jordan-Wielandt, right) singular vectors of the kept values:
+// Jordan-Wielandt u = sqrt2 z[0:mu], v = sqrt2 z[mu:mu+md]; Gram u = z.
+__global__ void sector_vectors_kernel(const SectorJob* __restrict__ jobs) {
+    const SectorJob J = jobs[blockIdx.y];
+    const int j = blockIdx.x;
+    if (j >= J.k) return;
+    const double f = J.jw ? sqrt(2.0) : 1.0;
+    const double* __restrict__ z = J.Z + (int64_t)j * J.ne;
+    for (int r = threadIdx.x; r < J.mu; r += blockDim.x) J.U[r + (int64_t)j * J.mu] = f * z[r];
+    if (J.jw)
+        for (int r = threadIdx.x; r < J.md; r += blockDim.x) J.V[r + (int64_t)j * J.md] = f * z[J.mu + r];
+}
+// Gram route: V = Y^T U S^-1, the last factor.
+__global__ void sector_scale_v_kernel(const SectorJob* __restrict__ jobs) {
+    const SectorJob J = jobs[blockIdx.y];
+    const int j = blockIdx.x;
+    if (j >= J.k) return;
+    const double f = pow(J.S[j], -1.0);
+    for (int r = threadIdx.x; r < J.md; r += blockDim.x) J.V[r + (int64_t)j * J.md] *= f;
+}
+// Column j of P and row j of P~ times s_j^-1/2, and their sign: the largest
+// entry of the row of P~ positive (the first of equals).
+__global__ __launch_bounds__(256) void sector_finish_kernel(const SectorJob* __restrict__ jobs) {
+    const SectorJob J = jobs[blockIdx.y];
+    const int j = blockIdx.x, n = J.n;
+    if (j >= J.k) return;
+    const double f = pow(J.S[j], -0.5);
+    double* __restrict__ pt = J.Pt + j;
+    double* __restrict__ p = J.P + (int64_t)j * n;
+    double best = -1.0;
+    int bi = 0x7fffffff;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const double v = fabs(pt[(int64_t)i * J.k] * f);
+        if (v > best || (v == best && i < bi)) {
+            best = v;
+            bi = i;
+        }
+    }
+    __shared__ double sb[256];
+    __shared__ int si[256];
+    sb[threadIdx.x] = best;
+    si[threadIdx.x] = bi;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if (threadIdx.x < s) {
+            const double ob = sb[threadIdx.x + s];
+            const int oi = si[threadIdx.x + s];
+            if (ob > sb[threadIdx.x] || (ob == sb[threadIdx.x] && oi < si[threadIdx.x])) {
+                sb[threadIdx.x] = ob;
+                si[threadIdx.x] = oi;
+            }
+        }
+        __syncthreads();
+    }
+    const int arg = si[0];
+    const double g = arg < n && pt[(int64_t)arg * J.k] * f < 0.0 ? -f : f;
+    __syncthreads();   // the entry is read before it is scaled
+    for (int i = threadIdx.x; i < n; i += 256) {
+        pt[(int64_t)i * J.k] *= g;
+        p[i] *= g;
     }
 }
 // Largest mn eigenpairs (syevd returns ascending order, NE of them) as
@@ -479,27 +568,6 @@ __global__ void eig_to_svd_kernel(const double* __restrict__ Z, int NE, const do
     if (jw)
         for (int r = threadIdx.x; r < rd; r += blockDim.x)
             V[r + (int64_t)j * rd] = f * Z[voff + r + (int64_t)idx * NE];
-}
-// Singular values of a sector from the eigenvalues w (ascending, NE of
-// them) of its Jordan-Wielandt (s = lambda) or Gram (s = sqrt(lambda))
-// matrix: the mn largest, descending, negatives (rounding) clamped to 0.
-__global__ void eigval_to_s_kernel(const double* __restrict__ w, int NE, int mn, int jw, double* __restrict__ S) {
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < mn; j += gridDim.x * blockDim.x) {
-        const double lam = fmax(w[NE - 1 - j], 0.0);
-        S[j] = jw ? lam : sqrt(lam);
-    }
-}
-// Left (and, Jordan-Wielandt, right) singular vectors of the k largest values
-// from eigenvectors Zk (NE x k, column j for the j-th largest):
-// Jordan-Wielandt u = sqrt2 z[0:ru], v = sqrt2 z[ru:ru+rd]; Gram u = z.
-__global__ void vec_to_uv_kernel(const double* __restrict__ Zk, int NE, int k, int ru, int rd, int jw,
-                                 double* __restrict__ U, double* __restrict__ V) {
-    const int j = blockIdx.x;
-    if (j >= k) return;
-    const double f = jw ? sqrt(2.0) : 1.0;
-    for (int r = threadIdx.x; r < ru; r += blockDim.x) U[r + (int64_t)j * ru] = f * Zk[r + (int64_t)j * NE];
-    if (jw)
-        for (int r = threadIdx.x; r < rd; r += blockDim.x) V[r + (int64_t)j * rd] = f * Zk[ru + r + (int64_t)j * NE];
 }
 // Non-finite entries of X (NaN, Inf) are replaced by 0 and reported in
 // *flag, so that the eigensolver only ever sees finite matrices; the move
@@ -547,16 +615,6 @@ void launch_nonfinite_guard(double* X, int64_t n, int* flag, hipStream_t st) {
     hipLaunchKernelGGL(nonfinite_guard_kernel, dim3(g1d(n)), dim3(256), 0, st, X, n, flag);
     HIPCHK(hipGetLastError());
 }
-void launch_scale_cols(double* X, int ld, int rows, int cols, const double* sv, double e, hipStream_t st) {
-    if ((int64_t)rows * cols == 0) return;
-    hipLaunchKernelGGL(scale_cols_kernel, dim3(g1d((int64_t)rows * cols)), dim3(256), 0, st, X, ld, rows, cols, sv, e);
-    HIPCHK(hipGetLastError());
-}
-void launch_scale_rows(double* X, int ld, int rows, int cols, const double* sv, double e, hipStream_t st) {
-    if ((int64_t)rows * cols == 0) return;
-    hipLaunchKernelGGL(scale_rows_kernel, dim3(g1d((int64_t)rows * cols)), dim3(256), 0, st, X, ld, rows, cols, sv, e);
-    HIPCHK(hipGetLastError());
-}
 void launch_eig_to_svd(const double* Z, int NE, const double* w, int voff, int mn, int ru, int rd, bool jw,
                        double* S, double* U, double* V, hipStream_t st) {
     if (mn <= 0) return;
@@ -564,15 +622,10 @@ void launch_eig_to_svd(const double* Z, int NE, const double* w, int voff, int m
                        V);
     HIPCHK(hipGetLastError());
 }
-void launch_eigval_to_s(const double* w, int NE, int mn, bool jw, double* S, hipStream_t st) {
-    if (mn <= 0) return;
-    hipLaunchKernelGGL(eigval_to_s_kernel, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0, st, w, NE, mn,
-                       jw ? 1 : 0, S);
-    HIPCHK(hipGetLastError());
-}
-void launch_vec_to_uv(const double* Zk, int NE, int k, int ru, int rd, bool jw, double* U, double* V, hipStream_t st) {
-    if (k <= 0) return;
-    hipLaunchKernelGGL(vec_to_uv_kernel, dim3((unsigned)k), dim3(256), 0, st, Zk, NE, k, ru, rd, jw ? 1 : 0, U, V);
+// One launch over `count` sectors, `per` workgroups each.
+void launch_sectors(void (*kernel)(const SectorJob*), const SectorJob* jobs, size_t count, int64_t per, hipStream_t st) {
+    if (count == 0 || per <= 0) return;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)per, (unsigned)count), dim3(256), 0, st, jobs);
     HIPCHK(hipGetLastError());
 }
 void launch_pad_blocks(const PadArgs& a, double* dst, hipStream_t st) {
@@ -683,9 +736,10 @@ struct ProjOut {
 
 // Work buffers of one cut's eigensolves, enqueued but not yet read back.
 struct ProjWork {
-    int ru = 0, rd = 0, ld = 0;  // ld: of H_u^T, H_d^T
+    int ru = 0, rd = 0, ldu = 0, ldd = 0;  // leading dims of H_u^T, H_d^T
     int ldy = 0;                 // of Y
-    double *HuT = nullptr, *HdT = nullptr, *Y = nullptr;
+    const double *HuT = nullptr, *HdT = nullptr;
+    double* Y = nullptr;
     int* info = nullptr;         // rocSOLVER's status (vendor route only)
     int* nonfinite = nullptr;    // set when Y held NaN or Inf (zeroed before the solve)
     int prob = -1;               // own route: the sector's problem in the cut set's EighWork
@@ -765,7 +819,7 @@ void solve_class(const std::vector<CutSector>& secs, std::vector<ProjWork>& w, c
         x.HuT = (double*)Hb->ptr + 2 * i * N2;          // H_u^T, col-major m x n
         x.HdT = (double*)Hb->ptr + (2 * i + 1) * N2;    // H_d^T
         x.Y = (double*)Mb->ptr + i * N2;
-        x.ld = N;
+        x.ldu = x.ldd = N;
         x.ldy = N;
         x.info = (int*)ib->ptr + i;
         x.nonfinite = (int*)fb->ptr;
@@ -789,6 +843,9 @@ std::vector<ProjPending> issue_solves_own(ctm_env* env, const std::vector<std::v
     const double one = 1.0, zero = 0.0;
     std::vector<ProjPending> pend(cuts.size());
     std::vector<EighProblem> probs;
+    std::vector<SectorJob> jobs;
+    int64_t max_h = 0, max_y = 0;
+    int max_mn = 0;
     for (size_t c = 0; c < cuts.size(); ++c) {
         std::vector<CutSector>& secs = *cuts[c];
         if (secs.empty()) fail(SYMTEN_E_LINALG, "ctm_move: the halves have no common sector");
@@ -814,42 +871,49 @@ std::vector<ProjPending> issue_solves_own(ctm_env* env, const std::vector<std::v
             ProjWork& x = pc.w[i];
             x.ru = b.mu;
             x.rd = b.md;
-            const int N = std::max(b.n, std::max(b.mu, b.md));
-            const size_t N2 = (size_t)N * N;
-            BufferPtr Hb = device_alloc(8 * N2 * 2);
-            PadArgs pa{};
-            pa.count = 2;
-            pa.N = N;
-            pa.src_f64 = f64;
-            pa.src[0] = b.hu;
-            pa.rows[0] = b.mu;
-            pa.cols[0] = b.n;
-            pa.src[1] = b.hd;
-            pa.rows[1] = b.md;
-            pa.cols[1] = b.n;
-            launch_pad_blocks(pa, (double*)Hb->ptr, s);
-            x.HuT = (double*)Hb->ptr;
-            x.HdT = (double*)Hb->ptr + N2;
-            x.ld = N;
+            // FP64 halves are taken where they lie (the caller holds them until
+            // the projectors are formed)
+            x.ldu = std::max(1, b.mu);
+            x.ldd = std::max(1, b.md);
+            SectorJob j{};
+            if (f64) {
+                x.HuT = (const double*)b.hu;
+                x.HdT = (const double*)b.hd;
+            } else {
+                const size_t eu = ((size_t)b.mu * b.n + 1) & ~(size_t)1, ed = (size_t)b.md * b.n;
+                BufferPtr Hb = device_alloc(8 * std::max<size_t>(1, eu + ed));
+                j.hu = (const float*)b.hu;
+                j.hd = (const float*)b.hd;
+                j.HuT = (double*)Hb->ptr;
+                j.HdT = j.HuT + eu;
+                x.HuT = j.HuT;
+                x.HdT = j.HdT;
+                pc.keep_alive.push_back(Hb);
+            }
             BufferPtr Yb = device_alloc(8 * std::max<size_t>(1, (size_t)b.mu * b.md));
             x.Y = (double*)Yb->ptr;
             x.ldy = std::max(1, b.mu);
-            rb_check(rocblas_dgemm(env->rb, rocblas_operation_none, rocblas_operation_transpose, b.mu, b.md, b.n,
-                                   &one, x.HuT, N, x.HdT, N, &zero, x.Y, x.ldy),
-                     "rocblas_dgemm(Y)");
             x.nonfinite = head;
-            launch_nonfinite_guard(x.Y, (int64_t)b.mu * b.md, x.nonfinite, s);
             x.ne = f64 ? b.mu + b.md : b.mu;
             BufferPtr Ab;
-            if (!f64) {
-                Ab = device_alloc(8 * (size_t)x.ne * x.ne);
-                rb_check(rocblas_dgemm(env->rb, rocblas_operation_none, rocblas_operation_transpose, b.mu, b.mu, b.md,
-                                       &one, x.Y, x.ldy, x.Y, x.ldy, &zero, (double*)Ab->ptr, x.ne),
-                         "rocblas_dgemm(YY^T)");
-            }
+            if (!f64) Ab = device_alloc(8 * (size_t)x.ne * x.ne);
             x.w = area + pc.w_off[i];
             x.sdev = area + pc.s_off[i];
             x.prob = (int)probs.size();
+            j.Y = x.Y;
+            j.flag = x.nonfinite;
+            j.w = x.w;
+            j.S = x.sdev;
+            j.mu = b.mu;
+            j.md = b.md;
+            j.n = b.n;
+            j.ne = x.ne;
+            j.mn = b.mn;
+            j.jw = f64;
+            jobs.push_back(j);
+            max_h = std::max(max_h, (int64_t)std::max(b.mu, b.md) * b.n);
+            max_y = std::max(max_y, (int64_t)b.mu * b.md);
+            max_mn = std::max(max_mn, b.mn);
             EighProblem ep;
             ep.n = x.ne;
             ep.lda = f64 ? x.ldy : x.ne;
@@ -861,19 +925,34 @@ std::vector<ProjPending> issue_solves_own(ctm_env* env, const std::vector<std::v
             ep.w = x.w;
             ep.status = head + 1 + i;
             probs.push_back(ep);
-            for (auto& k : {Hb, Yb, Ab})
+            for (auto& k : {Yb, Ab})
                 if (k) pc.keep_alive.push_back(k);
         }
     }
-    auto wk = eigh_values(probs, s);
-    for (size_t c = 0; c < cuts.size(); ++c) {
-        pend[c].eig = wk;
-        std::vector<CutSector>& secs = *cuts[c];
-        for (size_t i = 0; i < secs.size(); ++i) {
-            ProjWork& x = pend[c].w[i];
-            launch_eigval_to_s(x.w, x.ne, secs[i].mn, f64, x.sdev, s);
+    Tables tab;
+    const size_t oj = tab.add(jobs);
+    tab.send(s);
+    const SectorJob* dj = tab.at<SectorJob>(oj);
+    if (!f64) launch_sectors(sector_cast_kernel, dj, 2 * jobs.size(), std::min<int64_t>((max_h + 1023) / 1024, 256), s);
+    for (size_t c = 0; c < cuts.size(); ++c)
+        for (size_t i = 0; i < cuts[c]->size(); ++i) {
+            const CutSector& b = (*cuts[c])[i];
+            const ProjWork& x = pend[c].w[i];
+            rb_check(rocblas_dgemm(env->rb, rocblas_operation_none, rocblas_operation_transpose, b.mu, b.md, b.n,
+                                   &one, x.HuT, x.ldu, x.HdT, x.ldd, &zero, x.Y, x.ldy),
+                     "rocblas_dgemm(Y)");
         }
-    }
+    launch_sectors(sector_guard_kernel, dj, jobs.size(), std::min<int64_t>((max_y + 1023) / 1024, 256), s);
+    if (!f64)
+        for (const EighProblem& ep : probs) {
+            const SectorJob& j = jobs[&ep - probs.data()];
+            rb_check(rocblas_dgemm(env->rb, rocblas_operation_none, rocblas_operation_transpose, j.mu, j.mu, j.md,
+                                   &one, j.Y, std::max(1, j.mu), j.Y, std::max(1, j.mu), &zero, (double*)ep.A, j.ne),
+                     "rocblas_dgemm(YY^T)");
+        }
+    auto wk = eigh_values(probs, s);
+    launch_sectors(sector_values_kernel, dj, jobs.size(), (max_mn + 255) / 256, s);
+    for (auto& p : pend) p.eig = wk;
     return pend;
 }
 
@@ -1087,6 +1166,7 @@ ProjOut finish_projectors(ctm_env* env, std::vector<CutSector>& secs, ProjPendin
     out.gap = nkeep < (int)all.size() ? (all[nkeep - 1].s - all[nkeep].s) / out.smax : INFINITY;
     for (int i = 0; i < nkeep; ++i) secs[all[i].sec].k += 1;
     // the kept set of a sector is a prefix of its descending list
+    std::vector<BufferPtr> zvec;
     if (pend.eig) {
         // own route: eigenvectors of the kept values only, then u (and v)
         std::vector<int> kv(eigh_problems(*pend.eig), 0);
@@ -1104,14 +1184,13 @@ ProjOut finish_projectors(ctm_env* env, std::vector<CutSector>& secs, ProjPendin
         }
         eigh_vectors(*pend.eig, kv, zs, wh, s);
         for (size_t i = 0; i < secs.size(); ++i) {
-            ProjWork& x = w[i];
             const int k = secs[i].k;
             if (k == 0) continue;
-            x.U = device_alloc(8 * (size_t)x.ru * k);
-            x.V = device_alloc(8 * (size_t)x.rd * k);
-            launch_vec_to_uv((const double*)zb[i]->ptr, x.ne, k, x.ru, x.rd, f64, (double*)x.U->ptr,
-                             (double*)x.V->ptr, s);
+            w[i].U = device_alloc(8 * (size_t)w[i].ru * k);
+            w[i].V = device_alloc(8 * (size_t)w[i].rd * k);
         }
+        // (zb: read on s before its blocks are given out again there)
+        for (size_t i = 0; i < secs.size(); ++i) zvec.push_back(zb[i]);
     }
     // ---- P = H_d V_k S^-1/2 (n x k), P~ = S^-1/2 U_k^T H_u^T (k x n) -------
     for (auto& c : secs) {
@@ -1121,34 +1200,64 @@ ProjOut finish_projectors(ctm_env* env, std::vector<CutSector>& secs, ProjPendin
     out.P = device_alloc(8 * std::max<int64_t>(out.ptot, 1));
     out.Pt = device_alloc(8 * std::max<int64_t>(out.ptot, 1));
     const double one = 1.0, zero = 0.0;
+    std::vector<SectorJob> jobs;
+    int kmax = 0;
     for (size_t i = 0; i < secs.size(); ++i) {
         const CutSector& c = secs[i];
         ProjWork& x = w[i];
         out.flops += 2LL * x.ru * x.rd * c.n;
         if (c.k == 0) continue;
-        const int n = c.n, k = c.k;
-        double* Pq = (double*)out.P->ptr + c.pbase;
-        double* Ptq = (double*)out.Pt->ptr + c.pbase;
-        if (!f64) {
+        kmax = std::max(kmax, c.k);
+        SectorJob j{};
+        j.S = (double*)x.s_ptr();
+        j.mu = x.ru;
+        j.md = x.rd;
+        j.n = c.n;
+        j.ne = x.ne;
+        j.jw = f64;
+        j.k = c.k;
+        j.Z = pend.eig ? (const double*)zvec[i]->ptr : nullptr;
+        j.U = (double*)x.U->ptr;
+        j.V = (double*)x.V->ptr;
+        j.P = (double*)out.P->ptr + c.pbase;
+        j.Pt = (double*)out.Pt->ptr + c.pbase;
+        jobs.push_back(j);
+    }
+    Tables tab;
+    const size_t oj = tab.add(jobs);
+    tab.send(s);
+    const SectorJob* dj = tab.at<SectorJob>(oj);
+    if (pend.eig) launch_sectors(sector_vectors_kernel, dj, jobs.size(), kmax, s);
+    if (!f64) {
+        for (size_t i = 0; i < secs.size(); ++i) {
+            ProjWork& x = w[i];
+            const int k = secs[i].k;
+            if (k == 0) continue;
             // Gram path: V_k = Y^T U_k S_k^-1  (rd x k, ld rd)
             rb_check(rocblas_dgemm(env->rb, rocblas_operation_transpose, rocblas_operation_none, x.rd, k, x.ru, &one,
                                    (const double*)x.Y, x.ldy, (const double*)x.U->ptr, x.ru, &zero, (double*)x.V->ptr,
                                    x.rd),
                      "rocblas_dgemm(V)");
-            launch_scale_cols((double*)x.V->ptr, x.rd, x.rd, k, x.s_ptr(), -1.0, s);
         }
+        launch_sectors(sector_scale_v_kernel, dj, jobs.size(), kmax, s);
+    }
+    for (size_t i = 0; i < secs.size(); ++i) {
+        const CutSector& c = secs[i];
+        ProjWork& x = w[i];
+        if (c.k == 0) continue;
+        const int n = c.n, k = c.k;
+        double* Pq = (double*)out.P->ptr + c.pbase;
+        double* Ptq = (double*)out.Pt->ptr + c.pbase;
         // P = H_d V_k S^-1/2  (n x k, ld n; H_d = (H_d^T)^T)
         rb_check(rocblas_dgemm(env->rb, rocblas_operation_transpose, rocblas_operation_none, n, k, x.rd, &one,
-                               (const double*)x.HdT, x.ld, (const double*)x.V->ptr, x.rd, &zero, Pq, n),
+                               x.HdT, x.ldd, (const double*)x.V->ptr, x.rd, &zero, Pq, n),
                  "rocblas_dgemm(P)");
-        launch_scale_cols(Pq, n, n, k, x.s_ptr(), -0.5, s);
         // P~ = S^-1/2 U_k^T H_u^T  (k x n, ld k)
         rb_check(rocblas_dgemm(env->rb, rocblas_operation_transpose, rocblas_operation_none, k, n, x.ru, &one,
-                               (const double*)x.U->ptr, x.ru, (const double*)x.HuT, x.ld, &zero, Ptq, k),
+                               (const double*)x.U->ptr, x.ru, x.HuT, x.ldu, &zero, Ptq, k),
                  "rocblas_dgemm(Pt)");
-        launch_scale_rows(Ptq, k, k, n, x.s_ptr(), -0.5, s);
-        launch_sign_fix_rows(Ptq, k, k, n, Pq, n, s);
     }
+    launch_sectors(sector_finish_kernel, dj, jobs.size(), kmax, s);
     // the work buffers go back to the pool here; later launches that reuse
     // them are ordered after these on the same stream
     return out;

@@ -282,7 +282,6 @@ struct DoubleLayerArgs {
 };
 void launch_double_layer(const DoubleLayerArgs& a, hipStream_t s);
 // scatter of a contiguous-block tensor into a dense array
-void launch_sign_fix_rows(double* Pt, int ldPt, int rows, int n, double* P, int ldP, hipStream_t s);
 // FP64 symmetric eigensolver of the projector stage (eig.hip).  Phase one
 // enqueues the tridiagonalisations and all eigenvalues (w, ascending);
 // phase two, once the caller has the eigenvalues on the host, the

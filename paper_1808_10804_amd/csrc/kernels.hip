@@ -1046,45 +1046,6 @@ __global__ void scale_inv_sqrt_kernel(T* __restrict__ x, int64_t n, const double
         x[i] = (T)((double)x[i] * f);
 }
 
-// Projector sign gauge: for each row j of P~ (col-major, ld ldPt, n cols)
-// find the largest |entry| (lowest column on ties); if it is negative, flip
-// row j of P~ and column j of P (col-major, ld ldP).
-__global__ __launch_bounds__(256) void sign_fix_kernel(double* __restrict__ Pt, int ldPt, int n,
-                                                       double* __restrict__ P, int ldP) {
-    const int j = blockIdx.x;
-    double best = -1.0;
-    int bi = 0x7fffffff;
-    for (int f = threadIdx.x; f < n; f += 256) {
-        const double v = fabs(Pt[j + (int64_t)f * ldPt]);
-        if (v > best || (v == best && f < bi)) { best = v; bi = f; }
-    }
-    __shared__ double sb[256];
-    __shared__ int si[256];
-    sb[threadIdx.x] = best;
-    si[threadIdx.x] = bi;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            const double ob = sb[threadIdx.x + s];
-            const int oi = si[threadIdx.x + s];
-            if (ob > sb[threadIdx.x] || (ob == sb[threadIdx.x] && oi < si[threadIdx.x])) {
-                sb[threadIdx.x] = ob;
-                si[threadIdx.x] = oi;
-            }
-        }
-        __syncthreads();
-    }
-    const int arg = si[0];
-    const bool flip = arg < n && Pt[j + (int64_t)arg * ldPt] < 0.0;
-    __syncthreads();
-    if (flip) {
-        for (int f = threadIdx.x; f < n; f += 256) {
-            Pt[j + (int64_t)f * ldPt] = -Pt[j + (int64_t)f * ldPt];
-            P[(int64_t)j * ldP + f] = -P[(int64_t)j * ldP + f];
-        }
-    }
-}
-
 // Double layer: thread per output element.  Output blocks are contiguous
 // row-major in canonical order; per leg a fused state maps to (ket, bra)
 // states of the virtual leg.
@@ -1183,12 +1144,6 @@ void launch_scale_by_inv_sqrt(void* x, bool f64, int64_t n, const double* sumsq,
         hipLaunchKernelGGL(scale_inv_sqrt_kernel<double>, dim3(g), dim3(256), 0, s, (double*)x, n, sumsq);
     else
         hipLaunchKernelGGL(scale_inv_sqrt_kernel<float>, dim3(g), dim3(256), 0, s, (float*)x, n, sumsq);
-    HIPCHK(hipGetLastError());
-}
-
-void launch_sign_fix_rows(double* Pt, int ldPt, int rows, int n, double* P, int ldP, hipStream_t s) {
-    if (rows <= 0 || n <= 0) return;
-    hipLaunchKernelGGL(sign_fix_kernel, dim3(rows), dim3(256), 0, s, Pt, ldPt, n, P, ldP);
     HIPCHK(hipGetLastError());
 }
 
