@@ -1572,20 +1572,23 @@ struct BackJob {
 // Step 4.  NW waves per eigenvector (bmap[b] = (job, vector)), which stays in
 // registers: lane entries i = tid + 64 NW q, q < SL.  The reflectors are read
 // straight from memory (L2: all vectors go through them at about the same
-// time) kBackAhead of them ahead; each costs one dot product, one wavefront
-// sum and one update, so the dependent chain of the sum bounds it (0.1 us per
-// reflector at n = 696 with one wave, against 0.6 us with the vector in LDS
-// under eight waves and a workgroup barrier per reflector).  One wave while a
-// vector's entries and the reflectors ahead fit its registers; beyond that
-// four waves, whose partial sums meet in LDS.
-constexpr int kBackAhead = 4;
+// time), kBackAhead of them ahead; each costs one dot product, one wavefront
+// sum and one update, so the dependent chain of the sum bounds it: 0.3 us per
+// reflector at n = 696 with one wave.  The loads are global ones without
+// conditions, at most 63 in flight where the registers allow it (flat loads
+// under a test per slot were each waited for with all the others: the vectors
+// of a move at D = 6, chi = 64 292 us, now 213 us; D = 8, chi = 200 2.24 and
+// 2.16 ms).  One wave while a vector's entries and the reflectors ahead fit its
+// registers; beyond that four waves, whose partial sums meet in LDS.
 template <int NW, int SL>
-__global__ __launch_bounds__(64 * NW) void backtr_kernel(const BackJob* __restrict__ jobs,
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1))) void backtr_kernel(const BackJob* __restrict__ jobs,
                                                           const int2* __restrict__ bmap) {
     const int2 bm = bmap[blockIdx.x];
     const BackJob J = jobs[bm.x];
-    const int n = J.n, ldv = v_stride(n), tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = J.n, ldv = v_stride(n), tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     __shared__ double red[2][NW];
+    constexpr int kBackAhead = SL <= 4 ? 12 : (SL <= 8 ? 7 : (NW > 1 ? 8 : 5));
     double z[SL], v[kBackAhead][SL], tj[kBackAhead];
     const double* zt = J.Zt + (size_t)bm.y * J.ldt;
 #pragma unroll
@@ -1593,14 +1596,20 @@ __global__ __launch_bounds__(64 * NW) void backtr_kernel(const BackJob* __restri
         const int i = tid + 64 * NW * q;
         z[q] = i < n ? zt[J.row_of(i)] : 0.0;
     }
-    auto load = [&](int j, double (&vj)[SL], double& t) {
-        const double* row = J.V + (size_t)max(j, 0) * ldv;
-        t = j >= 0 ? J.tau[j] : 0.0;
+    // slots past the reflector's end read its last entries and leave z at 0
+    uint32_t off[SL];
+    double keep[SL];
 #pragma unroll
-        for (int q = 0; q < SL; ++q) {
-            const int i = tid + 64 * NW * q;
-            vj[q] = i < ldv ? row[i] : 0.0;
-        }
+    for (int q = 0; q < SL; ++q) {
+        const int first = 64 * (wave + NW * q);
+        off[q] = min(first, ldv - 64) + lane;
+        keep[q] = first < ldv ? 1.0 : 0.0;
+    }
+    auto load = [&](int j, double (&vj)[SL], double& t) {
+        const gf64* row = (const gf64*)J.V + (size_t)max(j, 0) * ldv;
+        t = ((cf64*)J.tau)[max(j, 0)];
+#pragma unroll
+        for (int q = 0; q < SL; ++q) vj[q] = *at8(row, off[q]);
     };
 #pragma unroll
     for (int u = 0; u < kBackAhead; ++u) load(J.count - 1 - u, v[u], tj[u]);
@@ -1623,9 +1632,9 @@ __global__ __launch_bounds__(64 * NW) void backtr_kernel(const BackJob* __restri
                 for (int q = 0; q < NW; ++q) part += red[par][q];
                 par ^= 1;
             }
-            const double f = part * tj[u];
+            const double f = j0 >= u ? part * tj[u] : 0.0;
 #pragma unroll
-            for (int q = 0; q < SL; ++q) z[q] -= f * v[u][q];
+            for (int q = 0; q < SL; ++q) z[q] = fma(-(f * keep[q]), v[u][q], z[q]);
             load(j0 - u - kBackAhead, v[u], tj[u]);
         }
     }
