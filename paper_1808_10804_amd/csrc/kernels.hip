@@ -110,9 +110,9 @@ __device__ __forceinline__ void copy_store(void* dstv, int64_t dofs, int64_t lo_
 // several equally strided sources with their scalars (SU(2) tree-sibling
 // blocks).
 // What bounds it: small launches the chain of dependent loads before the first
-// element (the task search, then the task: bisecting the prefix sums lane 0's
-// way took a load per level, x a at D = 5, chi = 53 16.7 us; now 64 candidates
-// per load and the task's fields in one round, 7.7 us), large ones the index
+// element (the task search, then the task: a bisection of the prefix sums is a
+// load per level, x a at D = 5, chi = 53 16.7 us; with 64 candidates per load
+// and the task's fields in one round 7.7 us), large ones the index
 // arithmetic per element.  So a thread takes runs of four along a dim other
 // than the destination's unit-stride one and computes one index for them
 // (T a and the other gathers of a move at D = 8, chi = 200, f32, 2.6 GB:
