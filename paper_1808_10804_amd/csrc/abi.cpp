@@ -1341,15 +1341,13 @@ TensorPtr fusion_isometry(const Leg& la, const Leg& lb, int fdir, int dtype, hip
             for (int y = 0; y < nb; ++y)
                 host[b.offset + x * b.stride[0] + y * b.stride[1] + (int64_t)(b0 + x * nb + y) * b.stride[2]] = w;
     }
-    const size_t es = F->esize();
-    F->buf = device_alloc(std::max<int64_t>(F->elems, 1) * es);
-    F->meta_only = false;
     if (dtype == SYMTEN_F64) {
-        HIPCHK(hipMemcpy(F->buf->ptr, host.data(), F->elems * 8, hipMemcpyHostToDevice));
+        upload_sync(F->buf, host.data(), host.size() * 8);
     } else {
-        std::vector<float> h32(host.begin(), host.end());
-        HIPCHK(hipMemcpy(F->buf->ptr, h32.data(), F->elems * 4, hipMemcpyHostToDevice));
+        const std::vector<float> h32(host.begin(), host.end());
+        upload_sync(F->buf, h32.data(), h32.size() * 4);
     }
+    F->meta_only = false;
     (void)s;
     cache[key.str()] = F;
     return F;

@@ -784,14 +784,13 @@ TensorPtr double_layer_su2_impl(const Tensor& A, const double* op, bool project,
                 host[wb.offset + (int64_t)row_in_sector[r] * wb.stride[0] + (int64_t)col * wb.stride[1]] = val;
             }
         }
-        w->buf = device_alloc(std::max<int64_t>(w->elems, 1) * w->esize());
-        w->meta_only = false;
         if (f64) {
-            HIPCHK(hipMemcpy(w->buf->ptr, host.data(), w->elems * 8, hipMemcpyHostToDevice));
+            upload_sync(w->buf, host.data(), host.size() * 8);
         } else {
-            std::vector<float> h32(host.begin(), host.end());
-            HIPCHK(hipMemcpy(w->buf->ptr, h32.data(), w->elems * 4, hipMemcpyHostToDevice));
+            const std::vector<float> h32(host.begin(), host.end());
+            upload_sync(w->buf, h32.data(), h32.size() * 4);
         }
+        w->meta_only = false;
         W[x] = w;
     }
     // change of basis on the four legs (each contraction rotates the leg order)

@@ -1,0 +1,217 @@
+// A HIP runtime without a GPU for host checks of the library's stream order:
+// preloaded, it takes the place of the calls that libsymten makes.  Device
+// memory is host memory, kernels do nothing, and work queued on a stream stays
+// queued until something waits for it, so that whatever the library leaves
+// unordered is run in the worst order.
+//   - a copy from pinned memory reads its source when it runs, one from other
+//     host memory when it is queued;
+//   - hipMemcpy runs at once, beside the streams' queues (non-blocking streams).
+//     One into memory that a kernel launched since its hipMalloc may use, while
+//     work is queued, counts in fake_hazards();
+//   - a stream that is being captured runs nothing, cannot be waited for, and
+//     an event recorded on it cannot be waited for either;
+//   - a destroyed stream is no longer accepted, its queued work may still run.
+#include <hip/hip_runtime.h>
+#include <rocblas/rocblas.h>
+#include <rocsolver/rocsolver.h>
+
+#include <cstdint>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <memory>
+#include <vector>
+
+#include "internal.hpp"
+
+namespace {
+struct Stream {
+    std::vector<std::function<void()>> ops;
+    size_t done = 0;
+    bool alive = true, capturing = false;
+    void run(size_t upto) {
+        while (done < upto) ops[done++]();   // (an op may run parts of other streams)
+    }
+    void run() { run(ops.size()); }
+    bool idle() const { return done == ops.size(); }
+};
+struct Event {
+    Stream* s = nullptr;
+    size_t upto = 0;
+    bool captured = false;
+};
+struct Range {
+    size_t bytes;
+    uint64_t born;   // launches before it was allocated
+};
+Stream null_stream;
+std::vector<Stream*> streams{&null_stream};
+std::map<char*, Range> device, pinned;
+uint64_t launches = 0;
+int hazards = 0, device_syncs = 0;
+struct {
+    dim3 grid, block;
+    size_t shared;
+    hipStream_t stream;
+} config;
+
+Stream* S(hipStream_t s) { return s ? (Stream*)s : &null_stream; }
+bool inside(const std::map<char*, Range>& m, const void* p, Range* r = nullptr) {
+    auto it = m.upper_bound((char*)p);
+    if (it == m.begin()) return false;
+    --it;
+    if ((char*)p >= it->first + it->second.bytes) return false;
+    if (r) *r = it->second;
+    return true;
+}
+bool any_queued() {
+    for (Stream* s : streams)
+        if (!s->idle()) return true;
+    return false;
+}
+bool any_capture() {
+    for (Stream* s : streams)
+        if (s->capturing) return true;
+    return false;
+}
+hipError_t alloc(std::map<char*, Range>& m, void** p, size_t n) {
+    *p = std::calloc(1, n ? n : 1);
+    m[(char*)*p] = Range{n, launches};
+    return hipSuccess;
+}
+hipError_t drop(std::map<char*, Range>& m, void* p) {
+    m.erase((char*)p);
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t queue(hipStream_t s, std::function<void()> f) {
+    if (!S(s)->alive) return hipErrorContextIsDestroyed;
+    if (!S(s)->capturing) S(s)->ops.push_back(std::move(f));
+    return hipSuccess;
+}
+}  // namespace
+
+extern "C" {
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned);
+
+// ------------------------------------------------------------- for the tests
+int fake_hazards() { return hazards; }
+void* fake_stream() {
+    hipStream_t s;
+    (void)hipStreamCreateWithFlags(&s, 0);
+    return s;
+}
+
+// ------------------------------------------------------------------ runtime
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+    *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : a == hipDeviceAttributeMaxSharedMemoryPerBlock ? 160 * 1024 : 0;
+    return hipSuccess;
+}
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 1; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void*) {
+    static char symbol[1 << 20];
+    *p = symbol;
+    return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t n) { return alloc(device, p, n); }
+hipError_t hipFree(void* p) { return drop(device, p); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return alloc(pinned, p, n); }
+hipError_t hipHostFree(void* p) { return drop(pinned, p); }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+    Range r;
+    if (inside(device, d, &r) && launches > r.born && any_queued()) ++hazards;
+    std::memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
+    if (inside(pinned, s) || inside(device, s)) return queue(st, [=] { std::memcpy(d, s, n); });
+    auto copy = std::make_shared<std::vector<char>>((const char*)s, (const char*)s + n);
+    return queue(st, [=] { std::memcpy(d, copy->data(), n); });
+}
+hipError_t hipDeviceSynchronize() {
+    if (any_capture()) return hipErrorStreamCaptureUnsupported;
+    ++device_syncs;
+    for (size_t i = 0; i < streams.size(); ++i) streams[i]->run();
+    return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+    streams.push_back(new Stream);
+    *s = (hipStream_t)streams.back();
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t s) { S(s)->alive = false; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    if (!S(s)->alive) return hipErrorContextIsDestroyed;
+    if (S(s)->capturing) return hipErrorStreamCaptureUnsupported;
+    S(s)->run();
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+    if (!S(s)->alive) return hipErrorContextIsDestroyed;
+    *st = S(s)->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) { S(s)->capturing = true; return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t s, hipGraph_t* g) { S(s)->capturing = false; *g = nullptr; return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+    const Event ev = *(Event*)e;
+    if (ev.captured != S(s)->capturing) return hipErrorStreamCaptureIsolation;
+    return queue(s, [ev] { if (ev.s) ev.s->run(ev.upto); });
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t) new Event; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
+hipError_t hipEventDestroy(hipEvent_t e) { delete (Event*)e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    if (!S(s)->alive) return hipErrorContextIsDestroyed;
+    *(Event*)e = Event{S(s), S(s)->ops.size(), S(s)->capturing};
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) {
+    Event* ev = (Event*)e;
+    if (ev->captured) return hipErrorCapturedEvent;
+    if (ev->s) ev->s->run(ev->upto);
+    return hipSuccess;
+}
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t shared, hipStream_t s) {
+    config = {g, b, shared, s};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* shared, hipStream_t* s) {
+    *g = config.grid;
+    *b = config.block;
+    *shared = config.shared;
+    *s = config.stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t s) {
+    ++launches;
+    return queue(s, [] {});
+}
+hipError_t hipLaunchCooperativeKernel(const void*, dim3, dim3, void**, unsigned, hipStream_t s) {
+    ++launches;
+    return queue(s, [] {});
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) { *e = nullptr; return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+
+// ----------------------------------------------------------- rocBLAS, -SOLVER
+rocblas_status rocblas_create_handle(rocblas_handle* h) { *h = (rocblas_handle) new hipStream_t(nullptr); return rocblas_status_success; }
+rocblas_status rocblas_destroy_handle(rocblas_handle h) { delete (hipStream_t*)h; return rocblas_status_success; }
+rocblas_status rocblas_set_stream(rocblas_handle h, hipStream_t s) { *(hipStream_t*)h = s; return rocblas_status_success; }
+rocblas_status rocblas_dgemm(rocblas_handle h, rocblas_operation, rocblas_operation, rocblas_int, rocblas_int, rocblas_int,
+                             const double*, const double*, rocblas_int, const double*, rocblas_int, const double*, double*,
+                             rocblas_int) {
+    ++launches;
+    (void)queue(*(hipStream_t*)h, [] {});
+    return rocblas_status_success;
+}
+}
