@@ -433,7 +433,10 @@ struct ctm_env {
         for (int i = 0; i < kAux; ++i) {
             if (rb_aux[i]) rocblas_destroy_handle(rb_aux[i]);
             if (ev_done[i]) (void)hipEventDestroy(ev_done[i]);
-            if (aux[i]) (void)hipStreamDestroy(aux[i]);
+            if (aux[i]) {
+                if (hipStreamSynchronize(aux[i]) == hipSuccess) retire_idle_stream(aux[i]);
+                (void)hipStreamDestroy(aux[i]);
+            }
         }
         if (ev_start) (void)hipEventDestroy(ev_start);
         if (pinned) (void)hipHostFree(pinned);
@@ -977,6 +980,7 @@ std::vector<ProjPending> issue_solves(ctm_env* env, const std::vector<std::vecto
     if (own_solver_fits(cuts, f64)) return issue_solves_own(env, cuts, f64, s);
     const hipEvent_t start = env->ev_start;
     HIPCHK(hipEventRecord(start, s));
+    mark_releases(s);   // the side streams' blocks come from s: they are not to wait for its eigensolves
     rb_check(rocblas_set_stream(env->rb, s), "rocblas_set_stream");
     constexpr int kSlots = ctm_env::kAux + 1;
     struct SolveClass {

@@ -68,10 +68,17 @@ hipStream_t call_stream();
 // belongs to the stream that released it: the stream of the call running on
 // the releasing thread, else the stream the block was allocated on.  Handing
 // the block to a call on another stream makes that stream wait for the first
-// one, so work queued on two streams never shares a block.
+// one's work before the release (and for what few calls queued after it), so
+// work queued on two streams never shares a block.
 struct DeviceBuffer;
 using BufferPtr = std::shared_ptr<DeviceBuffer>;
 BufferPtr device_alloc(size_t bytes);
+// Blocks released on s so far: other streams wait for no more than the work
+// queued on s by now.  Called where work is about to be spread over streams.
+void mark_releases(hipStream_t s);
+// Blocks released on s are free for any stream (s has been synchronised and
+// is about to be destroyed).
+void retire_idle_stream(hipStream_t s);
 struct DeviceBuffer {
     void* ptr = nullptr;
     size_t bytes = 0;

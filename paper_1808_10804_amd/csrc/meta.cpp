@@ -9,7 +9,9 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <deque>
 #include <functional>
+#include <map>
 #include <mutex>
 #include <numeric>
 #include <set>
@@ -66,45 +68,107 @@ bool call_stream_set() { return tl_stream_set; }
 hipStream_t call_stream() { return tl_stream; }
 
 namespace {
-// Released blocks carry the stream that released them and no event: a call on
-// the same stream is ordered after their last users by the queue itself.  A
-// call on another stream records the event then (order_after), which covers
-// at least the work up to the release.  An event at every release cost 4 us of
-// the host and 6 us of the queue each (its barrier packet), three of them per
-// contraction and about 90 per move: 22.9 us for a kernel and three events
-// against 3.4 us for the kernel alone.
-// (A stream destroyed in between is idle: hipStreamDestroy returned after the
-// 71 ms of products queued on it, also where its handle is given out again.)
+// Released blocks carry the stream that released them and no event of their
+// own: a call on the same stream is ordered after their last users by the queue
+// itself.  (An event at every release cost 4 us of the host and 6 us of the
+// queue each, its barrier packet, three of them per contraction and about 90
+// per move: 22.9 us for a kernel and three events against 3.4 us for the kernel
+// alone.)  Every kMarkEvery releases of a stream an event marks how far it has
+// come (at 64 a corner of nine releases at D = 6, chi = 64 took 69.5 us instead
+// of 68.3 us); a call on another stream waits for the first mark behind the
+// block's release, and only where there is none yet for all that is queued by
+// then.
+// (A stream whose handle is given out again counts as the same stream: its
+// predecessor's work has ended, hipStreamDestroy returned after the 71 ms of
+// products queued on it.)
+constexpr uint64_t kMarkEvery = 256;
+constexpr size_t kMarks = 8;   // kept per stream; releases before them wait for the oldest
 struct FreeBlock {
     void* ptr;
     hipStream_t stream;   // stream that released it
+    uint64_t seq;         // its number among that stream's releases; 0: no queued work uses the block
+};
+struct StreamReleases {
+    uint64_t count = 0;
+    std::deque<std::pair<uint64_t, hipEvent_t>> marks;   // (releases before it, event), ascending
 };
 struct Pool {
     std::mutex mu;
     std::multimap<size_t, FreeBlock> free_;   // capacity -> block
+    std::map<hipStream_t, StreamReleases> streams;
     size_t held = 0;
 };
-// Stream `cur` waits for the work queued on `from`; false where it cannot be
-// waited for (either of the two is being captured into a graph).
-bool order_after(hipStream_t cur, hipStream_t from) {
+enum class Order { Done, Refused, Gone };
+// An event behind everything released on stream s so far.  Refused while the
+// stream (or, for the null stream, any other) is being captured into a graph.
+Order mark_stream(StreamReleases& r, hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (const hipError_t e = hipStreamIsCapturing(s, &st); e != hipSuccess) {
+        (void)hipGetLastError();
+        return e == hipErrorStreamCaptureImplicit ? Order::Refused : Order::Gone;
+    }
+    if (st != hipStreamCaptureStatusNone) return Order::Refused;
+    hipEvent_t ev = nullptr;
+    if (r.marks.size() >= kMarks) {
+        ev = r.marks.front().second;
+        r.marks.pop_front();
+    } else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        return Order::Refused;
+    }
+    if (hipEventRecord(ev, s) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipEventDestroy(ev);
+        return Order::Refused;
+    }
+    r.marks.emplace_back(r.count, ev);
+    return Order::Done;
+}
+// Stream cur waits for the work queued on the block's stream before its release.
+Order order_after(Pool& P, hipStream_t cur, const FreeBlock& fb) {   // under P.mu
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     // a captured call may not wait for work outside of its graph
-    if (hipStreamIsCapturing(cur, &st) == hipSuccess && st != hipStreamCaptureStatusNone) return false;
-    (void)hipGetLastError();
-    if (const hipError_t e = hipStreamIsCapturing(from, &st); e != hipSuccess) {
+    if (hipStreamIsCapturing(cur, &st) != hipSuccess) (void)hipGetLastError();
+    else if (st != hipStreamCaptureStatusNone) return Order::Refused;
+    StreamReleases& r = P.streams[fb.stream];
+    if (r.marks.empty() || r.marks.back().first < fb.seq)
+        if (const Order o = mark_stream(r, fb.stream); o != Order::Done) return o;
+    auto m = r.marks.begin();
+    while (m->first < fb.seq) ++m;
+    if (hipStreamWaitEvent(cur, m->second, 0) != hipSuccess) {
         (void)hipGetLastError();
-        if (e == hipErrorStreamCaptureImplicit) return false;   // the null stream while another one is captured
-        HIPCHK(hipDeviceSynchronize());                         // the stream no longer exists
-        return true;
+        return Order::Refused;
     }
-    if (st != hipStreamCaptureStatusNone) return false;
-    hipEvent_t ev = nullptr;
-    HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-    hipError_t e = hipEventRecord(ev, from);
-    if (e == hipSuccess) e = hipStreamWaitEvent(cur, ev, 0);
-    (void)hipEventDestroy(ev);   // released once it has completed
-    HIPCHK(e);
-    return true;
+    return Order::Done;
+}
+void forget_marks(Pool& P, hipStream_t s) {   // under P.mu
+    auto r = P.streams.find(s);
+    if (r == P.streams.end()) return;
+    for (auto& m : r->second.marks) (void)hipEventDestroy(m.second);
+    P.streams.erase(r);
+}
+// The blocks of a stream that no longer exists become free for any stream, once
+// the device has been waited for (not under the pool's lock, and once for all of
+// them); while a capture forbids that, they stay as they are.
+bool retire_stream(Pool& P, hipStream_t s, std::unique_lock<std::mutex>& lk) {
+    std::vector<std::pair<size_t, FreeBlock>> mine;
+    for (auto it = P.free_.begin(); it != P.free_.end();) {
+        if (it->second.seq != 0 && it->second.stream == s) {
+            mine.emplace_back(*it);
+            it = P.free_.erase(it);
+        } else {
+            ++it;
+        }
+    }
+    lk.unlock();
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
+    if (!idle) (void)hipGetLastError();
+    lk.lock();
+    for (auto& b : mine) {
+        if (idle) b.second.seq = 0;
+        P.free_.emplace(b);
+    }
+    return idle;
 }
 Pool& pool() {
     static Pool* p = new Pool();   // leaked on purpose: buffers may outlive statics
@@ -173,23 +237,31 @@ BufferPtr device_alloc(size_t bytes) {
     b->stream = cur;
     {
         Pool& P = pool();
-        std::lock_guard<std::mutex> lk(P.mu);
-        // a block of this stream if there is one, else one of another stream
-        auto it = P.free_.end(), other = P.free_.end();
-        for (auto k = P.free_.lower_bound(cap); k != P.free_.end() && k->first <= cap * 2; ++k) {
-            if (k->second.stream == cur) {
-                it = k;
-                break;
+        std::unique_lock<std::mutex> lk(P.mu);
+        for (bool again = true; again;) {
+            again = false;
+            // an idle block or one of this stream if there is one, else one of another stream
+            auto it = P.free_.end(), other = P.free_.end();
+            for (auto k = P.free_.lower_bound(cap); k != P.free_.end() && k->first <= cap * 2; ++k) {
+                if (k->second.seq == 0 || k->second.stream == cur) {
+                    it = k;
+                    break;
+                }
+                if (other == P.free_.end()) other = k;
             }
-            if (other == P.free_.end()) other = k;
-        }
-        if (it == P.free_.end() && other != P.free_.end() && order_after(cur, other->second.stream)) it = other;
-        if (it != P.free_.end()) {
-            b->ptr = it->second.ptr;
-            b->cap = it->first;
-            P.free_.erase(it);
-            P.held -= b->cap;
-            return b;
+            if (it == P.free_.end() && other != P.free_.end()) {
+                const Order o = order_after(P, cur, other->second);
+                if (o == Order::Done) it = other;
+                else if (o == Order::Gone) again = retire_stream(P, other->second.stream, lk);
+            }
+            if (it != P.free_.end()) {
+                b->ptr = it->second.ptr;
+                b->cap = it->first;
+                b->used = it->second.seq != 0;
+                P.free_.erase(it);
+                P.held -= b->cap;
+                return b;
+            }
         }
     }
     void* p = nullptr;
@@ -232,8 +304,26 @@ DeviceBuffer::~DeviceBuffer() {
     const hipStream_t rs = call_stream_set() ? call_stream() : stream;
     Pool& P = pool();
     std::lock_guard<std::mutex> lk(P.mu);
-    P.free_.emplace(cap, FreeBlock{ptr, rs});
+    StreamReleases& r = P.streams[rs];
+    P.free_.emplace(cap, FreeBlock{ptr, rs, ++r.count});
     P.held += cap;
+    if (r.count % kMarkEvery == 0) (void)mark_stream(r, rs);
+}
+
+void mark_releases(hipStream_t s) {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lk(P.mu);
+    auto r = P.streams.find(s);
+    if (r != P.streams.end() && (r->second.marks.empty() || r->second.marks.back().first < r->second.count))
+        (void)mark_stream(r->second, s);
+}
+
+void retire_idle_stream(hipStream_t s) {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lk(P.mu);
+    for (auto& b : P.free_)
+        if (b.second.stream == s) b.second.seq = 0;
+    forget_marks(P, s);
 }
 
 // ------------------------------------------------------------------ tensors

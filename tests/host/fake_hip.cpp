@@ -215,3 +215,78 @@ rocblas_status rocblas_dgemm(rocblas_handle h, rocblas_operation, rocblas_operat
     return rocblas_status_success;
 }
 }
+
+namespace {
+struct Scope : symten::StreamScope {
+    explicit Scope(Stream* s) : StreamScope((hipStream_t)s) {}
+};
+Stream* new_stream() { return (Stream*)fake_stream(); }
+void* take_and_release(Stream* s, size_t bytes) {
+    Scope scope(s);
+    return symten::device_alloc(bytes)->ptr;
+}
+}  // namespace
+
+// ---------------------------------------------------------------- scenarios
+// (0: holds, else the number of the check that failed)
+extern "C" {
+// A block released on one stream and taken by another: the second waits for
+// what was queued before the release, not for what comes long after it.
+int pool_waits_for_the_release() {
+    Stream *a = new_stream(), *b = new_stream();
+    bool before = false, after = false;
+    a->ops.push_back([&] { before = true; });
+    void* x = take_and_release(a, 1 << 20);
+    for (int i = 0; i < 600; ++i) take_and_release(a, 4096);
+    a->ops.push_back([&] { after = true; });
+    void* y = take_and_release(b, 1 << 20);
+    b->run();
+    const bool late = after;
+    a->run();
+    return x != y ? 1 : !before ? 2 : late ? 3 : 0;
+}
+// The same where work is about to be spread over streams.
+int pool_waits_for_the_mark() {
+    Stream *a = new_stream(), *b = new_stream();
+    bool after = false;
+    void* x = take_and_release(a, 1 << 20);
+    symten::mark_releases((hipStream_t)a);
+    a->ops.push_back([&] { after = true; });
+    void* y = take_and_release(b, 1 << 20);
+    b->run();
+    const bool late = after;
+    a->run();
+    return x != y ? 1 : late ? 2 : 0;
+}
+// Blocks of a destroyed stream: the device is waited for once, and not at all
+// while another stream is being captured (they are left alone then).
+int pool_outlives_its_streams() {
+    Stream *d = new_stream(), *b = new_stream(), *c = new_stream();
+    bool before = false;
+    std::vector<symten::BufferPtr> keep;
+    std::vector<void*> old;
+    {
+        Scope scope(d);
+        for (int i = 0; i < 4; ++i) keep.push_back(symten::device_alloc(1 << 20));
+        for (auto& k : keep) old.push_back(k->ptr);
+        d->ops.push_back([&] { before = true; });
+        keep.clear();
+    }
+    d->alive = false;
+    auto is_old = [&](void* p) { return p == old[0] || p == old[1] || p == old[2] || p == old[3]; };
+    Scope scope(b);
+    c->capturing = true;
+    try {
+        keep.push_back(symten::device_alloc(1 << 20));
+    } catch (...) {
+        return 1;
+    }
+    if (is_old(keep[0]->ptr)) return 2;
+    c->capturing = false;
+    const int syncs = device_syncs;
+    for (int i = 0; i < 4; ++i) keep.push_back(symten::device_alloc(1 << 20));
+    for (int i = 1; i < 5; ++i)
+        if (!is_old(keep[i]->ptr)) return 3;
+    return !before ? 4 : device_syncs != syncs + 1 ? 5 : 0;
+}
+}

@@ -47,7 +47,13 @@ def su2_move():
 
 
 if __name__ == "__main__":
-    globals()[sys.argv[1]]()
+    scenario = globals().get(sys.argv[1])
+    if scenario:
+        scenario()
+    else:
+        check = getattr(fake, sys.argv[1])()   # those of fake_hip.cpp
+        if check:
+            sys.exit(f"{sys.argv[1]}: check {check} failed")
     n = fake.fake_hazards()
     if n:
         sys.exit(f"{sys.argv[1]}: {n} copies into memory that queued work may use")

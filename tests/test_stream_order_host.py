@@ -26,7 +26,8 @@ def runtime(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["su2_double_layer", "su2_move"])
+@pytest.mark.parametrize("scenario", [
+    "su2_double_layer", "su2_move", "pool_waits_for_the_release", "pool_waits_for_the_mark", "pool_outlives_its_streams"])
 def test_stream_order(runtime, scenario):
     env = dict(os.environ, SYMTEN_AUTOTUNE="0", PYTHONPATH=ROOT)
     env["LD_PRELOAD"] = " ".join(p for p in (runtime, env.get("LD_PRELOAD", "")) if p)
