@@ -966,61 +966,74 @@ namespace {
 // Descriptors go to the device through a ring of pinned host memory and an
 // asynchronous copy on the caller's stream (no host synchronisation inside a
 // move).  The ring has two halves; when one is full, events record how far the
-// streams that copied out of it are, and it is written again once they have
-// passed (an event per copy would put a barrier packet of 6 us behind each).
+// streams that copied out of it are, and the other is written again once they
+// have passed its events (an event per copy would put a barrier packet of 6 us
+// behind each).
 class PinnedRing {
   public:
     void upload(BufferPtr& dst, const void* src, size_t bytes, hipStream_t s) {
         dst = device_alloc(std::max<size_t>(bytes, 16));
         if (!bytes) return;
-        std::lock_guard<std::mutex> lk(mu_);
-        const size_t need = (bytes + 255) & ~(size_t)255;
-        if (need > kHalf) {   // larger than a half: a synchronous copy
-            HIPCHK(hipStreamSynchronize(s));   // the block's earlier users on this stream
-            HIPCHK(hipMemcpy(dst->ptr, src, bytes, hipMemcpyHostToDevice));
-            return;
+        if (!through_ring(dst->ptr, src, bytes, s)) {   // straight from the caller's memory
+            HIPCHK(hipMemcpyAsync(dst->ptr, src, bytes, hipMemcpyHostToDevice, s));
+            HIPCHK(hipStreamSynchronize(s));
         }
-        if (!host_) HIPCHK(hipHostMalloc((void**)&host_, 2 * kHalf, hipHostMallocDefault));
-        if (head_ + need > kHalf) {
-            leave(half_[cur_]);
-            cur_ ^= 1;
-            head_ = 0;
-            enter(half_[cur_]);
-        }
-        char* p = host_ + cur_ * kHalf + head_;
-        std::memcpy(p, src, bytes);
-        Half& h = half_[cur_];
-        if (std::find(h.used.begin(), h.used.end(), s) == h.used.end()) h.used.push_back(s);
-        HIPCHK(hipMemcpyAsync(dst->ptr, p, bytes, hipMemcpyHostToDevice, s));
-        head_ += need;
     }
 
   private:
     static constexpr size_t kHalf = 2 << 20;
     struct Half {
-        std::vector<hipStream_t> used;   // streams that copy out of it
+        std::vector<hipStream_t> used;   // streams that copied out of it since its last events
         std::vector<hipEvent_t> done;
     };
-    static void leave(Half& h) {
-        for (hipStream_t s : h.used) {
-            hipEvent_t ev = nullptr;
-            HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-            if (hipEventRecord(ev, s) != hipSuccess) {   // the stream no longer exists
-                (void)hipGetLastError();
-                (void)hipEventDestroy(ev);
-                HIPCHK(hipDeviceSynchronize());
-            } else {
-                h.done.push_back(ev);
-            }
-        }
-        h.used.clear();
+    // false: larger than a half, or the halves cannot be turned now
+    bool through_ring(void* dst, const void* src, size_t bytes, hipStream_t s) {
+        const size_t need = (bytes + 255) & ~(size_t)255;
+        if (need > kHalf) return false;
+        std::lock_guard<std::mutex> lk(mu_);
+        if (!host_) HIPCHK(hipHostMalloc((void**)&host_, 2 * kHalf, hipHostMallocDefault));
+        if (head_ + need > kHalf && !turn()) return false;
+        char* p = host_ + cur_ * kHalf + head_;
+        std::memcpy(p, src, bytes);
+        Half& h = half_[cur_];
+        if (std::find(h.used.begin(), h.used.end(), s) == h.used.end()) h.used.push_back(s);
+        head_ += need;
+        HIPCHK(hipMemcpyAsync(dst, p, bytes, hipMemcpyHostToDevice, s));
+        return true;
     }
-    static void enter(Half& h) {
-        for (hipEvent_t ev : h.done) {
-            HIPCHK(hipEventSynchronize(ev));
-            (void)hipEventDestroy(ev);
+    // Makes the other half the current one.  Refused (nothing lost: a later call
+    // goes on from there) while one of the full half's streams is being captured,
+    // since an event recorded then belongs to the graph, and where a wait fails.
+    bool turn() {
+        for (auto& used = half_[cur_].used; !used.empty(); used.pop_back()) {
+            const hipStream_t s = used.back();
+            hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+            if (const hipError_t e = hipStreamIsCapturing(s, &st); e != hipSuccess) {
+                (void)hipGetLastError();
+                if (e == hipErrorStreamCaptureImplicit) return false;   // the null stream while another one is captured
+                if (!succeeded(hipDeviceSynchronize())) return false;   // the stream no longer exists
+                continue;
+            }
+            if (st != hipStreamCaptureStatusNone) return false;
+            hipEvent_t ev = nullptr;
+            if (!succeeded(hipEventCreateWithFlags(&ev, hipEventDisableTiming))) return false;
+            if (!succeeded(hipEventRecord(ev, s))) {
+                (void)hipEventDestroy(ev);
+                return false;
+            }
+            half_[cur_].done.push_back(ev);
         }
-        h.done.clear();
+        for (auto& done = half_[cur_ ^ 1].done; !done.empty(); done.pop_back()) {
+            if (!succeeded(hipEventSynchronize(done.back()))) return false;
+            (void)hipEventDestroy(done.back());
+        }
+        cur_ ^= 1;
+        head_ = 0;
+        return true;
+    }
+    static bool succeeded(hipError_t e) {
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e == hipSuccess;
     }
     std::mutex mu_;
     char* host_ = nullptr;

@@ -49,7 +49,7 @@ Stream null_stream;
 std::vector<Stream*> streams{&null_stream};
 std::map<char*, Range> device, pinned;
 uint64_t launches = 0;
-int hazards = 0, device_syncs = 0;
+int hazards = 0, device_syncs = 0, failing_waits = 0;
 struct {
     dim3 grid, block;
     size_t shared;
@@ -174,6 +174,10 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
 }
 hipError_t hipEventSynchronize(hipEvent_t e) {
     Event* ev = (Event*)e;
+    if (failing_waits > 0) {
+        --failing_waits;
+        return hipErrorUnknown;
+    }
     if (ev->captured) return hipErrorCapturedEvent;
     if (ev->s) ev->s->run(ev->upto);
     return hipSuccess;
@@ -288,5 +292,71 @@ int pool_outlives_its_streams() {
     for (int i = 1; i < 5; ++i)
         if (!is_old(keep[i]->ptr)) return 3;
     return !before ? 4 : device_syncs != syncs + 1 ? 5 : 0;
+}
+
+// Uploads through the ring of pinned memory, more than it holds: what reaches
+// the buffers is what was uploaded, however late the streams run ...
+struct Uploads {
+    std::vector<symten::BufferPtr> buf;
+    void add(Stream* s, int count) {
+        Scope scope(s);
+        for (int i = 0; i < count; ++i) {
+            const std::vector<char> x(300000, (char)(buf.size() + 1));
+            symten::BufferPtr b;
+            symten::upload_async(b, x.data(), x.size(), (hipStream_t)s);
+            buf.push_back(b);
+        }
+    }
+    bool wrong() const {
+        for (size_t i = 0; i < buf.size(); ++i)
+            for (int at : {0, 299999})
+                if (((char*)buf[i]->ptr)[at] != (char)(i + 1)) return true;
+        return false;
+    }
+};
+// ... while a stream that used it is being captured into a graph;
+int ring_beside_a_capture() {
+    Stream *x = new_stream(), *y = new_stream();
+    Uploads u;
+    try {
+        u.add(x, 1);
+        x->capturing = true;
+        u.add(y, 40);
+        x->capturing = false;
+        u.add(y, 40);
+    } catch (...) {
+        return 1;
+    }
+    y->run();
+    x->run();
+    return u.wrong() ? 2 : 0;
+}
+// ... after a wait that failed;
+int ring_after_a_failed_wait() {
+    Stream *x = new_stream(), *y = new_stream();
+    Uploads u;
+    u.add(x, 6);
+    u.add(y, 6);   // both halves are full
+    failing_waits = 1;
+    try {
+        u.add(y, 1);
+    } catch (...) {
+    }
+    failing_waits = 0;
+    u.add(y, 30);
+    y->run();
+    x->run();
+    return u.wrong() ? 1 : 0;
+}
+// ... and after a stream that used it was destroyed.
+int ring_after_a_destroyed_stream() {
+    Stream *x = new_stream(), *y = new_stream();
+    Uploads u;
+    u.add(x, 3);
+    x->alive = false;
+    u.add(y, 30);
+    y->run();
+    x->run();
+    return u.wrong() ? 1 : 0;
 }
 }
