@@ -1314,9 +1314,11 @@ TensorPtr fusion_isometry(const Leg& la, const Leg& lb, int fdir, int dtype, hip
         key << ";";
     }
     key << fdir << "/" << dtype;
-    std::lock_guard<std::mutex> lk(mu);
-    auto it = cache.find(key.str());
-    if (it != cache.end()) return it->second;
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        auto it = cache.find(key.str());
+        if (it != cache.end()) return it->second;
+    }
     // fused multiplets and the position of each (ja, jb) pair inside J
     std::map<int, int> nJ;
     std::map<std::array<int, 3>, int> base;
@@ -1353,8 +1355,8 @@ TensorPtr fusion_isometry(const Leg& la, const Leg& lb, int fdir, int dtype, hip
     }
     F->meta_only = false;
     (void)s;
-    cache[key.str()] = F;
-    return F;
+    std::lock_guard<std::mutex> lk(mu);   // (the upload may wait for the caller's stream)
+    return cache.emplace(key.str(), F).first->second;
 }
 
 // The same tensor with every leg reversed.  A real invariant tensor stays

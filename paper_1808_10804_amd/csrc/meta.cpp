@@ -1469,9 +1469,13 @@ void validate_scatter(const std::vector<GemmGroup>& groups, const std::vector<in
     }
 }
 
+// Device tables of a plan.  They are uploaded outside the lock, since that may
+// wait for the caller's stream; of two threads that meet here the first one's stay.
 static std::shared_ptr<DevPlan> dev_plan(const ContractPlan& p) {
-    std::lock_guard<std::mutex> lk(g_devplan_mu);
-    if (p.dev) return std::static_pointer_cast<DevPlan>(p.dev);
+    {
+        std::lock_guard<std::mutex> lk(g_devplan_mu);
+        if (p.dev) return std::static_pointer_cast<DevPlan>(p.dev);
+    }
     auto d = std::make_shared<DevPlan>();
     std::vector<int64_t> prefix;
     copy_prefix(p.copies, prefix);
@@ -1504,8 +1508,9 @@ static std::shared_ptr<DevPlan> dev_plan(const ContractPlan& p) {
     validate_groups(gg, {pl * p.a_panel_elems, pl * p.b_panel_elems, p.out_elems}, panel_vw(p.prec), pl);
     d->host_groups = gg;
     upload_sync(d->groups, gg.data(), gg.size() * sizeof(GemmGroup));
-    p.dev = d;
-    return d;
+    std::lock_guard<std::mutex> lk(g_devplan_mu);
+    if (!p.dev) p.dev = d;
+    return std::static_pointer_cast<DevPlan>(p.dev);
 }
 
 TensorPtr run_contraction(const ContractPlan& p, const Tensor& A, const Tensor& B, hipStream_t stream) {
@@ -1569,9 +1574,11 @@ std::map<std::vector<const ContractPlan*>, std::shared_ptr<MultiDesc>> g_multi;
 std::shared_ptr<MultiDesc> multi_desc(const std::vector<std::shared_ptr<ContractPlan>>& plans) {
     std::vector<const ContractPlan*> key;
     for (auto& p : plans) key.push_back(p.get());
-    std::lock_guard<std::mutex> lk(g_multi_mu);
-    auto it = g_multi.find(key);
-    if (it != g_multi.end()) return it->second;
+    {
+        std::lock_guard<std::mutex> lk(g_multi_mu);
+        auto it = g_multi.find(key);
+        if (it != g_multi.end()) return it->second;
+    }
     const int n = (int)plans.size();
     auto d = std::make_shared<MultiDesc>();
     d->plans = plans;
@@ -1622,6 +1629,9 @@ std::shared_ptr<MultiDesc> multi_desc(const std::vector<std::shared_ptr<Contract
     upload_sync(d->tasks, d->host_tasks.data(), d->host_tasks.size() * sizeof(CopyTask));
     upload_sync(d->prefix, prefix.data(), prefix.size() * sizeof(int64_t));
     upload_sync(d->groups, d->host_groups.data(), d->host_groups.size() * sizeof(GemmGroup));
+    std::lock_guard<std::mutex> lk(g_multi_mu);   // (the uploads above may wait for the caller's stream)
+    auto it = g_multi.find(key);
+    if (it != g_multi.end()) return it->second;
     if (g_multi.size() > 256) g_multi.clear();
     g_multi[key] = d;
     return d;

@@ -49,6 +49,7 @@ Stream null_stream;
 std::vector<Stream*> streams{&null_stream};
 std::map<char*, Range> device, pinned;
 uint64_t launches = 0;
+void (*during_sync)() = nullptr;   // called once, from inside the next hipStreamSynchronize
 int hazards = 0, device_syncs = 0, failing_waits = 0;
 struct {
     dim3 grid, block;
@@ -97,6 +98,7 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned);
 
 // ------------------------------------------------------------- for the tests
 int fake_hazards() { return hazards; }
+void fake_during_sync(void (*call)()) { during_sync = call; }
 void* fake_stream() {
     hipStream_t s;
     (void)hipStreamCreateWithFlags(&s, 0);
@@ -149,6 +151,10 @@ hipError_t hipStreamDestroy(hipStream_t s) { S(s)->alive = false; return hipSucc
 hipError_t hipStreamSynchronize(hipStream_t s) {
     if (!S(s)->alive) return hipErrorContextIsDestroyed;
     if (S(s)->capturing) return hipErrorStreamCaptureUnsupported;
+    if (auto* call = during_sync) {
+        during_sync = nullptr;
+        call();
+    }
     S(s)->run();
     return hipSuccess;
 }

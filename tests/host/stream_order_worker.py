@@ -2,6 +2,7 @@
 GPU (fake_hip.cpp) preloaded; exits with 0 if it holds."""
 import ctypes as C
 import sys
+import threading
 
 sys.modules["torch"] = None   # its import would bring a HIP runtime of its own
 import numpy as np            # noqa: E402
@@ -44,6 +45,38 @@ def su2_move():
             env.move(a, 12, prec="f64", stream=S)
         except st.SymtenError as e:
             print(e)
+
+
+def _matrices(n, seed):
+    ts = [st.Tensor.create([({0: n}, 1), ({0: n}, -1)], 0, "f64") for _ in range(2)]
+    return [t.upload(np.random.default_rng(seed + i).standard_normal(n * n)) for i, t in enumerate(ts)]
+
+
+def new_plan_beside_another_thread():
+    """While a contraction seen for the first time waits for its stream before
+    it writes its tables, one of another thread and stream goes through."""
+    A, B = _matrices(20, 1)
+    X, Y = _matrices(21, 3)
+    other = fake.fake_stream()
+    for _ in range(3):
+        st.contract(X, Y, [1], [0], prec="f64", stream=other)
+        st.contract(X, Y, [1], [0], prec="f64", stream=S)   # leaves used blocks to S
+    through = []
+
+    def elsewhere():
+        st.contract(X, Y, [1], [0], prec="f64", stream=other)
+        st.sync(other)
+
+    @C.CFUNCTYPE(None)
+    def meanwhile():
+        t = threading.Thread(target=elsewhere, daemon=True)
+        t.start()
+        t.join(5)
+        through.append(not t.is_alive())
+
+    fake.fake_during_sync(meanwhile)
+    st.contract(A, B, [1], [0], prec="f64", stream=S)
+    assert through == [True], through
 
 
 if __name__ == "__main__":

@@ -28,7 +28,7 @@ def runtime(tmp_path_factory):
 
 @pytest.mark.parametrize("scenario", [
     "su2_double_layer", "su2_move", "pool_waits_for_the_release", "pool_waits_for_the_mark", "pool_outlives_its_streams",
-    "ring_beside_a_capture", "ring_after_a_failed_wait", "ring_after_a_destroyed_stream"])
+    "ring_beside_a_capture", "ring_after_a_failed_wait", "ring_after_a_destroyed_stream", "new_plan_beside_another_thread"])
 def test_stream_order(runtime, scenario):
     env = dict(os.environ, SYMTEN_AUTOTUNE="0", PYTHONPATH=ROOT)
     env["LD_PRELOAD"] = " ".join(p for p in (runtime, env.get("LD_PRELOAD", "")) if p)
