@@ -1330,7 +1330,12 @@ __global__ __launch_bounds__(128) void twist_kernel(const VecJob* __restrict__ j
             const double up = __shfl_up(before, o, 64);
             if (lane >= o) before *= up;
         }
-        for (int f = f0; f < f1; ++f) {
+        // (the product of a run by itself may overflow where the vector's
+        // entries do not, with couplings far below rounding: then one lane
+        // multiplies in order)
+        const bool scanned = !__any(!isfinite(before));
+        if (!scanned) before = 1.0;
+        for (int f = scanned ? f0 : 0, end = scanned ? f1 : (lane == 0 ? len : 0); f < end; ++f) {
             before *= z[r + step * (f + 1)];
             z[r + step * (f + 1)] = before;
         }

@@ -1,0 +1,38 @@
+"""The eigensolver on matrices that the random ones of the other tests do not
+resemble; eigenvalues, residuals and orthogonality with the bound of those
+tests, 1e-13 relative to max |lambda|."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1808_10804_amd as st
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-13
+
+
+def _solve(m, k):
+    w, Z = (x.cpu().numpy() for x in st.eigh([torch.from_numpy(m).to("cuda")], [k])[0])
+    ref = np.linalg.eigvalsh(m)
+    scale = np.max(np.abs(ref))
+    assert np.max(np.abs(w - ref)) <= TOL * scale
+    assert np.all(np.isfinite(Z))
+    return w, Z, scale
+
+
+@pytest.mark.parametrize("weakest", [20, 30, 40, 60])
+def test_couplings_below_rounding(weakest):
+    """Tridiagonal matrices of small integers whose parts are coupled by numbers
+    far below rounding: the ratios of neighbouring entries of a vector reach
+    1e+-200, and their products over parts of it leave the range of FP64 where
+    the entries do not."""
+    for seed in range(60):
+        rng = np.random.default_rng(seed)
+        n = int(rng.integers(40, 120)) * 2 + 1
+        d = np.round(rng.standard_normal(n))
+        e = np.ones(n - 1)
+        weak = rng.random(n - 1) < 0.5
+        e[weak] = 10.0 ** -rng.uniform(weakest / 2, weakest, int(weak.sum()))
+        print(f"seed = {seed}, n = {n}", flush=True)
+        _solve(np.diag(d) + np.diag(e, 1) + np.diag(e, -1), n)
