@@ -1026,7 +1026,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 struct BisJob {
     const double *d, *e, *e2, *scale;
     double* w;      // n eigenvalues, ascending, unscaled
-    double* range;  // lower end, upper end and norm of the spectrum's interval
+    double* range;  // lower end, upper end and norm (NaN: T is not finite) of the spectrum's interval
     int* count;     // eigenvalues below grid points 1 .. points of the interval
     int n, points;
     int half;       // > 0: spectrum +-, the `half` largest are found, the rest mirrored or zero
@@ -1095,18 +1095,20 @@ __global__ __launch_bounds__(kEigThreads) void bisect_grid_kernel(const BisJob* 
     const int n = J.n;
     __shared__ double red[kEigWaves];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double lo = INFINITY, hi = -INFINITY;
+    double lo = INFINITY, hi = -INFINITY, bad = 0.0;
     for (int i = tid; i < n; i += kEigThreads) {
         const double di = J.d[i];
         const double el = i > 0 ? fabs(J.e[i - 1]) : 0.0, er = i + 1 < n ? fabs(J.e[i]) : 0.0;
         lo = fmin(lo, di - el - er);
         hi = fmax(hi, di + el + er);
+        if (!isfinite(di + el + er)) bad = 1.0;
     }
     // (block_max is a maximum of values >= 0: of the distances from an entry)
     const double d0 = J.d[0];
     lo = d0 - block_max<kEigWaves>(d0 - fmin(lo, d0), red);
     hi = d0 + block_max<kEigWaves>(fmax(hi, d0) - d0, red);
-    const double tnorm = fmax(fabs(lo), fabs(hi));
+    // NaN or Inf in the matrix: no counts, NaN for every eigenvalue
+    const double tnorm = block_max<kEigWaves>(bad, red) > 0.0 ? NAN : fmax(fabs(lo), fabs(hi));
     lo -= 4.0 * DBL_EPSILON * tnorm * n;
     hi += 4.0 * DBL_EPSILON * tnorm * n;
     const int t = (bm.y + wave) * 64 + lane;
@@ -1133,8 +1135,8 @@ __global__ __launch_bounds__(kEigThreads) void bisect_kernel(const BisJob* __res
     const double eps = DBL_EPSILON;
     const bool mirror = J.half > 0;
     double a = lo, b = hi;
-    if (!(tnorm > 0.0)) {   // T = 0
-        a = b = 0.0;
+    if (!(tnorm > 0.0)) {   // T = 0, or not finite
+        a = b = tnorm;
     } else {
         // first grid point with more than j eigenvalues below it
         int first = 0, len = J.points;

@@ -36,3 +36,23 @@ def test_couplings_below_rounding(weakest):
         e[weak] = 10.0 ** -rng.uniform(weakest / 2, weakest, int(weak.sum()))
         print(f"seed = {seed}, n = {n}", flush=True)
         _solve(np.diag(d) + np.diag(e, 1) + np.diag(e, -1), n)
+
+
+@pytest.mark.parametrize("n", [1, 2, 65, 129, 400, 800])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("where", ["corner", "inside", "all"])
+def test_not_finite(n, value, where):
+    """No eigenvalue comes out of a matrix with NaN or Inf in it as a number;
+    matrices solved beside it are not touched by it."""
+    rng = np.random.default_rng(n)
+    m = rng.standard_normal((n, n))
+    m = m + m.T
+    good = m.copy()
+    i, j = {"corner": (0, 0), "inside": (n // 2, n // 3), "all": (slice(None), slice(None))}[where]
+    m[i, j] = m[j, i] = value
+    print(f"n = {n}", flush=True)
+    (w, _), (v, Z) = st.eigh([torch.from_numpy(x).to("cuda") for x in (m, good)], [0, 1])
+    assert not np.any(np.isfinite(w.cpu().numpy()))
+    ref = np.linalg.eigvalsh(good)
+    assert np.max(np.abs(v.cpu().numpy() - ref)) <= TOL * np.max(np.abs(ref))
+    assert np.all(np.isfinite(Z.cpu().numpy()))
