@@ -1519,48 +1519,38 @@ __global__ __launch_bounds__(64) void cluster_kernel(const VecJob* __restrict__ 
 
 // Vectors of eigenvalues a gap g ||T|| apart are orthogonal to about eps / g,
 // 2e-13 at the 1e-3 where clusters end: each gives up half of its product with
-// the kNear vectors on either side of it that are less than 1e-2 ||T|| away
-// (all products before any change), which leaves them orthogonal to rounding.
-constexpr int kNear = 3;
+// every other kept vector that is less than 1e-2 ||T|| away (all products
+// before any change), which leaves them orthogonal to rounding.  Those vectors
+// are a run of ranks lo .. hi-1 around its own.  (Three neighbours on either
+// side are not enough beside a multiplet: 4.7e-13 at order 200, now 1e-14;
+// 12.5 -> 13.2 us in the FP32 move at D = 6, chi = 64, 19 -> 21 us in FP64.)  A
+// wave takes a product, the products wait in LDS (kv doubles, dynamic), then
+// every thread subtracts at its own entries.
 __global__ __launch_bounds__(kEigThreads) void polish_kernel(const VecJob* __restrict__ jobs,
                                                               const int2* __restrict__ bmap) {
     const int2 bm = bmap[blockIdx.x];
     const VecJob J = jobs[bm.x];
     const int n = J.n, jr = bm.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    __shared__ double red[2 * kNear][kEigWaves];
+    extern __shared__ double dot[];
     const double near = 1e-2 * fmax(fabs(J.w[0]), fabs(J.w[n - 1])), wj = J.w[n - 1 - jr];
+    auto is_near = [&](int i) { return i >= 0 && i < J.kv && fabs(J.w[n - 1 - i] - wj) < near; };
+    int lo = jr, hi = jr + 1;
+    for (int c = 64; c == 64; lo -= c) c = __popcll(__ballot(is_near(lo - 1 - lane)));
+    for (int c = 64; c == 64; hi += c) c = __popcll(__ballot(is_near(hi + lane)));
     const double* z = J.Zt + (size_t)jr * n;
-    const double* y[2 * kNear];
-    double dot[2 * kNear];
-#pragma unroll
-    for (int q = 0; q < 2 * kNear; ++q) {
-        const int i = jr + (q < kNear ? q - kNear : q - kNear + 1);
-        y[q] = i >= 0 && i < J.kv && fabs(J.w[n - 1 - i] - wj) < near ? J.Zt + (size_t)i * n : nullptr;
-        dot[q] = 0.0;
-    }
-    for (int r = tid; r < n; r += kEigThreads) {
-        const double x = z[r];
-#pragma unroll
-        for (int q = 0; q < 2 * kNear; ++q)
-            if (y[q]) dot[q] = fma(y[q][r], x, dot[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < 2 * kNear; ++q) {
-        const double t = wave_sum(dot[q]);
-        if (lane == 0) red[q][wave] = t;
+    for (int i = lo + wave; i < hi; i += kEigWaves) {
+        const double* y = J.Zt + (size_t)i * n;
+        double part = 0.0;
+        for (int r = lane; r < n; r += 64) part = fma(y[r], z[r], part);
+        part = wave_sum(part);
+        if (lane == 0) dot[i - lo] = i == jr ? 0.0 : 0.5 * part;
     }
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 2 * kNear; ++q) {
-        dot[q] = 0.0;
-#pragma unroll
-        for (int u = 0; u < kEigWaves; ++u) dot[q] += red[q][u];
-    }
     for (int r = tid; r < n; r += kEigThreads) {
+        const double* y = J.Zt + (size_t)lo * n + r;
         double x = z[r];
-#pragma unroll
-        for (int q = 0; q < 2 * kNear; ++q)
-            if (y[q]) x = fma(-0.5 * dot[q], y[q][r], x);
+#pragma unroll 4
+        for (int i = 0; i < hi - lo; ++i) x = fma(-dot[i], y[(size_t)i * n], x);
         J.Zp[(size_t)jr * n + r] = x;
     }
 }
@@ -2024,7 +2014,7 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
     // clusters of close eigenvalues (descending), from the host copy of w
     std::vector<VecCluster> cl;
     size_t ztot = 0, worktot = 0;
-    int nvec = 0, nmax = 0, ncmax = 0;
+    int nvec = 0, nmax = 0, ncmax = 0, kmax = 0;
     for (int p = 0; p < np; ++p) {
         const int n = wk.probs[p].n, k = kv[p];
         if (k < 0 || k > n) fail(SYMTEN_E_INVAL, "eigh_vectors: vector count out of range");
@@ -2034,6 +2024,7 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
         const double ortol = 1e-3 * tn;
         nvec += k;
         nmax = std::max(nmax, n);
+        kmax = std::max(kmax, k);
         int j = 0;
         while (j < k) {
             int c = 1;
@@ -2110,7 +2101,7 @@ void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<do
             HIPCHK(hipGetLastError());
         });
     profile_launch("eigh_polish", 0, 0, 0, s, [&] {
-        hipLaunchKernelGGL(polish_kernel, dim3((unsigned)nvec), dim3(kEigThreads), 0, s, dvj, dmap);
+        hipLaunchKernelGGL(polish_kernel, dim3((unsigned)nvec), dim3(kEigThreads), 8 * (size_t)kmax, s, dvj, dmap);
         HIPCHK(hipGetLastError());
     });
     int64_t bflops = 0;   // back-transformation: 2 n^2 per vector

@@ -56,3 +56,25 @@ def test_not_finite(n, value, where):
     ref = np.linalg.eigvalsh(good)
     assert np.max(np.abs(v.cpu().numpy() - ref)) <= TOL * np.max(np.abs(ref))
     assert np.all(np.isfinite(Z.cpu().numpy()))
+
+
+@pytest.mark.parametrize("n", [200, 700, 1100])
+@pytest.mark.parametrize("count,gap", [(10, 1.05e-3), (40, 1.1e-3)])
+def test_values_beside_a_multiplet(n, count, gap):
+    """Multiplets of `count` equal eigenvalues, each with single ones `gap`
+    ||T|| away on both sides, just beyond where close values are taken for a
+    cluster: their vectors are orthogonal to every member of the multiplet."""
+    for seed in range(6):
+        rng = np.random.default_rng(n + count + 1000 * seed)
+        q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+        top = []
+        for g in range(3):
+            c = 1.0 - 4 * gap * g
+            top += [c] + [c - gap] * count + [c - 2 * gap]
+        m = (q * np.concatenate([top, 0.5 * rng.random(n - len(top))])) @ q.T
+        m = 0.5 * (m + m.T)
+        k = len(top)
+        print(f"n = {n}, seed = {seed}", flush=True)
+        w, Z, scale = _solve(m, k)
+        assert np.max(np.linalg.norm(m @ Z - Z * w[::-1][:k], axis=0)) <= TOL * scale
+        assert np.max(np.abs(Z.T @ Z - np.eye(k))) <= TOL
