@@ -836,10 +836,11 @@ void solve_class(const std::vector<CutSector>& secs, std::vector<ProjWork>& w, c
 }
 
 // The library's own eigensolver (every eigenproblem of the given cuts fits
-// its LDS): per sector, H_u^T and H_d^T as FP64 col-major blocks, Y = H_u^T
-// H_d (ru x rd, compact) and, but in FP64 moves, its Gram matrix; then one set
-// of launches reduces every matrix of every cut and finds all eigenvalues, and each sector's singular values are taken from them.
-// Everything is enqueued on s; no host thread, no side stream.
+// it): per sector, H_u^T and H_d^T as FP64 col-major blocks, Y = H_u^T H_d (ru x
+// rd, compact) and, but in FP64 moves, its Gram matrix; then one set of launches
+// reduces every matrix of every cut and finds all eigenvalues, and each sector's
+// singular values are taken from them.  Everything is enqueued on s; no host
+// thread, no side stream.
 std::vector<ProjPending> issue_solves_own(ctm_env* env, const std::vector<std::vector<CutSector>*>& cuts, bool f64,
                                           hipStream_t s) {
     rb_check(rocblas_set_stream(env->rb, s), "rocblas_set_stream");
@@ -1104,7 +1105,7 @@ ProjOut finish_projectors(ctm_env* env, std::vector<CutSector>& secs, ProjPendin
             for (size_t i = 0; i < secs.size(); ++i) {
                 bad[i] = head[0];
                 if (head[1 + i])
-                    fail(SYMTEN_E_HIP, "ctm_move: the workgroups of an eigensolve did not meet at a barrier");
+                    fail(SYMTEN_E_HIP, "ctm_move: the workgroups of an eigensolve did not meet");
                 w_host[i].assign(area + pend.w_off[i], area + pend.w_off[i] + pend.w[i].ne);
                 std::copy(area + pend.s_off[i], area + pend.s_off[i] + secs[i].mn, out.sv.begin() + sv_off[i]);
             }

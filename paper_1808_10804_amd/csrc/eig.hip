@@ -2003,7 +2003,7 @@ void eigh_status(const EighWork& wk, hipStream_t s) {
     HIPCHK(hipMemcpyAsync(st.data(), wk.status, sizeof(int) * np, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     for (int v : st)
-        if (v) fail(SYMTEN_E_HIP, "eigh: the workgroups of a tridiagonalisation did not meet at a barrier");
+        if (v) fail(SYMTEN_E_HIP, "eigh: the workgroups of a tridiagonalisation did not meet");
 }
 
 void eigh_vectors(EighWork& wk, const std::vector<int>& kv, const std::vector<double*>& Z,

@@ -365,4 +365,19 @@ int ring_after_a_destroyed_stream() {
     x->run();
     return u.wrong() ? 1 : 0;
 }
+
+// What the library's own eigensolver holds on 256 compute units with 160 KB of
+// LDS: orders up to 3328; of Jordan-Wielandt matrices sides up to 2048 and
+// 3993 in all.
+int eigensolver_capacity() {
+    if (!symten::eigh_fits(3328) || symten::eigh_fits(3329) || symten::eigh_max_order() != 3328) return 1;
+    const struct {
+        int ru, rd;
+        bool fits;
+    } jw[] = {{1, 1, true},       {1996, 1996, true},  {1997, 1997, false}, {1996, 1997, true}, {2048, 1945, true},
+              {2048, 1946, false}, {1945, 2048, true}, {2049, 1, false},    {1, 2049, false},   {0, 5, false}};
+    for (auto& x : jw)
+        if (symten::eigh_jw_fits(x.ru, x.rd) != x.fits) return 2;
+    return 0;
+}
 }

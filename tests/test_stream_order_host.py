@@ -30,8 +30,17 @@ def runtime(tmp_path_factory):
     "su2_double_layer", "su2_move", "pool_waits_for_the_release", "pool_waits_for_the_mark", "pool_outlives_its_streams",
     "ring_beside_a_capture", "ring_after_a_failed_wait", "ring_after_a_destroyed_stream", "new_plan_beside_another_thread"])
 def test_stream_order(runtime, scenario):
+    _run(runtime, scenario)
+
+
+def _run(runtime, scenario):
     env = dict(os.environ, SYMTEN_AUTOTUNE="0", PYTHONPATH=ROOT)
     env["LD_PRELOAD"] = " ".join(p for p in (runtime, env.get("LD_PRELOAD", "")) if p)
     r = subprocess.run([sys.executable, os.path.join(HOST, "stream_order_worker.py"), scenario], cwd=ROOT, env=env,
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-3000:]
+
+
+def test_eigensolver_capacity(runtime):
+    """The orders and sides that the library's own eigensolver takes."""
+    _run(runtime, "eigensolver_capacity")
