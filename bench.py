@@ -97,8 +97,10 @@ def profile_name(rocprof_name):
         kind = {"1": "bf16", "2": "bf16x3", "3": "bf16x6"}.get(tail[0], tail[0]) if tail else "?"
         scatter = ",scatter" if len(tail) > 1 and tail[1] == "true" else ""
         return "gemm_bf16_kernel<%sx%sx%s,%s%s>" % (t.groups() + (kind, scatter))
-    src = "f64" if "double" in args else "f32"
-    dst = {"0": "f32", "1": "f64", "2": "bf16", "3": "bf16x2", "4": "acc", "5": "bf16x3"}.get(last, last)
+    # source type, destination kind (then the chunks a workgroup takes)
+    src, kind = re.search(r"(double|float), *(\d+)", args).groups()
+    src = "f64" if src == "double" else "f32"
+    dst = {"0": "f32", "1": "f64", "2": "bf16", "3": "bf16x2", "4": "acc", "5": "bf16x3"}.get(kind, kind)
     return "copy_kernel<%s,%s>" % (src, dst)
 
 
