@@ -119,10 +119,12 @@ def write_traffic(base, workload, command, out=None):
             name = profile_name(r["kernel"])
             if name is None or r["counter"] != c:
                 continue
-            k = kern.setdefault(name, {})
-            k[c.lower() + "_kib_per_dispatch"] = r["avg_per_dispatch"]
-            k[c.lower() + "_dispatches"] = r["dispatches"]
-            k[("fetch" if c == "FETCH_SIZE" else "write") + "_bytes_per_launch"] = r["avg_per_dispatch"] * 1024.0 / cal[c]
+            # instantiations of one name: the average over all their dispatches
+            k, kib, n = kern.setdefault(name, {}), c.lower() + "_kib_per_dispatch", c.lower() + "_dispatches"
+            was = k.get(n, 0)
+            k[kib] = (k.get(kib, 0.0) * was + r["avg_per_dispatch"] * r["dispatches"]) / (was + r["dispatches"])
+            k[n] = was + r["dispatches"]
+            k[("fetch" if c == "FETCH_SIZE" else "write") + "_bytes_per_launch"] = k[kib] * 1024.0 / cal[c]
     for k in kern.values():
         if "fetch_bytes_per_launch" in k and "write_bytes_per_launch" in k:
             k["bytes_per_launch"] = k["fetch_bytes_per_launch"] + k["write_bytes_per_launch"]
