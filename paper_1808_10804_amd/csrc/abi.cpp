@@ -2679,7 +2679,10 @@ int symten_enlarged_corners_batched(int n, symten_t* out, const symten_t* Cs, co
             build_step(st->step[2], A3, B3, n, fuse, false);
             if (fuse) fuse_steps(st->step[1], A2, B2, st->step[2], n);
             std::lock_guard<std::mutex> lk(g_batch_mu);
-            if (g_batch.size() > 16) g_batch.clear();
+            if (g_batch.size() > 16) {
+                HIPCHK(hipDeviceSynchronize());   // batches in flight on any stream still use their buffers
+                g_batch.clear();
+            }
             g_batch[key] = st;
         }
         if (st->inputs != inputs) {

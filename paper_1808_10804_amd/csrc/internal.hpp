@@ -69,7 +69,8 @@ hipStream_t call_stream();
 // the releasing thread, else the stream the block was allocated on.  Handing
 // the block to a call on another stream makes that stream wait for the first
 // one's work before the release (and for what few calls queued after it), so
-// work queued on two streams never shares a block.
+// work queued on two streams never shares a block.  Tables kept for calls on
+// any stream (upload_sync) are given out again after a wait for the device.
 struct DeviceBuffer;
 using BufferPtr = std::shared_ptr<DeviceBuffer>;
 BufferPtr device_alloc(size_t bytes);
@@ -89,6 +90,7 @@ struct DeviceBuffer {
     void* user_ctx = nullptr;
     uint64_t user_gen = 0;  // registration that made it; a later one leaks it
     bool used = true;       // work queued earlier may still touch the block
+    bool table = false;     // read by calls on any stream: idle once the device has been waited for
     ~DeviceBuffer();
 };
 // Caller-registered device allocator (null fns: the library's own pool).

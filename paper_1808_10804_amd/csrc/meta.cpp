@@ -92,11 +92,15 @@ struct StreamReleases {
     uint64_t count = 0;
     std::deque<std::pair<uint64_t, hipEvent_t>> marks;   // (releases before it, event), ascending
 };
+// Tables that calls on any stream read (plans, evicted by a call on one of them)
+// wait apart until the device has been waited for, once for kTables of them.
+constexpr size_t kTables = 256, kTableBytes = 64 << 20;
 struct Pool {
     std::mutex mu;
     std::multimap<size_t, FreeBlock> free_;   // capacity -> block
     std::map<hipStream_t, StreamReleases> streams;
-    size_t held = 0;
+    std::vector<std::pair<size_t, void*>> tables;
+    size_t table_bytes = 0, held = 0;
 };
 enum class Order { Done, Refused, Gone };
 // An event behind everything released on stream s so far.  Refused while the
@@ -124,12 +128,15 @@ Order mark_stream(StreamReleases& r, hipStream_t s) {
     r.marks.emplace_back(r.count, ev);
     return Order::Done;
 }
+bool is_captured(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
 // Stream cur waits for the work queued on the block's stream before its release.
 Order order_after(Pool& P, hipStream_t cur, const FreeBlock& fb) {   // under P.mu
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    // a captured call may not wait for work outside of its graph
-    if (hipStreamIsCapturing(cur, &st) != hipSuccess) (void)hipGetLastError();
-    else if (st != hipStreamCaptureStatusNone) return Order::Refused;
+    if (is_captured(cur)) return Order::Refused;   // a captured call may not wait for work outside of its graph
     StreamReleases& r = P.streams[fb.stream];
     if (r.marks.empty() || r.marks.back().first < fb.seq)
         if (const Order o = mark_stream(r, fb.stream); o != Order::Done) return o;
@@ -169,6 +176,25 @@ bool retire_stream(Pool& P, hipStream_t s, std::unique_lock<std::mutex>& lk) {
         P.free_.emplace(b);
     }
     return idle;
+}
+// Released tables become free for any stream, in the same way.
+void recycle_tables(Pool& P, std::unique_lock<std::mutex>& lk) {
+    std::vector<std::pair<size_t, void*>> mine;
+    mine.swap(P.tables);
+    P.table_bytes = 0;
+    lk.unlock();
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
+    if (!idle) (void)hipGetLastError();
+    lk.lock();
+    for (auto& t : mine) {
+        if (idle) {
+            P.free_.emplace(t.first, FreeBlock{t.second, nullptr, 0});
+            P.held += t.first;
+        } else {
+            P.tables.push_back(t);
+            P.table_bytes += t.first;
+        }
+    }
 }
 Pool& pool() {
     static Pool* p = new Pool();   // leaked on purpose: buffers may outlive statics
@@ -238,6 +264,7 @@ BufferPtr device_alloc(size_t bytes) {
     {
         Pool& P = pool();
         std::unique_lock<std::mutex> lk(P.mu);
+        if ((P.tables.size() >= kTables || P.table_bytes >= kTableBytes) && !is_captured(cur)) recycle_tables(P, lk);
         for (bool again = true; again;) {
             again = false;
             // an idle block or one of this stream if there is one, else one of another stream
@@ -275,6 +302,9 @@ BufferPtr device_alloc(size_t bytes) {
             (void)hipDeviceSynchronize();
             for (auto& kv : P.free_) (void)hipFree(kv.second.ptr);
             P.free_.clear();
+            for (auto& t : P.tables) (void)hipFree(t.second);
+            P.tables.clear();
+            P.table_bytes = 0;
             P.held = 0;
         }
         e = hipMalloc(&p, cap);
@@ -304,6 +334,11 @@ DeviceBuffer::~DeviceBuffer() {
     const hipStream_t rs = call_stream_set() ? call_stream() : stream;
     Pool& P = pool();
     std::lock_guard<std::mutex> lk(P.mu);
+    if (table) {
+        P.tables.emplace_back(cap, ptr);
+        P.table_bytes += cap;
+        return;
+    }
     StreamReleases& r = P.streams[rs];
     P.free_.emplace(cap, FreeBlock{ptr, rs, ++r.count});
     P.held += cap;
@@ -957,6 +992,7 @@ std::mutex g_devplan_mu;
 
 void upload_sync(BufferPtr& buf, const void* host, size_t bytes) {
     buf = device_alloc(bytes);
+    buf->table = true;
     if (!bytes) return;
     if (buf->used) HIPCHK(hipStreamSynchronize(call_stream()));
     HIPCHK(hipMemcpy(buf->ptr, host, bytes, hipMemcpyHostToDevice));

@@ -15,6 +15,7 @@
 #include <rocblas/rocblas.h>
 #include <rocsolver/rocsolver.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -366,6 +367,40 @@ int ring_after_a_destroyed_stream() {
     return u.wrong() ? 1 : 0;
 }
 
+// A table that calls on several streams read, dropped by a call on one of them:
+// its block is not written again while work queued on another stream reads it.
+int tables_outlive_their_readers() {
+    Stream *a = new_stream(), *b = new_stream();
+    const std::vector<int> x(3000, 7), y(3000, 8);
+    symten::BufferPtr table, others[8];
+    {
+        Scope scope(a);
+        symten::upload_sync(table, x.data(), 4 * x.size());
+    }
+    int read = 0;
+    const int* p = (const int*)table->ptr;
+    a->ops.push_back([&read, p] { read = p[2999]; });
+    {
+        Scope scope(b);
+        table.reset();
+        for (auto& o : others) symten::upload_sync(o, y.data(), 4 * y.size());
+    }
+    a->run();
+    return read != 7;
+}
+// ... and tables that come and go take a bounded number of blocks.
+int tables_are_given_back() {
+    Stream* a = new_stream();
+    Scope scope(a);
+    const std::vector<int> x(3000, 7);
+    std::vector<void*> seen;
+    for (int i = 0; i < 3000; ++i) {
+        symten::BufferPtr t;
+        symten::upload_sync(t, x.data(), 4 * x.size());
+        if (std::find(seen.begin(), seen.end(), t->ptr) == seen.end()) seen.push_back(t->ptr);
+    }
+    return seen.size() > 600;
+}
 // What the library's own eigensolver holds on 256 compute units with 160 KB of
 // LDS: orders up to 3328; of Jordan-Wielandt matrices sides up to 2048 and
 // 3993 in all.

@@ -28,7 +28,8 @@ def runtime(tmp_path_factory):
 
 @pytest.mark.parametrize("scenario", [
     "su2_double_layer", "su2_move", "pool_waits_for_the_release", "pool_waits_for_the_mark", "pool_outlives_its_streams",
-    "ring_beside_a_capture", "ring_after_a_failed_wait", "ring_after_a_destroyed_stream", "new_plan_beside_another_thread"])
+    "ring_beside_a_capture", "ring_after_a_failed_wait", "ring_after_a_destroyed_stream", "new_plan_beside_another_thread",
+    "tables_outlive_their_readers", "tables_are_given_back"])
 def test_stream_order(runtime, scenario):
     _run(runtime, scenario)
 
